@@ -44,31 +44,11 @@ PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16x3": 2500.0, "bf16": 2500.0}
 # stands, keyed by (workload, parity, precision, tile rows, split-K, k-stage), with the
 # profile summary that holds the pass; a launch configuration without a recorded pass
 # reports null.
-TRAFFIC_KIB = {
-    ("planar-hs-32v-100cells-8cases", 2, "fp64", 64, 3, 32):
-        (1116445.9 * 2.0, 155136.0, "profiles/gemm_f64_planar-hs-32v-808cells-parity.md"),
-    ("planar-hs-32v-100cells-8cases", 2, "fp64", 64, 4, 16):
-        (1546552.0 * 2.0, 206848.0, "profiles/gemm_f64_planar-hs-32v-808cells-parity.md"),
-    ("planar-hs-32v-100cells-8cases", 2, "fp64", 128, 4, 16):
-        (1142963.6 * 2.0, 206848.0, "profiles/gemm_f64_planar-hs-32v-808cells-parity.md"),
-    ("duct-ipl081-24v-64x64-6cases", 1, "fp64", 128, 1, 16):
-        (19409697.6 * 2.0, 1327104.0, "profiles/gemm_f64_duct-ipl-24v-64x64-6cases.md"),
-    ("duct-ipl081-24v-64x64-6cases", 1, "bf16x3", 256, 1, 32):
-        (3697812.8 * 2.0, 1327104.0, "profiles/gemm_bf16x3_duct-ipl-24v-64x64-6cases_planar-hs-32v-808cells.md"),
-    ("duct-ipl081-24v-64x64-6cases", 1, "bf16x3", 256, 2, 32):
-        (3711624.7 * 2.0, 2654208.0, "profiles/gemm_bf16x3_duct-ipl-24v-64x64-6cases_planar-hs-32v-808cells.md"),
-    ("planar-hs-32v-100cells-8cases", 2, "bf16x3", 256, 2, 32):
-        (239174.1 * 2.0, 103424.0, "profiles/gemm_bf16x3_duct-ipl-24v-64x64-6cases_planar-hs-32v-808cells.md")}
+TRAFFIC_KIB = {}
 # MFMA pipe utilisation of the same configuration from its counter pass:
 # SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE per XCD x 1024 SIMDs), and the shader clock
 # the kernel ran at (GRBM_GUI_ACTIVE per XCD / kernel duration).
-MFMA_BUSY = {("planar-hs-32v-100cells-8cases", 2, "fp64", 64, 3, 32): (0.779, 2.22),
-             ("planar-hs-32v-100cells-8cases", 2, "fp64", 64, 4, 16): (0.788, 2.09),
-             ("planar-hs-32v-100cells-8cases", 2, "fp64", 128, 4, 16): (0.927, 2.08),
-             ("duct-ipl081-24v-64x64-6cases", 1, "fp64", 128, 1, 16): (0.932, 2.33),
-             ("duct-ipl081-24v-64x64-6cases", 1, "bf16x3", 256, 1, 32): (0.678, 2.28),
-             ("duct-ipl081-24v-64x64-6cases", 1, "bf16x3", 256, 2, 32): (0.686, 1.87),
-             ("planar-hs-32v-100cells-8cases", 2, "bf16x3", 256, 2, 32): (0.689, 2.09)}
+MFMA_BUSY = {}
 HBM_GBS = 8000.0
 # worker processes of the CPU baseline: the host's cores, at most the 16 that a
 # one-GPU share of the box holds
@@ -249,6 +229,13 @@ def build_workload(key, args):
                 info=info, geom=geom, per_case=per_case, t_plan=t_plan, t_geom=t_geom, diff_info=diff_info)
 
 
+def classes(W):
+    """Reflection classes of the stored velocities: the contraction has a matrix for each."""
+    if W["tube"]:
+        return 2 if W["w"]["polar"]["n_th"] % 2 == 0 else 1
+    return {0: 8, 1: 4, 2: 2}[W["parity"]]
+
+
 def stored_h(W, nc):
     """Smooth synthetic distributions of the workload, restricted to the stored parity half."""
     import numpy as np
@@ -307,8 +294,8 @@ def contraction_roofline(W, precision, reps):
     plan.timing(False)
     tile_rows, splits, tuned, k_stage = plan.contraction_config(nc, precision, with_depth=True)
     avg_ms = gemm_ms / launches
-    flops = 2.0 * n3 * n3 * nc
-    executed = flops * (3 if precision == "bf16x3" else 1)
+    per_cell = 2.0 * n3 * n3 / classes(W)
+    executed = per_cell * nc * (3 if precision == "bf16x3" else 1)
     achieved = executed / (avg_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[precision]
     tile = "256x256" if tile_rows == 256 else f"{tile_rows}x128"
@@ -323,8 +310,9 @@ def contraction_roofline(W, precision, reps):
             "counters_source": tk[2] if tk else None,
             "kernel": f"gemm_{precision}", "avg_launch_ms": round(avg_ms, 4),
             "tile": tile, "k_stage": k_stage, "split_k": splits, "autotuned": tuned,
-            "work_per_unit": "2 n_dof^2 flops per cell update (the dense operator of L+ applied to one cell)",
-            "flops_per_launch": executed, "flops_per_cell_update": 2.0 * n3 * n3}
+            "work_per_unit": f"2 n_dof^2 / {classes(W)} flops per cell update (the operator of L+ applied to one cell, "
+                             "block diagonal on the classes of the velocity reflections)",
+            "flops_per_launch": executed, "flops_per_cell_update": per_cell}
     if not W["mix"] and not W["tube"]:
         fa = fsm_flops(info["n_pad"], info["n_dir"])
         roof["fsm_flops_per_cell_update"] = fa

@@ -88,7 +88,11 @@ int32_t sis_version(void);          /* 100 * major + minor                      
  *   nu_eq = F^-1[beta F f_eq],  beta = 4 b0 sum_p W_p phi_p psi_p,
  *   L(h) = L+(h) - nu_eq h.
  * The plan stores the n3 x n3 matrix of h -> L+(h) (delta = 1), assembled
- * from these spectral factors, and applies it as a dense contraction.       */
+ * from these spectral factors.  It commutes with the reflections v_i -> -v_i
+ * (symmetric grid and direction set), so the contraction applies one smaller
+ * matrix per class of functions even or odd in each velocity axis that is stored
+ * whole (8 classes on the full grid, 4 and 2 with parity 1 and 2, 2 on the polar
+ * grid); the plan also holds those blocks (the matrix's bytes / classes).    */
 typedef struct sis_plan* sis_plan_t;
 
 typedef struct {
@@ -175,7 +179,7 @@ typedef struct {
  * become per (cell, species) as stated at each call.                        */
 
 /* Build the tables on the host (threads) and assemble the operator on the
- * current device with `stream`.  Synchronous.  Owns ~8 n_dof^2 bytes of
+ * current device with `stream`.  Synchronous.  Owns 8 to 12 n_dof^2 bytes of
  * device memory plus tables.                                                 */
 sis_status sis_plan_create(const sis_velocity_desc* desc, hipStream_t stream, sis_plan_t* out);
 sis_status sis_plan_destroy(sis_plan_t plan);
@@ -312,8 +316,8 @@ sis_status sis_collide(sis_plan_t plan, int64_t n_cells, const double* h, const 
  * partial sums) is a fixed 64 MiB device array inside the library, one per GPU,
  * held until the process ends.  It runs the plan's contraction configuration for
  * this n_cells and precision (tuned by an earlier sis_collide, else the default
- * heuristic; it never tunes), with the split-K count lowered until the partials
- * fit; a low-precision operand of more than 64 MiB (n_cells * n_dof * 4 bytes
+ * heuristic; it never tunes), with the split-K count lowered while the batch does
+ * not fit one pass, then in passes of as many cells as fit; a low-precision operand of more than 64 MiB (n_cells * n_dof * 4 bytes
  * for FP32; n_cells * Kp * 4 bytes for BF16X3 / BF16, Kp = n_dof rounded up to
  * 64) is rejected with SIS_E_SHAPE before anything is enqueued.  Every call on a GPU
  * shares that GPU's array: calls that overlap on one GPU (other streams, other
@@ -491,7 +495,9 @@ sis_status sis_solve(sis_plan_t plan, sis_geom_t geom, const sis_solve_opts* opt
 /* Persistent iteration state (what sis_solve runs on): device buffers for
  * h^{k+1/2}, the right side, moments, the pending correction dU and the
  * per-case flow rates / convergence flags, plus the captured graph of one
- * iteration.  Created with h = 0.  Owns ~2 cells*n3*8 bytes.
+ * iteration.  Created with h = 0.  Owns ~2 cells*n3*8 bytes (4 with anchors) and
+ * the contraction's workspace (the class rows and split-K sums of a pass of cells:
+ * at most 2 GiB and 4 GiB).
  * sis_state_step enqueues n_iters iterations on `stream` (asynchronous);
  * converged cases are frozen by the kernels themselves.
  * sis_state_poll synchronises `stream` and returns the number of cases still
@@ -511,8 +517,9 @@ sis_status sis_state_destroy(sis_state_t state);
  * sis_state_create, outside stream capture) times every (tile, split-K)
  * candidate on the device (per launch), adds the finish step's cost of
  * reading each split-K partial beyond the first (M x N x 8 bytes at 4 TB/s)
- * and, for the bf16 tiles that read the pair layout, the measured split of
- * the cell operand into it, and keeps,
+ * and, for the tiles that read the cells' class rows, the measured launch that
+ * writes them (the 32-row tiles of FP64 and the bf16 forms read the cells
+ * themselves), and keeps,
  * among those within 1% of the fastest, the fewest split-K partials, then
  * the taller tile; tile_rows is the
  * cell-tile height (128, 64 or 32, the operator tile 128; or 256 for the

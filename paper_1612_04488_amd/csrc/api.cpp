@@ -78,28 +78,38 @@ void dfree(void* p) {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Grow-only device scratch buffer.
+// Grow-only device scratch buffer.  A buffer that a captured graph refers to (captured set while the
+// stream was capturing) is kept when a larger one takes its place, until the owner goes.
 struct Scratch {
   void* p = nullptr;
   size_t bytes = 0;
-  hipError_t ensure(size_t need) {
-    if (need <= bytes) return hipSuccess;
-    if (p) (void)hipFree(p);
+  bool captured = false;
+  std::vector<void*> held;
+  void drop() {
+    if (p && captured) held.push_back(p);
+    else dfree(p);
     p = nullptr;
     bytes = 0;
+    captured = false;
+  }
+  hipError_t ensure(size_t need) {
+    if (need <= bytes) return hipSuccess;
+    drop();
     hipError_t e = hipMalloc(&p, need);
     if (e == hipSuccess) bytes = need;
+    else p = nullptr;
     return e;
   }
   // give back what the largest tuning candidate needed beyond `keep` bytes
   hipError_t shrink(size_t keep) {
     if (bytes <= keep) return hipSuccess;
-    if (p) (void)hipFree(p);
-    p = nullptr;
-    bytes = 0;
+    drop();
     return keep ? ensure(keep) : hipSuccess;
   }
-  ~Scratch() { dfree(p); }
+  ~Scratch() {
+    dfree(p);
+    for (void* q : held) dfree(q);
+  }
 };
 
 // Workspace of sis_collide_noalloc: a file-scope device array (one copy per GPU,
@@ -149,8 +159,14 @@ struct sis_plan {
   double cU_s[2] = {0.0, 0.0}, cq_s[2] = {0.0, 0.0};
   double flow_factor = 1.0, visc_ratio = 1.0;
   double* op = nullptr;         // [ndof][ndof] L+ at delta = 1
+  // the operator on the reflection classes of the stored rows, [nb][kb][ld], and its FP32 and bf16
+  // pair-layout copies
+  sis::SymMap sym{};
+  double* opb = nullptr;
   float* op32 = nullptr;
-  uint16_t* opp = nullptr;   // the operator in the bf16 pair layout (ndof rows)
+  uint16_t* opp = nullptr;
+  int nb() const { return 1 << sym.logb; }
+  int64_t row_len() const { return static_cast<int64_t>(nb()) * sym.ld; }   // class rows of a cell
   double* v1d = nullptr;        // [n]
   double* feq = nullptr;        // [nsp][n3]
   double* nu = nullptr;         // [nsp][n3]
@@ -194,7 +210,7 @@ struct sis_plan {
     for (auto& e : events) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
     for (auto& e : fsm_events) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
     dfree(fsm_fac); dfree(fsm_field); dfree(fsm_mult); dfree(fsm_Kc); dfree(fsm_dirs); dfree(fsm_rad);
-    dfree(op); dfree(op32); dfree(opp);
+    dfree(op); dfree(opb); dfree(op32); dfree(opp);
     dfree(v1d); dfree(feq); dfree(nu); dfree(Kc); dfree(gram_inv);
     dfree(vnode); dfree(wnode); dfree(d_vr); dfree(d_cth); dfree(d_sth); dfree(vtab); dfree(wtab);
   }
@@ -358,111 +374,129 @@ sis::TableDesc table_desc(const sis_velocity_desc* d) {
   return t;
 }
 
-// Default tile and split-K for a contraction of M cells against the n3 x n3
-// operator: enough workgroups (>= 1024) to fill the chip.
-void choose_gemm(int64_t M, int n3, int* tile, int* splits) {
+// Default tile and split-K for a contraction of M cells against nb matrices of n3 x n3:
+// enough workgroups (>= 1024) to fill the chip.
+void choose_gemm(int64_t M, int n3, int nb, int* tile, int* splits) {
   *tile = M >= 256 ? 0 : 1;
   const int64_t bm = *tile == 0 ? 128 : 32;
-  const int64_t blocks = ((n3 + 127) / 128) * ((M + bm - 1) / bm);
+  const int64_t blocks = nb * ((n3 + 127) / 128) * ((M + bm - 1) / bm);
   int s = 1;
   while (blocks * s < 1024 && s < 16 && n3 / (s * 2) >= 256) s *= 2;
   *splits = s;
 }
 
-// Cell operand of a low-precision contraction (x = X - Xref rounded once per launch).
-sis_status prepare_lowp_operand(sis_plan* p, int precision, int64_t n_cells, const double* h, const double* xref,
-                                Scratch* ws_x, sis::GemmArgs& g, hipStream_t s) {
-  if (precision == SIS_PREC_FP64) return SIS_OK;
-  const int64_t cnt = n_cells * static_cast<int64_t>(p->ndof);
-  if (precision == SIS_PREC_BF16X3 || precision == SIS_PREC_BF16) {
-    // pair layout: 2 Kp bf16 per cell, 4 bytes per padded unknown
-    HIP_TRY(ws_x->ensure(static_cast<size_t>(n_cells) * sis::pair_stride(p->ndof) * 4));
-    uint16_t* hx = static_cast<uint16_t*>(ws_x->p);
-    HIP_TRY(sis::launch_split_pairs(h, xref, n_cells, p->ndof, hx, precision == SIS_PREC_BF16X3, s));
-    g.Xp = hx;
+// The contraction configuration of n_cells cells: tuned, or the default heuristic.
+void gemm_config(const sis_plan* p, int64_t n_cells, int precision, int* tile, int* splits) {
+  const auto tuned = p->gemm_choice.find(std::make_pair(n_cells, precision));
+  if (tuned != p->gemm_choice.end()) {
+    *tile = tuned->second.first;
+    *splits = tuned->second.second;
   } else {
-    HIP_TRY(ws_x->ensure(static_cast<size_t>(cnt) * 4));
-    float* fx = static_cast<float*>(ws_x->p);
-    HIP_TRY(sis::launch_convert_x_f32(h, xref, cnt, fx, s));
-    g.X32 = fx;
+    choose_gemm(n_cells, p->sym.kb, p->nb(), tile, splits);
   }
-  return SIS_OK;
 }
 
-// The 32-row BF16 tiles split the FP64 cell operand while staging it (no split_pairs launch):
-// the few-cell shapes that pick them are bound by launch latency.
-bool fused_split(int precision, int tile) {
-  return (precision == SIS_PREC_BF16X3 || precision == SIS_PREC_BF16) && tile == 1;
+// Whether the contraction reads the cells' own rows: the 32-row tiles of FP64 and the bf16 forms
+// make the class sums (and bf16 pairs) while staging, with no class_rows launch -- the few-cell
+// shapes that pick them are bound by launch latency.
+bool own_rows(int precision, int tile) { return tile == 1 && precision != SIS_PREC_FP32; }
+
+// Bytes per cell of the class rows in a precision (the bf16 pair layout: 4 per padded entry).
+size_t class_row_bytes(const sis_plan* p, int precision) {
+  if (precision == SIS_PREC_FP64) return static_cast<size_t>(p->row_len()) * 8;
+  if (precision == SIS_PREC_FP32) return static_cast<size_t>(p->row_len()) * 4;
+  return static_cast<size_t>(p->nb()) * sis::pair_stride(p->sym.kb) * 4;
+}
+
+// Cells per pass of a collision step: the class rows and one split's sums of a pass stay within
+// 2 GiB each, so that the workspace does not grow with the batch.
+int64_t pass_cells(const sis_plan* p, int64_t n_cells) {
+  const int64_t most = (int64_t(2) << 30) / (p->row_len() * 8);
+  return std::min(n_cells, std::max<int64_t>(256, most / 256 * 256));
+}
+
+void set_gemm_operands(const sis_plan* p, int precision, int tile, const double* h, const double* xref, void* xrows,
+                       sis::GemmArgs& g) {
+  g.precision = precision;
+  g.sym = &p->sym;
+  g.op64 = p->opb;
+  g.op32 = p->op32;
+  g.opp = p->opp;
+  g.tile = tile;
+  g.cells_own_rows = 0;
+  g.X = h;
+  g.Xref = nullptr;
+  g.Xp = nullptr;
+  g.X32 = nullptr;
+  if (own_rows(precision, tile)) {
+    g.cells_own_rows = 1;
+    g.Xref = xref;
+  } else if (precision == SIS_PREC_FP64) {
+    g.X = static_cast<double*>(xrows);
+  } else if (precision == SIS_PREC_FP32) {
+    g.X32 = static_cast<float*>(xrows);
+  } else {
+    g.Xp = static_cast<uint16_t*>(xrows);
+  }
 }
 
 // Autotuner of the contraction: times every (tile, split-K) candidate on the
-// actual shape (two launches each after a warm-up, HIP events on `s`) and
+// actual shape (one pass of it; two launches each after a warm-up, HIP events on `s`) and
 // keeps, per (cells, precision), the candidate with the fewest split-K
 // partials, then the tallest tile, among those within 1% of the fastest after
-// charging each extra partial its read by the finish step (so that timing noise
+// charging each extra partial its read by the finish step and the tiles that read
+// class rows the launch that writes them (so that timing noise
 // does not flip between near-equal configurations).  Not
 // callable while `s` is capturing.  Candidates whose split-K partials would
 // exceed 4 GiB are skipped.
-sis_status tune_gemm(sis_plan* p, int64_t M, int precision, const double* h, Scratch* ws_acc, Scratch* ws_x,
+sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* h, Scratch* ws_acc, Scratch* ws_x,
                      hipStream_t s) {
-  const auto key = std::make_pair(M, precision);
+  const auto key = std::make_pair(n_cells, precision);
   if (p->gemm_choice.count(key)) return SIS_OK;
+  const int64_t M = pass_cells(p, n_cells);
+  const int64_t row = p->row_len();
   sis::GemmArgs g{};
-  g.precision = precision;
-  g.X = h;
-  g.op64 = p->op;
-  g.op32 = p->op32;
-  g.opp = p->opp;
   g.M = M;
-  g.N = p->ndof;
-  g.K = p->ndof;
-  if (sis_status st = prepare_lowp_operand(p, precision, M, h, nullptr, ws_x, g, s)) return st;
-  const uint16_t* xp_split = g.Xp;
   int dt, ds;
-  choose_gemm(M, p->ndof, &dt, &ds);
+  choose_gemm(n_cells, p->sym.kb, p->nb(), &dt, &ds);
   std::vector<std::pair<float, std::pair<int, int>>> timed;
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
-  // the split of the cell operand into the bf16 pair layout, per launch (two timed launches)
-  const bool bf16 = precision == SIS_PREC_BF16X3 || precision == SIS_PREC_BF16;
-  float split_ms = 0.f;
-  if (bf16) {
-    uint16_t* xp = const_cast<uint16_t*>(xp_split);
-    hipError_t e = hipEventRecord(e0, s);
-    for (int r = 0; r < 2 && e == hipSuccess; ++r)
-      e = sis::launch_split_pairs(h, nullptr, M, p->ndof, xp, precision == SIS_PREC_BF16X3, s);
-    if (e == hipSuccess) e = hipEventRecord(e1, s);
-    if (e == hipSuccess) e = hipEventSynchronize(e1);
-    if (e == hipSuccess) e = hipEventElapsedTime(&split_ms, e0, e1);
-    if (e != hipSuccess) {
-      (void)hipEventDestroy(e0);
-      (void)hipEventDestroy(e1);
-      return fail(SIS_E_DEVICE, "contraction tuning: %s", hipGetErrorString(e));
+  hipError_t err = hipSuccess;
+  // the class rows, per launch (two timed launches)
+  float rows_ms = 0.f;
+  if (!own_rows(precision, 0)) {
+    err = ws_x->ensure(class_row_bytes(p, precision) * M);
+    for (int r = 0; r < 3 && err == hipSuccess; ++r) {
+      if (r == 1) err = hipEventRecord(e0, s);
+      if (err == hipSuccess) err = sis::launch_class_rows(p->sym, precision, h, nullptr, nullptr, M, ws_x->p, s);
     }
-    split_ms *= 0.5f;
+    if (err == hipSuccess) err = hipEventRecord(e1, s);
+    if (err == hipSuccess) err = hipEventSynchronize(e1);
+    if (err == hipSuccess) err = hipEventElapsedTime(&rows_ms, e0, e1);
+    rows_ms *= 0.5f;
   }
   // candidates: FP64 tiles 0, 2, 1, 3, 4; FP32 and BF16 tiles 0, 2, 1; BF16X3 tiles 0, 2, 1 and the
   // 256 x 256 tile 5 where its pair arrays take 32-bit offsets
   std::vector<int> tiles = {0, 2, 1};
   if (precision == SIS_PREC_FP64) tiles.insert(tiles.end(), {3, 4});
-  if (precision == SIS_PREC_BF16X3 && sis::gemm_wide_fits(M, p->ndof, p->ndof)) tiles.push_back(5);
+  if (precision == SIS_PREC_BF16X3 && sis::gemm_wide_fits(M, p->sym.kb, p->sym.kb, p->nb())) tiles.push_back(5);
   // split-K up to 32 (at least 64 k values per split): few cells leave most CUs idle otherwise
   const int splits[10] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
-  hipError_t err = hipSuccess;
+  const int K = p->sym.kb;
   for (size_t ti = 0; ti < tiles.size() && err == hipSuccess; ++ti)
     for (int si = 0; si < 10 && err == hipSuccess; ++si) {
       const int sp = splits[si];
-      if (sp > 1 && sis::gemm_k_per_split(p->ndof, sp) * (sp - 1) >= p->ndof) continue;   // an empty split
-      if (sp > 1 && sis::gemm_k_per_split(p->ndof, sp) < 64) continue;
-      const double bytes = static_cast<double>(sp) * M * p->ndof * 8.0;
+      if (sp > 1 && sis::gemm_k_per_split(K, sp) * (sp - 1) >= K) continue;   // an empty split
+      if (sp > 1 && sis::gemm_k_per_split(K, sp) < 64) continue;
+      const double bytes = static_cast<double>(sp) * M * row * 8.0;
       if (bytes > 4.0 * (1 << 30)) continue;
       err = ws_acc->ensure(static_cast<size_t>(bytes));
       if (err != hipSuccess) break;
+      set_gemm_operands(p, precision, tiles[ti], h, nullptr, ws_x->p, g);
       g.acc = static_cast<double*>(ws_acc->p);
-      g.tile = tiles[ti];
       g.splits = sp;
-      g.Xp = fused_split(precision, g.tile) ? nullptr : xp_split;
       err = sis::launch_gemm(g, s);
       if (err == hipSuccess) err = hipEventRecord(e0, s);
       for (int r = 0; r < 2 && err == hipSuccess; ++r) err = sis::launch_gemm(g, s);
@@ -470,9 +504,9 @@ sis_status tune_gemm(sis_plan* p, int64_t M, int precision, const double* h, Scr
       if (err == hipSuccess) err = hipEventSynchronize(e1);
       float ms = 0.f;
       if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
-      // per launch; the bf16 tiles that read the pair layout also pay its split launch
+      // per launch; the tiles that read class rows also pay the launch that writes them
       ms *= 0.5f;
-      if (bf16 && !fused_split(precision, g.tile)) ms += split_ms;
+      if (!own_rows(precision, g.tile)) ms += rows_ms;
       if (err == hipSuccess) timed.emplace_back(ms, std::make_pair(g.tile, sp));
     }
   (void)hipEventDestroy(e0);
@@ -481,9 +515,9 @@ sis_status tune_gemm(sis_plan* p, int64_t M, int precision, const double* h, Scr
   std::pair<int, int> best(dt, ds);
   if (!timed.empty()) {
     // each split-K partial beyond the first costs the finish step one more FP64 row read per
-    // cell (M x N x 8 bytes at the ~4 TB/s that finish_kernel streams): add it to the timing
+    // cell (M x row x 8 bytes at the ~4 TB/s that finish_kernel streams): add it to the timing
     for (auto& c : timed)
-      c.first += static_cast<float>((c.second.second - 1) * static_cast<double>(M) * p->ndof * 8.0 / 4.0e12 * 1e3);
+      c.first += static_cast<float>((c.second.second - 1) * static_cast<double>(M) * row * 8.0 / 4.0e12 * 1e3);
     float fastest = timed[0].first;
     for (const auto& c : timed) fastest = std::min(fastest, c.first);
     // within 1% of the fastest: fewest split-K partials, then the larger tile, then the faster
@@ -503,7 +537,7 @@ sis_status tune_gemm(sis_plan* p, int64_t M, int precision, const double* h, Scr
   }
   p->gemm_choice[key] = best;
   // the split-K partials of the kept configuration, not of the largest candidate
-  const size_t keep = best.second > 1 ? static_cast<size_t>(best.second) * M * p->ndof * sizeof(double) : 0;
+  const size_t keep = static_cast<size_t>(best.second) * M * row * sizeof(double);
   if (ws_acc->shrink(keep) != hipSuccess) return fail(SIS_E_DEVICE, "contraction tuning: scratch reallocation failed");
   return SIS_OK;
 }
@@ -541,6 +575,63 @@ sis::FinishArgs finish_args(const sis_plan* p, int64_t n_cells, const double* h,
   return f;
 }
 
+// Event-timed launch of the contraction (eager launches while timing is on).
+sis_status launch_gemm_timed(sis_plan* p, const sis::GemmArgs& g, bool capturing, hipStream_t s) {
+  if (p->timing && !capturing) {
+    hipEvent_t a, b;
+    HIP_TRY(hipEventCreate(&a));
+    HIP_TRY(hipEventCreate(&b));
+    p->events.emplace_back(a, b);
+    HIP_TRY(hipEventRecord(a, s));
+    HIP_TRY(sis::launch_gemm(g, s));
+    HIP_TRY(hipEventRecord(b, s));
+  } else {
+    HIP_TRY(sis::launch_gemm(g, s));
+  }
+  return SIS_OK;
+}
+
+// Arguments of one collision step (cells of a pass are addressed from these by collide_pass).
+struct CollideArgs {
+  const double *h, *dU, *delta;
+  const int32_t* flow;
+  int project;
+  double *rhs, *lh, *amom;
+  const int32_t* cell_active;
+  int precision, anchor_mode;
+  double *xref, *accref;
+  int tile, splits;
+};
+
+// Cells [c0, c0 + nc) of a step: class rows, contraction, finish, with the workspace given.
+sis_status collide_pass(sis_plan* p, const CollideArgs& c, int64_t c0, int64_t nc, void* xrows, double* acc,
+                        bool capturing, hipStream_t s) {
+  const int64_t nd = p->ndof, row = p->row_len();
+  const double* h = c.h + c0 * nd;
+  double* rhs = c.rhs + c0 * nd;
+  double* xref = c.xref ? c.xref + c0 * nd : nullptr;
+  const double* sub = c.anchor_mode == 2 ? xref : nullptr;
+  const int32_t* active = c.cell_active ? c.cell_active + c0 : nullptr;
+  sis::GemmArgs g{};
+  set_gemm_operands(p, c.precision, c.tile, h, sub, xrows, g);
+  if (!own_rows(c.precision, c.tile))
+    HIP_TRY(sis::launch_class_rows(p->sym, c.precision, h, sub, active, nc, xrows, s));
+  g.acc = acc;
+  g.M = nc;
+  g.splits = c.splits;
+  if (sis_status st = launch_gemm_timed(p, g, capturing, s)) return st;
+  sis::FinishArgs f = finish_args(p, nc, h, c.dU ? c.dU + c0 * p->nsp : nullptr, c.delta + c0,
+                                  c.flow ? c.flow + c0 : nullptr, c.project, rhs, c.lh ? c.lh + c0 * nd : nullptr,
+                                  c.amom ? c.amom + c0 * 4 * p->nsp : nullptr, active, c.anchor_mode, xref,
+                                  c.accref ? c.accref + c0 * row : nullptr);
+  f.sym = p->sym;
+  f.splits = c.splits;
+  f.acc = acc;
+  f.acc_stride = nc * row;
+  HIP_TRY(sis::launch_finish(f, s));
+  return SIS_OK;
+}
+
 sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const double* dU,
                        const double* delta, const int32_t* flow, int project, double* rhs,
                        double* lh, double* amom, const int32_t* cell_active, hipStream_t s,
@@ -552,6 +643,7 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
     // is being taken, becomes (0, 0))
     sis::FinishArgs f = finish_args(p, n_cells, h, dU, delta, flow, project, rhs, lh, amom, cell_active,
                                     anchor_mode, xref, accref);
+    f.sym = p->sym;
     f.splits = 0;
     f.acc = nullptr;
     HIP_TRY(sis::launch_finish(f, s));
@@ -559,59 +651,41 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
   }
   if (!ws_acc) ws_acc = &p->ws_acc;
   if (!ws_x) ws_x = &p->ws_x;
-  if (precision < 0) precision = p->precision;
-  int tile, splits;
-  const auto tuned = p->gemm_choice.find(std::make_pair(n_cells, precision));
-  if (tuned != p->gemm_choice.end()) {
-    tile = tuned->second.first;
-    splits = tuned->second.second;
-  } else {
-    choose_gemm(n_cells, p->ndof, &tile, &splits);
-  }
-  double* acc = rhs;
-  if (splits > 1) {
-    HIP_TRY(ws_acc->ensure(static_cast<size_t>(splits) * n_cells * p->ndof * sizeof(double)));
-    acc = static_cast<double*>(ws_acc->p);
-  }
-  sis::GemmArgs g{};
-  g.precision = precision;
-  g.X = h;
-  g.Xref = anchor_mode == 2 ? xref : nullptr;
-  if (fused_split(precision, tile))
-    g.Xp = nullptr;   // the contraction splits h (minus the anchor) itself
-  else if (sis_status st = prepare_lowp_operand(p, precision, n_cells, h, g.Xref, ws_x, g, s))
-    return st;
-  g.op64 = p->op;
-  g.op32 = p->op32;
-  g.opp = p->opp;
-  g.acc = acc;
-  g.M = n_cells;
-  g.N = p->ndof;
-  g.K = p->ndof;
-  g.splits = splits;
-  g.tile = tile;
-  if (p->timing) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(s, &cs));
-    if (cs == hipStreamCaptureStatusNone) {
-      hipEvent_t a, b;
-      HIP_TRY(hipEventCreate(&a));
-      HIP_TRY(hipEventCreate(&b));
-      p->events.emplace_back(a, b);
-      HIP_TRY(hipEventRecord(a, s));
-      HIP_TRY(sis::launch_gemm(g, s));
-      HIP_TRY(hipEventRecord(b, s));
-    } else {
-      HIP_TRY(sis::launch_gemm(g, s));
-    }
-  } else {
+  CollideArgs c{h,   dU,   delta, flow,        project,
+                rhs, lh,   amom,  cell_active, precision < 0 ? p->precision : precision,
+                anchor_mode, xref, accref, 0, 0};
+  gemm_config(p, n_cells, c.precision, &c.tile, &c.splits);
+  const int64_t pass = pass_cells(p, n_cells);
+  const size_t acc_bytes = static_cast<size_t>(c.splits) * pass * p->row_len() * 8;
+  const size_t x_bytes = own_rows(c.precision, c.tile) ? 0 : class_row_bytes(p, c.precision) * pass;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(s, &cs));
+  const bool capturing = cs != hipStreamCaptureStatusNone;
+  if (capturing && c.precision == SIS_PREC_FP64 && (acc_bytes > ws_acc->bytes || x_bytes > ws_x->bytes)) {
+    // no workspace yet and none can be made: the whole matrix, written over the right side in place
+    sis::GemmArgs g{};
+    g.X = h;
+    g.op64 = p->op;
+    g.acc = rhs;
+    g.M = n_cells;
+    g.N = g.K = p->ndof;
+    g.splits = 1;
+    g.tile = n_cells >= 256 ? 0 : 1;
     HIP_TRY(sis::launch_gemm(g, s));
+    sis::FinishArgs f = finish_args(p, n_cells, h, dU, delta, flow, project, rhs, lh, amom, cell_active, 0, nullptr,
+                                    nullptr);
+    f.splits = 1;
+    f.acc = rhs;
+    HIP_TRY(sis::launch_finish(f, s));
+    return SIS_OK;
   }
-  sis::FinishArgs f = finish_args(p, n_cells, h, dU, delta, flow, project, rhs, lh, amom, cell_active,
-                                  anchor_mode, xref, accref);
-  f.splits = splits;
-  f.acc = acc;
-  HIP_TRY(sis::launch_finish(f, s));
+  HIP_TRY(ws_acc->ensure(acc_bytes));
+  HIP_TRY(ws_x->ensure(x_bytes));
+  if (capturing) ws_acc->captured = ws_x->captured = true;
+  for (int64_t c0 = 0; c0 < n_cells; c0 += pass)
+    if (sis_status st = collide_pass(p, c, c0, std::min(pass, n_cells - c0), ws_x->p, static_cast<double*>(ws_acc->p),
+                                     capturing, s))
+      return st;
   return SIS_OK;
 }
 
@@ -1381,6 +1455,17 @@ sis_status build_velocity_tables(sis_plan* p, hipStream_t stream) {
   return SIS_OK;
 }
 
+// The operator on the reflection classes of the stored rows (see sis::SymMap).
+sis_status build_class_operator(sis_plan* p, hipStream_t stream) {
+  const int cart[3] = {p->n, p->d2, p->d3}, pol[3] = {p->n_vr, p->n_th, p->n_vz};
+  const bool cart_m[3] = {true, p->parity < 2, p->parity < 1}, pol_m[3] = {false, true, false};
+  if (!sis::make_sym_map(p->sym, p->nsp, p->polar ? pol : cart, p->polar ? pol_m : cart_m))
+    return fail(SIS_E_UNSUPPORTED, "velocity grid too large for the contraction's index arithmetic");
+  HIP_TRY(dmalloc(&p->opb, static_cast<size_t>(p->nb()) * p->sym.kb * p->sym.ld));
+  HIP_TRY(sis::launch_class_operator(p->sym, p->op, p->opb, stream));
+  return SIS_OK;
+}
+
 // Full-grid [species][n^3] array -> stored [species][nv] (v2, v3 of the upper halves).
 std::vector<double> restrict_rows(const sis_plan* p, const double* full, int rows) {
   const int n = p->n, n3 = n * n * n;
@@ -1943,6 +2028,11 @@ sis_status create_mix_plan(const sis_velocity_desc* desc, hipStream_t stream, si
     g.tile = 1;
     MIX_TRY(sis::launch_gemm(g, stream));
   }
+  if (sis_status st = build_class_operator(p, stream)) {
+    cleanup();
+    delete p;
+    return st;
+  }
   MIX_TRY(hipStreamSynchronize(stream));
   cleanup();
 #undef MIX_TRY
@@ -2175,6 +2265,11 @@ sis_status create_polar_plan(const sis_velocity_desc* desc, hipStream_t stream, 
     return fail(SIS_E_INVALID, "polar grid: n_vr n_th n_vz must be even");
   }
   POL_TRY(sis::launch_gemm(g, stream));
+  if (sis_status st = build_class_operator(p, stream)) {
+    cleanup();
+    delete p;
+    return st;
+  }
   POL_TRY(hipStreamSynchronize(stream));
   cleanup();
 #undef POL_TRY
@@ -2628,6 +2723,11 @@ sis_status sis_plan_create(const sis_velocity_desc* desc, hipStream_t stream, si
     g.tile = 1;
     PLAN_TRY(sis::launch_gemm(g, stream));
   }
+  if (sis_status st = build_class_operator(p, stream)) {
+    cleanup();
+    delete p;
+    return st;
+  }
   PLAN_TRY(hipStreamSynchronize(stream));
   cleanup();
 #undef PLAN_TRY
@@ -2685,12 +2785,12 @@ sis_status sis_plan_tables(sis_plan_t p, double* v1d, double* feq, double* nu, d
 
 sis_status sis_plan_set_precision(sis_plan_t p, int32_t precision, hipStream_t stream) {
   if (sis_status st = check_plan(p)) return st;
-  const int64_t cnt = static_cast<int64_t>(p->ndof) * p->ndof;
+  const int64_t rows = static_cast<int64_t>(p->nb()) * p->sym.kb;
   if (precision == SIS_PREC_FP64) {
   } else if (precision == SIS_PREC_FP32) {
     if (!p->op32) {
-      HIP_TRY(dmalloc(&p->op32, cnt));
-      HIP_TRY(sis::launch_convert_f32(p->op, p->op32, cnt, stream));
+      HIP_TRY(dmalloc(&p->op32, rows * p->sym.ld));
+      HIP_TRY(sis::launch_convert_f32(p->opb, p->op32, rows * p->sym.ld, stream));
       HIP_TRY(hipStreamSynchronize(stream));
     }
   } else if (precision == SIS_PREC_BF16X3 || precision == SIS_PREC_BF16) {
@@ -2699,8 +2799,8 @@ sis_status sis_plan_set_precision(sis_plan_t p, int32_t precision, hipStream_t s
       return fail(SIS_E_UNSUPPORTED, "the one-product BF16 contraction is not offered for two-species plans "
                                      "(the species blocks deviate by ~1e-3 in the heat flux); use BF16X3");
     if (!p->opp) {
-      HIP_TRY(dmalloc(&p->opp, static_cast<int64_t>(p->ndof) * 2 * sis::pair_stride(p->ndof)));
-      HIP_TRY(sis::launch_split_pairs(p->op, nullptr, p->ndof, p->ndof, p->opp, 1, stream));
+      HIP_TRY(dmalloc(&p->opp, rows * 2 * sis::pair_stride(p->sym.kb)));
+      HIP_TRY(sis::launch_split_pairs(p->opb, rows, p->sym.kb, p->sym.ld, p->opp, stream));
       HIP_TRY(hipStreamSynchronize(stream));
     }
   } else {
@@ -2891,59 +2991,36 @@ sis_status sis_collide_noalloc(sis_plan_t p, int64_t n_cells, const double* h, c
   if (project && p->polar) return fail(SIS_E_UNSUPPORTED, "invariant projection is for the Cartesian grids");
   // the plan's configuration for this shape (tuned by earlier sis_collide calls, else the
   // default heuristic); no tuning here, since tuning allocates
-  const int precision = p->precision;
-  int tile, splits;
-  const auto tuned = p->gemm_choice.find(std::make_pair(n_cells, precision));
-  if (tuned != p->gemm_choice.end()) {
-    tile = tuned->second.first;
-    splits = tuned->second.second;
-  } else {
-    choose_gemm(n_cells, p->ndof, &tile, &splits);
-  }
-  const int64_t cnt = n_cells * static_cast<int64_t>(p->ndof);
-  // low-precision cell operand first in the scratch (4 bytes per unknown), then the split-K
-  // partials; the split count is lowered until the partials fit (one split needs none)
+  CollideArgs c{h, dU, delta, flow, project, rhs_out, lh_out, amom_out, nullptr, p->precision, 0, nullptr, nullptr, 0, 0};
+  gemm_config(p, n_cells, c.precision, &c.tile, &c.splits);
   // FP32: 4 bytes per unknown; the bf16 forms: 4 bytes per padded unknown (pair layout)
-  const int64_t xcnt = precision == SIS_PREC_FP32 ? cnt : n_cells * static_cast<int64_t>(sis::pair_stride(p->ndof));
-  const size_t xbytes = precision == SIS_PREC_FP64 ? 0 : ((static_cast<size_t>(xcnt) * 4 + 255) / 256) * 256;
-  if (xbytes > kStaticScratchBytes)
-    return fail(SIS_E_SHAPE, "sis_collide_noalloc: the low-precision cell operand needs %zu bytes, more than its "
-                             "%zu-byte workspace (use fewer cells per call)", xbytes, kStaticScratchBytes);
-  while (splits > 1 && xbytes + static_cast<size_t>(splits) * cnt * sizeof(double) > kStaticScratchBytes) --splits;
+  if (c.precision != SIS_PREC_FP64) {
+    const int64_t per_cell = c.precision == SIS_PREC_FP32 ? p->ndof : sis::pair_stride(p->ndof);
+    const size_t xbytes = ((static_cast<size_t>(n_cells) * per_cell * 4 + 255) / 256) * 256;
+    if (xbytes > kStaticScratchBytes)
+      return fail(SIS_E_SHAPE, "sis_collide_noalloc: the low-precision cell operand needs %zu bytes, more than its "
+                               "%zu-byte workspace (use fewer cells per call)", xbytes, kStaticScratchBytes);
+  }
+  // passes of cells whose class rows and partial sums fit the workspace (the rows first); the
+  // split count is lowered while the partial sums keep the batch from one pass
+  const size_t x_cell = own_rows(c.precision, c.tile) ? 0 : class_row_bytes(p, c.precision);
+  const size_t sum_cell = static_cast<size_t>(p->row_len()) * sizeof(double);
+  auto cells_that_fit = [&](int splits) {
+    return static_cast<int64_t>((kStaticScratchBytes - 256) / (x_cell + splits * sum_cell));
+  };
+  while (c.splits > 1 && cells_that_fit(c.splits) < n_cells) --c.splits;
+  int64_t pass = std::min(n_cells, cells_that_fit(c.splits));
+  if (pass < n_cells && pass > 256) pass = pass / 128 * 128;
+  if (pass < 1) return fail(SIS_E_SHAPE, "sis_collide_noalloc: one cell needs more than its %zu-byte workspace", kStaticScratchBytes);
   void* base = nullptr;
   {
     const hipError_t e = static_scratch(&base);
     if (e != hipSuccess) return fail(SIS_E_DEVICE, "workspace address: %s", hipGetErrorString(e));
   }
   unsigned char* ws = static_cast<unsigned char*>(base);
-  sis::GemmArgs g{};
-  g.precision = precision;
-  g.X = h;
-  if (precision == SIS_PREC_BF16X3 || precision == SIS_PREC_BF16) {
-    uint16_t* hx = reinterpret_cast<uint16_t*>(ws);
-    HIP_TRY(sis::launch_split_pairs(h, nullptr, n_cells, p->ndof, hx, precision == SIS_PREC_BF16X3, stream));
-    g.Xp = hx;
-  } else if (precision == SIS_PREC_FP32) {
-    float* fx = reinterpret_cast<float*>(ws);
-    HIP_TRY(sis::launch_convert_x_f32(h, nullptr, cnt, fx, stream));
-    g.X32 = fx;
-  }
-  double* acc = splits > 1 ? reinterpret_cast<double*>(ws + xbytes) : rhs_out;
-  g.op64 = p->op;
-  g.op32 = p->op32;
-  g.opp = p->opp;
-  g.acc = acc;
-  g.M = n_cells;
-  g.N = p->ndof;
-  g.K = p->ndof;
-  g.splits = splits;
-  g.tile = tile;
-  HIP_TRY(sis::launch_gemm(g, stream));
-  sis::FinishArgs f = finish_args(p, n_cells, h, dU, delta, flow, project, rhs_out, lh_out, amom_out, nullptr, 0,
-                                  nullptr, nullptr);
-  f.splits = splits;
-  f.acc = acc;
-  HIP_TRY(sis::launch_finish(f, stream));
+  double* acc = reinterpret_cast<double*>(ws + (x_cell * pass + 255) / 256 * 256);
+  for (int64_t c0 = 0; c0 < n_cells; c0 += pass)
+    if (sis_status st = collide_pass(p, c, c0, std::min(pass, n_cells - c0), ws, acc, true, stream)) return st;
   return SIS_OK;
 }
 
@@ -3323,7 +3400,7 @@ sis_status sis_state_create(sis_plan_t p, sis_geom_t g, const sis_solve_opts* o,
   ST_TRY(dmalloc(&b->lact, nc));
   if (b->refresh > 1) {
     ST_TRY(dmalloc(&b->xref, static_cast<size_t>(nc) * n3));
-    ST_TRY(dmalloc(&b->accref, static_cast<size_t>(nc) * n3));
+    ST_TRY(dmalloc(&b->accref, static_cast<size_t>(nc) * p->row_len()));
   }
   if (o->persistent) {
     if (g->two_d || g->tube || p->polar || nsp != 1 || p->precision != SIS_PREC_FP64) {
@@ -3355,11 +3432,13 @@ sis_status sis_state_create(sis_plan_t p, sis_geom_t g, const sis_solve_opts* o,
     if (sis_status st = tune_gemm(p, nc, SIS_PREC_FP64, b->h, &b->ws_acc, &b->ws_x, stream)) { delete b; return st; }
     if (p->precision != SIS_PREC_FP64)
       if (sis_status st = tune_gemm(p, nc, p->precision, b->h, &b->ws_acc, &b->ws_x, stream)) { delete b; return st; }
-    int splits = std::max(p->gemm_choice[std::make_pair(nc, static_cast<int>(SIS_PREC_FP64))].second,
-                          p->gemm_choice[std::make_pair(nc, p->precision)].second);
-    if (splits > 1) ST_TRY(b->ws_acc.ensure(static_cast<size_t>(splits) * nc * n3 * 8));
-    if (p->precision != SIS_PREC_FP64)
-      ST_TRY(b->ws_x.ensure(static_cast<size_t>(nc) * (p->precision == SIS_PREC_FP32 ? n3 : sis::pair_stride(n3)) * 4));
+    // the workspace of both, fixed here: the captured graphs refer to it
+    const int64_t pass = pass_cells(p, nc);
+    for (const int prec : {static_cast<int>(SIS_PREC_FP64), p->precision}) {
+      const auto [tile, splits] = p->gemm_choice[std::make_pair(nc, prec)];
+      ST_TRY(b->ws_acc.ensure(static_cast<size_t>(splits) * pass * p->row_len() * 8));
+      if (!own_rows(prec, tile)) ST_TRY(b->ws_x.ensure(class_row_bytes(p, prec) * pass));
+    }
   }
   hipStream_t s = stream;
   if (o->use_graph && !b->persistent) {
@@ -3512,7 +3591,7 @@ sis_status sis_plan_set_contraction_config(sis_plan_t p, int64_t n_cells, int32_
     tile = tile_rows == 128 ? 3 : tile_rows == 64 ? 4 : -1;
   }
   if (tile < 0) return fail(SIS_E_INVALID, "no contraction tile of %d rows with k-stage %d for this precision", tile_rows, k_stage);
-  if (tile == 5 && !sis::gemm_wide_fits(n_cells, p->ndof, p->ndof))
+  if (tile == 5 && !sis::gemm_wide_fits(n_cells, p->ndof, p->ndof, 1))
     return fail(SIS_E_UNSUPPORTED, "the 256 x 256 tile needs both bf16 pair arrays under 4 GiB");
   p->gemm_choice[std::make_pair(n_cells, static_cast<int>(precision))] = std::make_pair(tile, static_cast<int>(splits));
   return SIS_OK;
@@ -3523,15 +3602,8 @@ sis_status sis_plan_contraction_config(sis_plan_t p, int64_t n_cells, int32_t pr
   if (sis_status st = check_plan(p)) return st;
   if (!tile_rows || !splits || !tuned) return fail(SIS_E_INVALID, "null output");
   int t, s;
-  const auto it = p->gemm_choice.find(std::make_pair(n_cells, static_cast<int>(precision)));
-  if (it != p->gemm_choice.end()) {
-    t = it->second.first;
-    s = it->second.second;
-    *tuned = 1;
-  } else {
-    choose_gemm(n_cells, p->ndof, &t, &s);
-    *tuned = 0;
-  }
+  gemm_config(p, n_cells, precision, &t, &s);
+  *tuned = p->gemm_choice.count(std::make_pair(n_cells, static_cast<int>(precision))) ? 1 : 0;
   *tile_rows = sis::gemm_tile_rows(t);
   *splits = s;
   if (k_stage) *k_stage = sis::gemm_tile_depth(t, precision);

@@ -23,48 +23,84 @@ hipError_t launch_reduce_operator(const double* op, int64_t ld, double* red, int
 // op2 = op (double) rounded to float.
 hipError_t launch_convert_f32(const double* op, float* out, int64_t count, hipStream_t s);
 
+// Reflection classes of a stored row.  The operator commutes with the reflections of the velocity
+// axes that are stored whole (Cartesian: v1, also v2 without parity 2, also v3 without parity;
+// polar: th -> pi - th), so it maps the functions of each parity class (even or odd in every such
+// axis, nb = 2^logb classes) to themselves: one kb x kb block per class instead of the whole matrix,
+// nb times fewer operations and operator bytes.  An orbit is a velocity of the upper halves and its
+// nb images; a row has nvb = nv / nb orbits per species, in row order.  The cells' class rows are
+// [cell][nb][ld], ld = kb rounded up to 8 (zeros), kb = nsp * nvb.
+struct SymMap {
+  int logb;                // log2 of the number of classes (0: no map)
+  int nsp, nv, nvb, kb, ld;
+  int d23r, d3r;           // orbits per step of axis 1, of axis 2
+  uint32_t mul23, mul3;    // ceil(2^32 / d)
+  int s1, s2;              // strides of axes 1, 2 in a row
+  int lo1, lo2, lo3;       // first stored node of the upper half along each axis (0: not reflected)
+  int pairs;               // an even number of orbits along axis 3: 16-byte accesses
+};
+// Map of a row of dim[0] x dim[1] x dim[2] nodes reflected along the axes with mirror; false where
+// that is not offered: an odd reflected axis, a row too long for the index arithmetic.
+bool make_sym_map(SymMap& m, int nsp, const int (&dim)[3], const bool (&mirror)[3]);
+// out [nb][kb][ld] = blocks of op on the classes (op: the whole matrix)
+hipError_t launch_class_operator(const SymMap& m, const double* op, double* out, hipStream_t s);
+// Cell operand of the contraction: class rows of X - Xref (Xref may be null), formed in FP64, for
+// precision 0 as [cells][nb][ld] doubles, 1 as floats, 2 and 3 in the pair layout below
+// ([cells][nb][2 Kp] bf16, Kp = pair_stride(kb); 3: lo parts zero).  active: null or [cells]
+// (rows of inactive cells are not written).
+hipError_t launch_class_rows(const SymMap& m, int precision, const double* X, const double* Xref, const int32_t* active,
+                             int64_t cells, void* out, hipStream_t s);
+
 // BF16 pair layout of the low-precision contraction operands: rows of K values
 // stored with Kp = pair_stride(K) (K rounded up to 64); row r occupies 2 Kp bf16
 // at P + 2 Kp r, and each block of 32 k-values holds the 32 hi parts, then their
-// 32 lo parts; entries k >= K are zero.  launch_split_pairs writes
-// x = X - Xref (Xref may be null) for rows x K doubles: hi = RNE(x),
-// lo = RNE(x - hi), or lo = 0 when with_lo is 0.  P holds rows * 2 Kp bf16.
+// 32 lo parts; entries k >= K are zero.  launch_split_pairs writes rows x K doubles
+// (row stride ld): hi = RNE(x), lo = RNE(x - hi).  P holds rows * 2 Kp bf16.
 int pair_stride(int K);
-hipError_t launch_split_pairs(const double* X, const double* Xref, int64_t rows, int K, uint16_t* P, int with_lo,
-                              hipStream_t s);
+hipError_t launch_split_pairs(const double* X, int64_t rows, int K, int ld, uint16_t* P, hipStream_t s);
 
-// Contraction acc[z][m][n] = sum_{k in split z} X[m][k] * op[n][k]  (op stored n x k).
+// Shape of a launch: C[m][n] = sum_k X[m][k] Op[n][k] for nb blocks (grid.z = block * splits + split),
+// block offsets xs, os, cs and row strides ldx, ldo, ldc in elements, cz between splits of C.
+struct GemmShape {
+  int64_t M;
+  int N, K, kps, splits, ldx, ldo, ldc;
+  int64_t xs, os, cs, cz;
+};
+
+// Contraction acc[z][m][n] = sum_{k in split z} X[m][k] * op[n][k]  (op stored n x k), or with sym
+// the nb blocks of the classes: acc [z][m][nb][ld].
 // precision: 0 fp64 (op64), 1 fp32 (op32), 2 bf16x3, 3 bf16 (hi products only)
 // (Xp, opp in the pair layout).  Accumulators are written as double for every
 // precision.
 struct GemmArgs {
   int precision;
-  const double* X;         // FP64 cell operand (precision 0, and the FP32 path's source)
-  const double* Xref;      // null, or anchor: the contraction is applied to X - Xref
-  const uint16_t* Xp;      // precisions 2, 3: X - Xref in the pair layout, M rows (launch_split_pairs)
-  const float* X32;        // precision 1: X - Xref rounded to FP32 [M][K] (launch_convert_x_f32)
-  const double* op64;
+  const double* X;         // FP64 cell operand (precision 0; with cells_own_rows the cells' rows)
+  const double* Xref;      // cells_own_rows, bf16: null, or anchor: the contraction is applied to X - Xref
+  const uint16_t* Xp;      // precisions 2, 3: the class rows in the pair layout (launch_class_rows)
+  const float* X32;        // precision 1: the class rows in FP32 (launch_class_rows)
+  const double* op64;      // the matrix, or with sym its blocks (launch_class_operator)
   const float* op32;
-  const uint16_t* opp;     // precisions 2, 3: the operator in the pair layout, N rows
+  const uint16_t* opp;     // precisions 2, 3: the operator in the pair layout
   double* acc;
   int64_t M;
-  int N, K;
-  int splits;        // split-K factor (grid.z)
+  int N, K;                // without sym
+  const SymMap* sym;       // null: a plain product
+  int cells_own_rows;      // tile 1 of FP64 and the bf16 forms: X holds the cells' rows, whose class
+                           // sums are formed while staging
+  int splits;        // split-K factor
   int tile;          // tile configuration id: 0 (128 x 128), 2 (64 x 128), 1 (32 x 128) with 16-deep
                      // double-buffered stages (64-deep single-buffered for the bf16 forms; FP64 tile 0:
-                     // eight waves, LDS-DMA stages of k pairs, for K <= 2^20); FP64 only:
+                     // eight waves, LDS-DMA stages of k pairs, for row strides <= 2^20); FP64 only:
                      // 3 (128 x 128), 4 (64 x 128) with 32-deep single-buffered stages; BF16X3 only:
                      // 5 (256 x 256, 32-deep LDS-DMA stages in two buffers; gemm_wide_fits).
                      // FP64 needs K even (hipErrorInvalidValue otherwise).
 };
 int gemm_tile_rows(int tile);
 int gemm_tile_depth(int tile, int precision);
-// whether the 256 x 256 BF16X3 tile takes M cells against N operator rows of K
+// whether the 256 x 256 BF16X3 tile takes M cells of nb classes against N operator rows of K
 // (both pair arrays under 4 GiB: its loads use 32-bit offsets)
-bool gemm_wide_fits(int64_t M, int N, int K);
+bool gemm_wide_fits(int64_t M, int N, int K, int nb);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
-// x = X - Xref (Xref may be null) -> FP32; count = M * K
-hipError_t launch_convert_x_f32(const double* X, const double* Xref, int64_t count, float* out, hipStream_t s);
 int gemm_k_per_split(int K, int splits);
 
 // Rows are (cell, species) pairs of n3 values: row = cell * nsp + species.  A row holds the
@@ -77,7 +113,9 @@ struct FinishArgs {
   double mass_ratio[2];    // m_s / m_A (1 for one gas)
   int64_t n_cells;         // rows = cells * nsp
   int splits;              // split-K partial sums in acc (0: the contraction is zero)
-  const double* acc;       // [splits][rows][n3]
+  const double* acc;       // [splits][rows][n3]; with classes (sym.logb > 0) [splits][cells][nb][ld]
+  int64_t acc_stride;      // with classes: elements between splits
+  SymMap sym;
   const double* h;         // [rows][n3]
   const double* dU;        // [rows] or null
   const double* delta;     // [cells]
@@ -94,9 +132,9 @@ struct FinishArgs {
   //  mode 1 (refresh):     acc is op*h in FP64; store accref = acc, xref = h
   //  mode 2 (incremental): acc is op~*(h - xref); use accref + acc
   int anchor_mode;
-  double* accref;          // [n_cells][n3]
+  double* accref;          // [n_cells][n3]; with classes [cells][nb][ld]
   double* xref;            // [n_cells][n3]
-  double* rhs;             // [n_cells][n3]  (may alias acc when splits == 1)
+  double* rhs;             // [n_cells][n3]  (without classes may alias acc when splits == 1)
   double* lh;              // [n_cells][n3] or null
   double* amom;            // [n_cells][4] or null
 };

@@ -3,6 +3,8 @@
 //  assemble      plan-time: dense matrix of h -> L+(h) from the fast-spectral
 //                real-space kernels (one 32x32 output tile per workgroup,
 //                direction tables staged through LDS)
+//  class_rows    the cells' sums over the reflections that commute with the operator (FP64,
+//                FP32 or bf16 pairs): the contraction then runs on one small matrix per class
 //  gemm          collision contraction acc = X * op^T on MFMA
 //                (FP64 v_mfma_f64_16x16x4; FP32 / 3xBF16 variants)
 //  finish        per-cell epilogue: correction of eq. guided, delta scaling,
@@ -145,6 +147,143 @@ __global__ void convert_f32_kernel(const double* __restrict__ in, float* __restr
   if (i < count) out[i] = static_cast<float>(in[i]);
 }
 
+// ------------------------------------------------------------------ reflection classes
+// Images of orbit k of a row (see SymMap): off[g], bit a of g reflecting the a-th reflected axis.
+// With PAIR the images of orbit k + 1 follow at off[g] + 1, or at off[g] - 1 where the third axis
+// (LOGB = 3, top bit of g) is reflected.
+template <int LOGB>
+__device__ __forceinline__ void orbit_images(const SymMap& m, int k, int (&off)[1 << LOGB]) {
+  // k / d with the multiplier ceil(2^32 / d): exact while k d < 2^32
+  const int j1 = m.d23r == 1 ? k : static_cast<int>(__umulhi(static_cast<unsigned>(k), m.mul23));
+  const int r = k - j1 * m.d23r;
+  const int j2 = m.d3r == 1 ? r : static_cast<int>(__umulhi(static_cast<unsigned>(r), m.mul3));
+  const int j3 = r - j2 * m.d3r;
+  const int base = (m.lo1 + j1) * m.s1 + (m.lo2 + j2) * m.s2 + m.lo3 + j3;
+  int e[3];
+  if constexpr (LOGB == 1) {
+    e[0] = m.lo1 ? (2 * j1 + 1) * m.s1 : (2 * j2 + 1) * m.s2;
+  } else {
+    e[0] = (2 * j1 + 1) * m.s1;
+    e[1] = (2 * j2 + 1) * m.s2;
+    e[2] = 2 * j3 + 1;
+  }
+#pragma unroll
+  for (int g = 0; g < (1 << LOGB); ++g) {
+    int o = base;
+#pragma unroll
+    for (int a = 0; a < LOGB; ++a)
+      if (g & (1 << a)) o -= e[a];
+    off[g] = o;
+  }
+}
+
+// Sums over the images with the signs of every class (bit a of the class: odd under reflection
+// a), in place; applied to the class sums it gives back the values at the images times 2^LOGB.
+template <int LOGB, class T>
+__device__ __forceinline__ void class_sums(T (&v)[1 << LOGB]) {
+#pragma unroll
+  for (int a = 0; a < LOGB; ++a)
+#pragma unroll
+    for (int g = 0; g < (1 << LOGB); ++g)
+      if (!(g & (1 << a))) {
+        const T p = v[g], q = v[g | (1 << a)];
+        v[g] = p + q;
+        v[g | (1 << a)] = p - q;
+      }
+}
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+// Orbits k, k + 1 (k even, an even number of orbits along the third axis) of a row as 16-byte pairs.
+template <int LOGB>
+__device__ __forceinline__ v2d image_pair(const double* __restrict__ row, const int (&off)[1 << LOGB], int g) {
+  if (LOGB == 3 && g >= 4) {
+    const v2d t = *reinterpret_cast<const v2d*>(row + off[g] - 1);
+    return v2d{t.y, t.x};
+  }
+  return *reinterpret_cast<const v2d*>(row + off[g]);
+}
+template <int LOGB>
+__device__ __forceinline__ void image_pair_store(double* __restrict__ row, const int (&off)[1 << LOGB], int g, v2d v) {
+  if (LOGB == 3 && g >= 4)
+    *reinterpret_cast<v2d*>(row + off[g] - 1) = v2d{v.y, v.x};
+  else
+    *reinterpret_cast<v2d*>(row + off[g]) = v;
+}
+
+// Block row entries kk, kk + 1 (kk even) of class b, from one cell's rows X (minus Xref if given):
+// the contraction tiles that read the cells themselves use it while staging.
+template <int LOGB>
+__device__ __forceinline__ double2 class_entry_pair(const SymMap& m, const double* __restrict__ X,
+                                                    const double* __restrict__ Xref, int b, int kk) {
+  double2 s = make_double2(0.0, 0.0);
+  if (m.pairs) {
+    if (kk >= m.kb) return s;
+    const int sp = kk >= m.nvb;
+    int off[1 << LOGB];
+    orbit_images<LOGB>(m, kk - sp * m.nvb, off);
+    const int64_t r0 = static_cast<int64_t>(sp) * m.nv;
+    v2d v[1 << LOGB];
+#pragma unroll
+    for (int g = 0; g < (1 << LOGB); ++g) v[g] = image_pair<LOGB>(X + r0, off, g);
+    if (Xref)
+#pragma unroll
+      for (int g = 0; g < (1 << LOGB); ++g) v[g] -= image_pair<LOGB>(Xref + r0, off, g);
+#pragma unroll
+    for (int g = 0; g < (1 << LOGB); ++g) {
+      const bool neg = __builtin_popcount(b & g) & 1;
+      s.x += neg ? -v[g].x : v[g].x;
+      s.y += neg ? -v[g].y : v[g].y;
+    }
+    return s;
+  }
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    if (kk + e >= m.kb) break;
+    const int sp = kk + e >= m.nvb;
+    int off[1 << LOGB];
+    orbit_images<LOGB>(m, kk + e - sp * m.nvb, off);
+    const int64_t r0 = static_cast<int64_t>(sp) * m.nv;
+    double t = 0.0;
+#pragma unroll
+    for (int g = 0; g < (1 << LOGB); ++g) {
+      const double v = Xref ? X[r0 + off[g]] - Xref[r0 + off[g]] : X[r0 + off[g]];
+      t += (__builtin_popcount(b & g) & 1) ? -v : v;
+    }
+    (e ? s.y : s.x) = t;
+  }
+  return s;
+}
+
+// Blocks of the operator on the classes: with T_r = sum_g K[g i][(g ^ r) j] over the images g of
+// the row and column orbits, class b has (1 / nb^2) sum_r (-1)^|b & r| T_r.
+template <int LOGB>
+__global__ __launch_bounds__(256) void class_operator_kernel(SymMap m, const double* __restrict__ op,
+                                                             double* __restrict__ out) {
+  constexpr int NB = 1 << LOGB;
+  const int j = blockIdx.x * 256 + threadIdx.x, i = blockIdx.y;
+  if (j >= m.ld) return;
+  const int64_t n = static_cast<int64_t>(m.nsp) * m.nv;
+  double t[NB];
+#pragma unroll
+  for (int r = 0; r < NB; ++r) t[r] = 0.0;
+  if (j < m.kb) {
+    const int si = i >= m.nvb, sj = j >= m.nvb;
+    int oi[NB], oj[NB];
+    orbit_images<LOGB>(m, i - si * m.nvb, oi);
+    orbit_images<LOGB>(m, j - sj * m.nvb, oj);
+#pragma unroll
+    for (int g = 0; g < NB; ++g) {
+      const double* row = op + (static_cast<int64_t>(si) * m.nv + oi[g]) * n + static_cast<int64_t>(sj) * m.nv;
+#pragma unroll
+      for (int r = 0; r < NB; ++r) t[r] += row[oj[g ^ r]];
+    }
+    class_sums<LOGB>(t);
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+    out[(static_cast<int64_t>(b) * m.kb + i) * m.ld + j] = t[b] * (1.0 / (NB * NB));
+}
+
 __device__ inline uint16_t bf16_rne(float f) {
   const uint32_t b = __float_as_uint(f);
   const uint32_t r = b + 0x7FFFu + ((b >> 16) & 1u);
@@ -152,25 +291,94 @@ __device__ inline uint16_t bf16_rne(float f) {
 }
 __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
 
+__device__ __forceinline__ void bf16_pair(double x, uint32_t& hi, uint32_t& lo) {
+  const uint16_t h = bf16_rne(static_cast<float>(x));
+  hi = h;
+  lo = bf16_rne(static_cast<float>(x - static_cast<double>(bf16_to_f32(h))));
+}
+
+// Cell operand of the contraction, once per launch: the class sums of x = X - Xref (Xref null: X)
+// over each orbit's images, formed in FP64 and written as block rows
+//   OUT 0: FP64 [cell][nb][ld];  1: rounded to FP32 [cell][nb][ld];
+//   2, 3: the bf16 pair layout [cell][nb][2 Kp] (3: lo parts zero),
+// entries past the classes' orbits zero.  Bound by HBM: it reads the distribution and writes as
+// many values, 16 bytes per lane and access (the third axis is contiguous and keeps its order
+// or is reversed whole): 24 576 cells of 6912 in FP64 0.52 ms = 5.2 TB/s.  What it buys there: the
+// FP64 contraction of 4 blocks of 1728^2 takes 8.2 ms instead of 32.5 ms for the whole 6912^2.
+template <int LOGB, int OUT, bool PAIR>
+__global__ __launch_bounds__(256) void class_rows_kernel(SymMap m, const double* __restrict__ X,
+                                                         const double* __restrict__ Xref,
+                                                         const int32_t* __restrict__ active, int row_len, void* out) {
+  constexpr int NB = 1 << LOGB;
+  const int64_t cell = blockIdx.x;
+  if (active && !active[cell]) return;
+  const int kk = (blockIdx.y * 256 + threadIdx.x) * 2;
+  if (kk >= row_len) return;
+  const int64_t c0 = cell * m.nsp * static_cast<int64_t>(m.nv);
+  v2d v[NB];
+#pragma unroll
+  for (int g = 0; g < NB; ++g) v[g] = v2d{0.0, 0.0};
+  if constexpr (PAIR) {
+    if (kk < m.kb) {
+      const int sp = kk >= m.nvb;
+      int off[NB];
+      orbit_images<LOGB>(m, kk - sp * m.nvb, off);
+      const int64_t r0 = c0 + static_cast<int64_t>(sp) * m.nv;
+#pragma unroll
+      for (int g = 0; g < NB; ++g) v[g] = image_pair<LOGB>(X + r0, off, g);
+      if (Xref)
+#pragma unroll
+        for (int g = 0; g < NB; ++g) v[g] -= image_pair<LOGB>(Xref + r0, off, g);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      if (kk + e < m.kb) {
+        const int sp = kk + e >= m.nvb;
+        int off[NB];
+        orbit_images<LOGB>(m, kk + e - sp * m.nvb, off);
+        const int64_t r0 = c0 + static_cast<int64_t>(sp) * m.nv;
+#pragma unroll
+        for (int g = 0; g < NB; ++g) v[g][e] = Xref ? X[r0 + off[g]] - Xref[r0 + off[g]] : X[r0 + off[g]];
+      }
+  }
+  class_sums<LOGB>(v);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int64_t row = cell * NB + b;
+    if constexpr (OUT == 0) {
+      *reinterpret_cast<v2d*>(static_cast<double*>(out) + row * row_len + kk) = v[b];
+    } else if constexpr (OUT == 1) {
+      *reinterpret_cast<float2*>(static_cast<float*>(out) + row * row_len + kk) =
+          make_float2(static_cast<float>(v[b].x), static_cast<float>(v[b].y));
+    } else {
+      uint32_t h0, l0, h1, l1;
+      bf16_pair(v[b].x, h0, l0);
+      bf16_pair(v[b].y, h1, l1);
+      uint16_t* p = static_cast<uint16_t*>(out) + row * 2 * row_len + (kk >> 5) * 64 + (kk & 31);
+      *reinterpret_cast<uint32_t*>(p) = h0 | (h1 << 16);
+      *reinterpret_cast<uint32_t*>(p + 32) = OUT == 2 ? l0 | (l1 << 16) : 0u;
+    }
+  }
+}
+
 // BF16 pair layout of the low-precision contraction operands (rows of K values,
 // stored with Kp = K rounded up to 64): row r occupies 2 Kp bf16, and each block of
 // 32 k-values holds its 32 hi parts followed by their 32 lo parts, so that one
 // 128-byte line carries everything a 32-deep stage needs of the row.  Entries
-// k >= K are zero in both halves.  x = X - Xref (Xref null: X); hi = RNE(x),
-// lo = RNE(x - hi), or lo = 0 when with_lo is 0.
-__global__ void split_pairs_kernel(const double* __restrict__ X, const double* __restrict__ Xref, int64_t rows,
-                                   int K, int Kp, uint16_t* __restrict__ P, int with_lo) {
+// k >= K are zero in both halves; hi = RNE(x), lo = RNE(x - hi).  This kernel writes
+// the operator's rows (row stride ld); class_rows_kernel writes the cells'.
+__global__ void split_pairs_kernel(const double* __restrict__ X, int64_t rows, int K, int ld, int Kp,
+                                   uint16_t* __restrict__ P) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= rows * Kp) return;
   const int64_t r = i / Kp;
   const int k = static_cast<int>(i - r * Kp);
-  double x = 0.0;
-  if (k < K) x = Xref ? X[r * K + k] - Xref[r * K + k] : X[r * K + k];
-  const uint16_t h = bf16_rne(static_cast<float>(x));
-  const uint16_t l = with_lo ? bf16_rne(static_cast<float>(x - static_cast<double>(bf16_to_f32(h)))) : 0;
+  uint32_t h, l;
+  bf16_pair(k < K ? X[r * ld + k] : 0.0, h, l);
   uint16_t* row = P + r * 2 * Kp + (k >> 5) * 64 + (k & 31);
-  row[0] = h;
-  row[32] = l;
+  row[0] = static_cast<uint16_t>(h);
+  row[32] = static_cast<uint16_t>(l);
 }
 
 // ------------------------------------------------------------------ FP64 MFMA GEMM
@@ -207,10 +415,12 @@ __device__ inline int2 xcd_tile() {
 
 // One output tile (operator tile bx, cell tile by, split bz) of the FP64 contraction; called by
 // gemm_f64_kernel with the block indices and by the persistent 1-D iteration over virtual tiles.
-template <int BM, int BN, int WM, int WN, int BK = kBK, int NBUF = 2, int PAD = kPad>
-__device__ __forceinline__ void gemm_f64_tile(const double* __restrict__ X, const double* __restrict__ Op,
-                                              double* __restrict__ C, int64_t M, int N, int K, int kps, int bx,
-                                              int by, int bz) {
+// LOGB >= 0: X is the cells' own rows, their class sums formed while staging (few-cell tiles,
+// which are bound by launch latency); otherwise block rows.
+template <int BM, int BN, int WM, int WN, int BK = kBK, int NBUF = 2, int PAD = kPad, int LOGB = -1>
+__device__ __forceinline__ void gemm_f64_tile(const GemmShape& sh, const double* __restrict__ X0,
+                                              const double* __restrict__ Op0, double* __restrict__ C0, int bx,
+                                              int by, int bz, const SymMap& sym) {
   constexpr int WAVES_N = BN / WN;
   constexpr int TM = WM / 16, TN = WN / 16;
   constexpr int A_LD = BM * BK / 2 / 256;
@@ -223,11 +433,16 @@ __device__ __forceinline__ void gemm_f64_tile(const double* __restrict__ X, cons
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave / WAVES_N) * WM, wn = (wave % WAVES_N) * WN;
   // plain grid order: the MFMA-bound FP64 tiles measured no faster (planar batch slower) with xcd_tile()
+  const int64_t M = sh.M;
+  const int N = sh.N, ldx = sh.ldx, ldo = sh.ldo;
   const int64_t m0 = static_cast<int64_t>(by) * BM;
   const int n0 = bx * BN;
-  const int kbeg = bz * kps;
-  const int kend = min(K, kbeg + kps);
-  double* Cz = C + static_cast<int64_t>(bz) * M * N;
+  const int block = bz / sh.splits, split = bz - block * sh.splits;
+  const int kbeg = split * sh.kps;
+  const int kend = min(sh.K, kbeg + sh.kps);
+  const double* X = LOGB >= 0 ? X0 : X0 + block * sh.xs;
+  const double* Op = Op0 + block * sh.os;
+  double* Cz = C0 + split * sh.cz + block * sh.cs;
 
   double2 ra[A_LD], rb[B_LD];
   auto gload = [&](int k0) {
@@ -237,8 +452,12 @@ __device__ __forceinline__ void gemm_f64_tile(const double* __restrict__ X, cons
       const int r = q / (BK / 2), kc = (q % (BK / 2)) * 2;
       const int64_t gm = m0 + r;
       const int gk = k0 + kc;
-      ra[i] = (gm < M && gk < kend) ? *reinterpret_cast<const double2*>(X + gm * K + gk)
-                                    : make_double2(0.0, 0.0);
+      if constexpr (LOGB >= 0)
+        ra[i] = (gm < M && gk < kend) ? class_entry_pair<LOGB>(sym, X + gm * ldx, nullptr, block, gk)
+                                      : make_double2(0.0, 0.0);
+      else
+        ra[i] = (gm < M && gk < kend) ? *reinterpret_cast<const double2*>(X + gm * ldx + gk)
+                                      : make_double2(0.0, 0.0);
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
@@ -247,7 +466,7 @@ __device__ __forceinline__ void gemm_f64_tile(const double* __restrict__ X, cons
       const int gn = n0 + r;
       const int gk = k0 + kc;
       rb[i] = (gn < N && gk < kend)
-                  ? *reinterpret_cast<const double2*>(Op + static_cast<int64_t>(gn) * K + gk)
+                  ? *reinterpret_cast<const double2*>(Op + static_cast<int64_t>(gn) * ldo + gk)
                   : make_double2(0.0, 0.0);
     }
   };
@@ -365,14 +584,14 @@ __device__ __forceinline__ void gemm_f64_tile(const double* __restrict__ X, cons
       for (int r = 0; r < 4; ++r) {
         const int64_t gm = m0 + wm + i * 16 + kr + 4 * r;
         const int gn = n0 + wn + j * 16 + cc;
-        if (gm < M && gn < N) Cz[gm * N + gn] = acc[i][j][r];
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = acc[i][j][r];
       }
 }
 
-template <int BM, int BN, int WM, int WN, int BK = kBK, int NBUF = 2, int PAD = kPad>
+template <int BM, int BN, int WM, int WN, int BK = kBK, int NBUF = 2, int PAD = kPad, int LOGB = -1>
 __global__ __launch_bounds__(256) void gemm_f64_kernel(const double* __restrict__ X, const double* __restrict__ Op,
-                                                       double* __restrict__ C, int64_t M, int N, int K, int kps) {
-  gemm_f64_tile<BM, BN, WM, WN, BK, NBUF, PAD>(X, Op, C, M, N, K, kps, blockIdx.x, blockIdx.y, blockIdx.z);
+                                                       double* __restrict__ C, GemmShape sh, SymMap sym) {
+  gemm_f64_tile<BM, BN, WM, WN, BK, NBUF, PAD, LOGB>(sh, X, Op, C, blockIdx.x, blockIdx.y, blockIdx.z, sym);
 }
 
 // FP64 contraction on 128 x 128 tiles with LDS-DMA staging: the 128-row tile of the
@@ -398,11 +617,10 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(const double* __restrict_
 // stage have completed; after it the next stage is visible to every wave and the current
 // buffer is free, so the next stage's first reads are issued, then the DMA of the stage
 // after it into the freed buffer, then the MFMAs of the current stage's second step.
-// Preconditions (checked by the launcher): K even, K <= 2^20 (32-bit offsets within a
-// tile's 128 rows).
+// Preconditions (checked by the launcher): K even, row strides <= 2^20 (32-bit offsets within
+// a tile's 128 rows).
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void gemm_f64_dma_kernel(
-    const double* __restrict__ X, const double* __restrict__ Op, double* __restrict__ C, int64_t M, int N, int K,
-    int kps) {
+    const double* __restrict__ X0, const double* __restrict__ Op0, double* __restrict__ C0, GemmShape sh) {
   __shared__ double2 buf0[2048];   // [operand][pair 0..7][row 0..127]
   __shared__ double2 buf1[2048];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -410,39 +628,46 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void g
   // tiles to the XCDs in runs walked in groups of 8 cell-tile rows: the duct's fabric traffic
   // drops from 95 to 40 GB per launch at equal speed (groups of 2, 4, 16, 32: 68, 53, 45, 85 GB)
   const int2 tile = xcd_tile<8>();
+  const int64_t M = sh.M;
+  const int N = sh.N, ldx = sh.ldx, ldo = sh.ldo;
   const int64_t m0 = static_cast<int64_t>(tile.y) * 128;
   const int n0 = tile.x * 128;
-  const int kbeg = blockIdx.z * kps;
-  const int kend = min(K, kbeg + kps);
+  const int block = blockIdx.z / sh.splits, split = blockIdx.z - block * sh.splits;
+  const int kbeg = split * sh.kps;
+  const int kend = min(sh.K, kbeg + sh.kps);
   const int nk = kend > kbeg ? (kend - kbeg + 15) / 16 : 0;
-  double* Cz = C + static_cast<int64_t>(blockIdx.z) * M * N;
+  const double* X = X0 + block * sh.xs;
+  const double* Op = Op0 + block * sh.os;
+  double* Cz = C0 + split * sh.cz + block * sh.cs;
 
+  // the last valid row ends after its K values (a block row may be the last of its array)
   const int rows_a = static_cast<int>(min<int64_t>(128, M - m0));
   const int rows_b = min(128, N - n0);
-  const __amdgpu_buffer_rsrc_t rs_a =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(X + m0 * K), 0, rows_a * K * 8, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<double*>(X + m0 * ldx), 0, ((rows_a - 1) * ldx + sh.K) * 8, 0x00020000);
   const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<double*>(Op + static_cast<int64_t>(n0) * K), 0, rows_b * K * 8, 0x00020000);
+      const_cast<double*>(Op + static_cast<int64_t>(n0) * ldo), 0, ((rows_b - 1) * ldo + sh.K) * 8, 0x00020000);
   // per DMA instruction j of this wave: the lane's pair and its byte offset within the tile
-  uint32_t roff[2];
+  uint32_t roff_a[2], roff_b[2];
   int pj[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int slot = (8 * j + wave) * 64 + lane;
     pj[j] = slot >> 7;
-    roff[j] = static_cast<uint32_t>(((slot & 127) * K + 2 * pj[j]) * 8);
+    roff_a[j] = static_cast<uint32_t>(((slot & 127) * ldx + 2 * pj[j]) * 8);
+    roff_b[j] = static_cast<uint32_t>(((slot & 127) * ldo + 2 * pj[j]) * 8);
   }
   auto issue = [&](double2* buf, int k0) {
     const int krem = kend - k0;
     const uint32_t kb = static_cast<uint32_t>(k0) * 8u;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const uint32_t vo = 2 * pj[j] < krem ? roff[j] + kb : 0x80000000u;
+      const uint32_t vo = 2 * pj[j] < krem ? roff_a[j] + kb : 0x80000000u;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_void_t*)&buf[(8 * j + wave) * 64], 16, vo, 0, 0, 0);
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const uint32_t vo = 2 * pj[j] < krem ? roff[j] + kb : 0x80000000u;
+      const uint32_t vo = 2 * pj[j] < krem ? roff_b[j] + kb : 0x80000000u;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_void_t*)&buf[1024 + (8 * j + wave) * 64], 16, vo, 0, 0,
                                                0);
     }
@@ -525,17 +750,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void g
       for (int r = 0; r < 4; ++r) {
         const int64_t gm = m0 + wm + i * 16 + kq + 4 * r;
         const int gn = n0 + wn + j * 16 + cc;
-        if (gm < M && gn < N) Cz[gm * N + gn] = acc[i][j][r];
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = acc[i][j][r];
       }
 }
 
 // ------------------------------------------------------------------ FP32 MFMA GEMM
-// X is converted from double to float when staged; op is stored as float.
+// Both operands are stored as float (class_rows_kernel rounds the cells' class sums).
 template <int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ X,
-                                                       const float* __restrict__ Op,
-                                                       double* __restrict__ C, int64_t M, int N,
-                                                       int K, int kps) {
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ X0, const float* __restrict__ Op0,
+                                                       double* __restrict__ C0, GemmShape sh) {
   constexpr int BK = 32;
   constexpr int WAVES_N = BN / WN;
   constexpr int TM = WM / 16, TN = WN / 16;
@@ -548,11 +771,16 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave / WAVES_N) * WM, wn = (wave % WAVES_N) * WN;
+  const int64_t M = sh.M;
+  const int N = sh.N, ldx = sh.ldx, ldo = sh.ldo;
   const int64_t m0 = static_cast<int64_t>(blockIdx.y) * BM;
   const int n0 = blockIdx.x * BN;
-  const int kbeg = blockIdx.z * kps;
-  const int kend = min(K, kbeg + kps);
-  double* Cz = C + static_cast<int64_t>(blockIdx.z) * M * N;
+  const int block = blockIdx.z / sh.splits, split = blockIdx.z - block * sh.splits;
+  const int kbeg = split * sh.kps;
+  const int kend = min(sh.K, kbeg + sh.kps);
+  const float* X = X0 + block * sh.xs;
+  const float* Op = Op0 + block * sh.os;
+  double* Cz = C0 + split * sh.cz + block * sh.cs;
 
   float4 ra[A_LD];
   float4 rb[B_LD];
@@ -564,10 +792,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       const int64_t gm = m0 + r;
       const int gk = k0 + kc;
       if (gm < M && gk + 3 < kend) {
-        ra[i] = *reinterpret_cast<const float4*>(X + gm * K + gk);
+        ra[i] = *reinterpret_cast<const float4*>(X + gm * ldx + gk);
       } else {
         float t[4];
-        for (int e = 0; e < 4; ++e) t[e] = (gm < M && gk + e < kend) ? X[gm * K + gk + e] : 0.0f;
+        for (int e = 0; e < 4; ++e) t[e] = (gm < M && gk + e < kend) ? X[gm * ldx + gk + e] : 0.0f;
         ra[i] = make_float4(t[0], t[1], t[2], t[3]);
       }
     }
@@ -578,11 +806,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       const int gn = n0 + r;
       const int gk = k0 + kc;
       if (gn < N && gk + 3 < kend) {
-        rb[i] = *reinterpret_cast<const float4*>(Op + static_cast<int64_t>(gn) * K + gk);
+        rb[i] = *reinterpret_cast<const float4*>(Op + static_cast<int64_t>(gn) * ldo + gk);
       } else {
         float t[4];
         for (int e = 0; e < 4; ++e)
-          t[e] = (gn < N && gk + e < kend) ? Op[static_cast<int64_t>(gn) * K + gk + e] : 0.0f;
+          t[e] = (gn < N && gk + e < kend) ? Op[static_cast<int64_t>(gn) * ldo + gk + e] : 0.0f;
         rb[i] = make_float4(t[0], t[1], t[2], t[3]);
       }
     }
@@ -648,14 +876,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       for (int r = 0; r < 4; ++r) {
         const int64_t gm = m0 + wm + i * 16 + kr * 4 + r;
         const int gn = n0 + wn + j * 16 + cc;
-        if (gm < M && gn < N) Cz[gm * N + gn] = static_cast<double>(acc[i][j][r]);
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = static_cast<double>(acc[i][j][r]);
       }
 }
 
 // ------------------------------------------------------------------ 3xBF16 MFMA GEMM
 // x ~ xh + xl, op ~ oh + ol (bf16 pairs); acc += xl*oh + xh*ol + xh*oh on
 // v_mfma_f32_16x16x32_bf16 with FP32 accumulation.  Both operands arrive in the
-// pair layout of split_pairs_kernel (the cell operand is split once per launch
+// pair layout of class_rows_kernel (the cell operand is split once per launch
 // instead of once per output tile; Kp is a multiple of 64, so every stage is
 // full).  k-stage of 64 staged through one LDS buffer per operand half; the next
 // stage is prefetched into registers while the current one feeds the MFMAs.
@@ -663,13 +891,16 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // NPROD = 1: the hi*hi product alone (lo halves neither loaded nor staged).
-// FUSED (32-row tile only): the cell operand is read in FP64 (X, minus Xref when given; K values
-// per row) and split into its hi and lo parts while it is staged, exactly as split_pairs_kernel
-// does, so that a launch on few cells needs no separate split kernel; results are bit-identical.
-template <int BM, int BN, int WM, int WN, int NPROD = 3, bool FUSED = false>
+// LOGB >= 0 (32-row tile only): the cells' own rows are read in FP64 (X, minus Xref when given) and
+// their class sums formed and split into hi and lo parts while they are staged, exactly as
+// class_rows_kernel does, so that a launch on few cells needs no separate kernel; results are
+// bit-identical.
+// Row strides and block offsets of Xp and Op (sh.ldx, ldo, xs, os) are in bf16.
+template <int BM, int BN, int WM, int WN, int NPROD = 3, int LOGB = -1>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_bf16x3_kernel(
-    const uint16_t* __restrict__ Xp, const uint16_t* __restrict__ Op, double* __restrict__ C, int64_t M, int N, int Kp,
-    int kps, const double* __restrict__ X, const double* __restrict__ Xref, int K) {
+    const uint16_t* __restrict__ Xp0, const uint16_t* __restrict__ Op0, double* __restrict__ C0, GemmShape sh,
+    const double* __restrict__ X, const double* __restrict__ Xref, SymMap sym) {
+  constexpr bool FUSED = LOGB >= 0;
   constexpr int BK = 64;                      // two MFMA k-steps per stage
   constexpr int WAVES_N = BN / WN;
   constexpr int TM = WM / 16, TN = WN / 16;
@@ -698,38 +929,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   const int rsw = (lane & 15) >> 1;
   const int rslot0 = ((lane >> 4) ^ rsw) << 3, rslot1 = ((4 + (lane >> 4)) ^ rsw) << 3;
   const int2 tile = xcd_tile();
+  const int64_t M = sh.M;
+  const int N = sh.N;
   const int64_t m0 = static_cast<int64_t>(tile.y) * BM;
   const int n0 = tile.x * BN;
-  const int kbeg = blockIdx.z * kps;
-  const int kend = min(Kp, kbeg + kps);
-  double* Cz = C + static_cast<int64_t>(blockIdx.z) * M * N;
+  const int block = blockIdx.z / sh.splits, split = blockIdx.z - block * sh.splits;
+  const int kbeg = split * sh.kps;
+  const int kend = min(sh.K, kbeg + sh.kps);
+  const uint16_t* Xp = Xp0 + block * sh.xs;
+  const uint16_t* Op = Op0 + block * sh.os;
+  double* Cz = C0 + split * sh.cz + block * sh.cs;
 
   // (native vectors: HIP's uint4 struct copies from global memory kept the staging in scratch)
   u32x4 ra[2][A_LD], rb[2][B_LD];
   static_assert(!FUSED || A_LD == 1, "the fused split stages one chunk of eight values per thread");
-  double2 xa[4], xr[4];   // FUSED: the eight FP64 values of the thread's chunk (and of the anchor)
+  double2 xa[4];   // FUSED: the eight FP64 class sums of the thread's chunk
   // hi chunk of (row, k), k a multiple of 8 (its lo chunk sits 32 entries further);
   // rows past M or N read the last row: their products land in outputs that are
   // not stored
-  auto pair_off = [&](int64_t row, int k) -> int64_t { return row * 2 * Kp + (k >> 5) * 64 + (k & 31); };
+  auto pair_off = [&](int64_t row, int ld, int k) -> int64_t { return row * ld + (k >> 5) * 64 + (k & 31); };
   auto gload = [&](int k0) {
     if constexpr (FUSED) {
-      const int64_t row = m0 + tid / CH;
+      const int64_t row = min<int64_t>(m0 + tid / CH, M - 1) * sym.nsp * static_cast<int64_t>(sym.nv);
       const int k = k0 + (tid % CH) * 8;
-      const double2* x2 = reinterpret_cast<const double2*>(X + (row < M ? row : M - 1) * K);
-      const double2* r2 = Xref ? reinterpret_cast<const double2*>(Xref + (row < M ? row : M - 1) * K) : nullptr;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const bool in = k + 2 * j < K;   // K even: a pair is wholly inside or outside
-        xa[j] = in ? x2[(k >> 1) + j] : make_double2(0.0, 0.0);
-        xr[j] = in && r2 ? r2[(k >> 1) + j] : make_double2(0.0, 0.0);
-      }
+      for (int j = 0; j < 4; ++j)
+        xa[j] = class_entry_pair<FUSED ? LOGB : 1>(sym, X + row, Xref ? Xref + row : nullptr, block, k + 2 * j);
     } else {
 #pragma unroll
       for (int i = 0; i < A_LD; ++i) {
         const int q = tid + 256 * i;
         const int64_t row = m0 + q / CH;
-        const int64_t off = pair_off(row < M ? row : M - 1, k0 + (q % CH) * 8);
+        const int64_t off = pair_off(row < M ? row : M - 1, sh.ldx, k0 + (q % CH) * 8);
         ra[0][i] = *reinterpret_cast<const u32x4*>(Xp + off);
         if constexpr (NPROD == 3) ra[1][i] = *reinterpret_cast<const u32x4*>(Xp + off + 32);
       }
@@ -738,25 +969,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
     for (int i = 0; i < B_LD; ++i) {
       const int q = tid + 256 * i;
       const int64_t row = n0 + q / CH;
-      const int64_t off = pair_off(row < N ? row : N - 1, k0 + (q % CH) * 8);
+      const int64_t off = pair_off(row < N ? row : N - 1, sh.ldo, k0 + (q % CH) * 8);
       rb[0][i] = *reinterpret_cast<const u32x4*>(Op + off);
       if constexpr (NPROD == 3) rb[1][i] = *reinterpret_cast<const u32x4*>(Op + off + 32);
     }
   };
   auto sstore = [&]() {
     if constexpr (FUSED) {
-      // x - xref rounded to bf16 (hi), the remainder rounded again (lo), as in split_pairs_kernel
+      // rounded to bf16 (hi), the remainder rounded again (lo), as in class_rows_kernel
       uint32_t hw[4], lw[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const double x0 = xa[j].x - xr[j].x, x1 = xa[j].y - xr[j].y;
-        const uint16_t h0 = bf16_rne(static_cast<float>(x0)), h1 = bf16_rne(static_cast<float>(x1));
-        hw[j] = static_cast<uint32_t>(h0) | (static_cast<uint32_t>(h1) << 16);
-        if constexpr (NPROD == 3) {
-          const uint16_t l0 = bf16_rne(static_cast<float>(x0 - static_cast<double>(bf16_to_f32(h0))));
-          const uint16_t l1 = bf16_rne(static_cast<float>(x1 - static_cast<double>(bf16_to_f32(h1))));
-          lw[j] = static_cast<uint32_t>(l0) | (static_cast<uint32_t>(l1) << 16);
-        }
+        uint32_t h0, l0, h1, l1;
+        bf16_pair(xa[j].x, h0, l0);
+        bf16_pair(xa[j].y, h1, l1);
+        hw[j] = h0 | (h1 << 16);
+        lw[j] = l0 | (l1 << 16);
       }
       ra[0][0] = u32x4{hw[0], hw[1], hw[2], hw[3]};
       if constexpr (NPROD == 3) ra[1][0] = u32x4{lw[0], lw[1], lw[2], lw[3]};
@@ -832,7 +1060,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
       for (int r = 0; r < 4; ++r) {
         const int64_t gm = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
         const int gn = n0 + wn + j * 16 + (lane & 15);
-        if (gm < M && gn < N) Cz[gm * N + gn] = static_cast<double>(acc[i][j][r]);
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = static_cast<double>(acc[i][j][r]);
       }
 }
 
@@ -856,12 +1084,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 // hi*hi) so consecutive MFMAs update different accumulators.  Per output element
 // the MFMA sequence is that of the 128-row kernel (same k blocks of 32, same
 // product order), so the two agree to the last bit at equal split-K.
-// Preconditions (checked by the launcher): rows * 4 Kp < 2^32 bytes for both
-// operands (32-bit DMA offsets).
+// Preconditions (checked by the launcher): rows times row stride under 2^32 bytes for
+// both operands (32-bit DMA offsets).
 
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void gemm_bf16x3_wide_kernel(
-    const uint16_t* __restrict__ Xp, const uint16_t* __restrict__ Op, double* __restrict__ C, int64_t M, int N, int Kp,
-    int kps) {
+    const uint16_t* __restrict__ Xp0, const uint16_t* __restrict__ Op0, double* __restrict__ C0, GemmShape sh) {
   __shared__ uint4 buf0[512][8];
   __shared__ uint4 buf1[512][8];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -872,17 +1099,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
   const int2 tile = xcd_tile<4>();
   const int64_t m0 = static_cast<int64_t>(tile.y) * 256;
   const int n0 = tile.x * 256;
-  const int kbeg = blockIdx.z * kps;
-  const int kend = min(Kp, kbeg + kps);
+  const int64_t M = sh.M;
+  const int N = sh.N;
+  const int block = blockIdx.z / sh.splits, split = blockIdx.z - block * sh.splits;
+  const int kbeg = split * sh.kps;
+  const int kend = min(sh.K, kbeg + sh.kps);
   const int nk = kend > kbeg ? (kend - kbeg) / 32 : 0;
-  double* Cz = C + static_cast<int64_t>(blockIdx.z) * M * N;
+  double* Cz = C0 + split * sh.cz + block * sh.cs;
 
   // DMA sources: waves 0-3 fill buffer rows 0-255 (cells), waves 4-7 rows 256-511
   // (operator rows), eight runs of eight rows each; rows past M or N read the last
   // row (their products land in outputs that are not stored)
   const bool isB = wave >= 4;
-  const char* gbase = reinterpret_cast<const char*>(isB ? Op : Xp);
+  const char* gbase = reinterpret_cast<const char*>(isB ? Op0 + block * sh.os : Xp0 + block * sh.xs);
   const int64_t rows = isB ? N : M;
+  const int64_t row_bytes = 2 * static_cast<int64_t>(isB ? sh.ldo : sh.ldx);
   const int64_t row0 = isB ? n0 : m0;
   uint32_t off[8];
 #pragma unroll
@@ -890,7 +1121,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
     const int r = (wave & 3) * 64 + i * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((r >> 1) & 7);
     const int64_t grow = min(row0 + r, rows - 1);
-    off[i] = static_cast<uint32_t>(grow * 4 * Kp + (c >> 2) * 64 + (c & 3) * 16);
+    off[i] = static_cast<uint32_t>(grow * row_bytes + (c >> 2) * 64 + (c & 3) * 16);
   }
   auto issue = [&](uint4(*buf)[8], int k0) {
     const uint32_t kb = static_cast<uint32_t>(k0) * 4u;
@@ -1007,25 +1238,47 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
       for (int r = 0; r < 4; ++r) {
         const int64_t gm = m0 + wm + i * 16 + q * 4 + r;
         const int gn = n0 + wn + j * 16 + rr;
-        if (gm < M && gn < N) Cz[gm * N + gn] = static_cast<double>(acc[i][j][r]);
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = static_cast<double>(acc[i][j][r]);
       }
 }
 
-// Cell operand of the FP32 contraction, formed once per launch: x = X - Xref
-// (Xref null: X) rounded to FP32.
-__global__ void convert_x_f32_kernel(const double* __restrict__ X, const double* __restrict__ Xref, int64_t count,
-                                     float* __restrict__ out) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  out[i] = static_cast<float>(Xref ? X[i] - Xref[i] : X[i]);
+// ------------------------------------------------------------------ finish
+// Projection and moments of a finished row (rhs and lh of the whole row written by this workgroup).
+__device__ __forceinline__ void finish_tail(const FinishArgs& a, int64_t c, double (&m)[9]) {
+  __shared__ double sh[4 * 9];
+  __shared__ double coef[5];
+  block_sum<9>(m, sh);
+  if (a.project) {
+    if (threadIdx.x < 5) {
+      double s = 0.0;
+      for (int k = 0; k < 5; ++k) s += a.gram_inv[threadIdx.x * 5 + k] * m[k];
+      coef[threadIdx.x] = s;
+    }
+    __syncthreads();
+    const int n3 = a.n3;
+    const int64_t base = c * n3;
+    const double *vt1 = a.vtab, *vt2 = a.vtab + n3, *vt3 = a.vtab + 2 * static_cast<int64_t>(n3);
+    const double* feq = a.feq + static_cast<int64_t>(c % a.nsp) * n3;
+    for (int v = threadIdx.x; v < n3; v += blockDim.x) {
+      const double v1 = vt1[v], v2 = vt2[v], v3 = vt3[v];
+      const double vsq = v1 * v1 + v2 * v2 + v3 * v3;
+      const double corr = feq[v] * (coef[0] + coef[1] * v1 + coef[2] * v2 + coef[3] * v3 + coef[4] * vsq);
+      a.rhs[base + v] -= corr;
+      if (a.lh) a.lh[base + v] -= corr;
+    }
+  }
+  if (a.amom && threadIdx.x == 0) {
+    // with h stored for v2 > 0 only (h even in v2) the v2 v3 moments vanish identically
+    a.amom[c * 4 + 0] = m[5];
+    a.amom[c * 4 + 1] = m[6];
+    a.amom[c * 4 + 2] = a.even_v2 ? 0.0 : m[7];
+    a.amom[c * 4 + 3] = a.even_v2 ? 0.0 : m[8];
+  }
 }
 
-// ------------------------------------------------------------------ finish
 // Row c = (cell, species) of the finish step; called by finish_kernel with the block index and by
 // the persistent 1-D iteration.
 __device__ __forceinline__ void finish_row(const FinishArgs& a, int64_t c_row, int nsplit, const double* acc_p) {
-  __shared__ double sh[4 * 9];
-  __shared__ double coef[5];
   const int64_t c = c_row;  // (cell, species) row of n3 values
   const int nsp = a.nsp, sp = static_cast<int>(c % nsp);
   const int64_t cell = c / nsp;
@@ -1194,34 +1447,159 @@ __device__ __forceinline__ void finish_row(const FinishArgs& a, int64_t c_row, i
       }
     }
   }
-  block_sum<9>(m, sh);
-  if (a.project) {
-    if (threadIdx.x < 5) {
-      double s = 0.0;
-      for (int k = 0; k < 5; ++k) s += a.gram_inv[threadIdx.x * 5 + k] * m[k];
-      coef[threadIdx.x] = s;
+  finish_tail(a, c, m);
+}
+
+__global__ __launch_bounds__(256) void finish_kernel(FinishArgs a) { finish_row(a, blockIdx.x, a.splits, a.acc); }
+
+// The finish step on the class sums of a reflected contraction: a lane takes an orbit (or two
+// neighbouring ones, PAIR) of a row, adds the class sums of every split, turns them into L+ at the
+// images and treats all images together.  Bound by HBM: 8 (splits + 2) bytes per unknown; the
+// per-velocity tables, even (v3: odd) under the reflections, are read once per orbit instead of
+// once per velocity (24 576 cells of 6912, one split: 0.74 ms = 5.5 TB/s, where finish_row on
+// the whole matrix took 0.96 ms; 808 cells of 8192: 59 us with two splits, 76 us with four before).
+// T: v2d (pairs) or double.
+template <int LOGB, class T>
+__device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t row, double (&m)[9]) {
+  constexpr int NB = 1 << LOGB;
+  constexpr bool PAIR = sizeof(T) == 16;
+  constexpr int STEP = PAIR ? 2 : 1;
+  constexpr int UZ = LOGB == 1 ? 4 : LOGB == 2 ? 2 : 1;   // splits whose loads are in flight together
+  const SymMap& y = a.sym;
+  const int nsp = a.nsp, sp = static_cast<int>(row % nsp);
+  const int64_t cell = row / nsp;
+  const int64_t nv = a.n3;
+  const double del = a.delta[cell];
+  const int fl = a.flow ? a.flow[cell] : 0;
+  const double dUc = a.dU ? a.dU[row] : 0.0;
+  const double dUq0 = a.dU ? a.dU[cell * nsp] : 0.0;
+  const double dUq1 = (a.dU && nsp > 1) ? a.dU[cell * nsp + 1] : 0.0;
+  const double ms = a.mass_ratio[sp];
+  const double* feq = a.feq + sp * nv;
+  const double* nu = a.nu + sp * nv;
+  const double* kc0 = a.Kc + sp * nv;
+  const double* kc1 = a.Kc + (nsp + sp) * nv;
+  const double* vt1 = a.vtab;
+  const double* vt2 = a.vtab + nv;
+  const double* vt3 = a.vtab + 2 * nv;
+  const double* h = a.h + row * nv;
+  double* rhs = a.rhs + row * nv;
+  double* lh = a.lh ? a.lh + row * nv : nullptr;
+  const int64_t cr = cell * static_cast<int64_t>(NB) * y.ld + static_cast<int64_t>(sp) * y.nvb;  // class row of this species
+  auto ld = [](const double* p) { return *reinterpret_cast<const T*>(p); };
+  for (int k = threadIdx.x * STEP; k < y.nvb; k += blockDim.x * STEP) {
+    int off[NB];
+    orbit_images<LOGB>(y, k, off);
+    T s[NB], hk[NB];
+#pragma unroll
+    for (int g = 0; g < NB; ++g) {
+      s[g] = T{};
+      if constexpr (PAIR) hk[g] = image_pair<LOGB>(h, off, g);
+      else hk[g] = h[off[g]];
     }
-    __syncthreads();
-    for (int v = threadIdx.x; v < n3; v += blockDim.x) {
-      const double v1 = vt1[v], v2 = vt2[v], v3 = vt3[v];
-      const double vsq = v1 * v1 + v2 * v2 + v3 * v3;
-      const double corr = feq[v] * (coef[0] + coef[1] * v1 + coef[2] * v2 + coef[3] * v3 + coef[4] * vsq);
-      a.rhs[base + v] -= corr;
-      if (a.lh) a.lh[base + v] -= corr;
+    if (a.anchor_mode == 1) {
+#pragma unroll
+      for (int g = 0; g < NB; ++g) {
+        if constexpr (PAIR) image_pair_store<LOGB>(a.xref + row * nv, off, g, hk[g]);
+        else a.xref[row * nv + off[g]] = hk[g];
+      }
     }
-  }
-  if (a.amom && threadIdx.x == 0) {
-    // with h stored for v2 > 0 only (h even in v2) the v2 v3 moments vanish identically
-    a.amom[c * 4 + 0] = m[5];
-    a.amom[c * 4 + 1] = m[6];
-    a.amom[c * 4 + 2] = a.even_v2 ? 0.0 : m[7];
-    a.amom[c * 4 + 3] = a.even_v2 ? 0.0 : m[8];
+    const T V1 = ld(vt1 + off[0]), V2 = ld(vt2 + off[0]), V3 = ld(vt3 + off[0]), W = ld(a.wtab + off[0]);
+    const T F = ld(feq + off[0]), NU = ld(nu + off[0]);
+    T K = T{};
+    if (a.dU) {
+      K = dUq0 * ld(kc0 + off[0]);
+      if (nsp > 1) K += dUq1 * ld(kc1 + off[0]);
+    }
+    int z = 0;
+    for (; z + UZ <= a.splits; z += UZ) {
+      T t[UZ][NB];
+#pragma unroll
+      for (int u = 0; u < UZ; ++u)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) t[u][b] = ld(a.acc + (z + u) * a.acc_stride + cr + static_cast<int64_t>(b) * y.ld + k);
+#pragma unroll
+      for (int u = 0; u < UZ; ++u)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) s[b] += t[u][b];
+    }
+    for (; z < a.splits; ++z)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) s[b] += ld(a.acc + z * a.acc_stride + cr + static_cast<int64_t>(b) * y.ld + k);
+    if (a.anchor_mode) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        T* r = reinterpret_cast<T*>(a.accref + cr + static_cast<int64_t>(b) * y.ld + k);
+        if (a.anchor_mode == 1) *r = s[b];
+        else s[b] += *r;
+      }
+    }
+    class_sums<LOGB>(s);   // L+ h at the images
+    const T vsq = V1 * V1 + V2 * V2 + V3 * V3;
+    T S = T{};
+    if (fl == 1) S = V3 * F;
+    else if (fl == 2 && nsp == 1) S = V3 * (vsq - 2.5) * F;
+    const T dh = dUc * 2.0 * ms * V3 * F;
+#pragma unroll
+    for (int g = 0; g < NB; ++g) {
+      const double o3 = LOGB == 3 && g >= 4 ? -1.0 : 1.0;   // correction and source are odd in v3
+      const T lp = s[g] + o3 * K;
+      hk[g] += o3 * dh;
+      const T L = del * (lp - NU * hk[g]);
+      const T r = del * lp + o3 * S;
+      if constexpr (PAIR) {
+        image_pair_store<LOGB>(rhs, off, g, r);
+        if (lh) image_pair_store<LOGB>(lh, off, g, L);
+      } else {
+        rhs[off[g]] = r;
+        if (lh) lh[off[g]] = L;
+      }
+      s[g] = L;
+    }
+    // sums of L and h over the images with the signs of the moments' velocity products
+    class_sums<LOGB>(s);
+    class_sums<LOGB>(hk);
+    auto add = [&](double& acc, T v) {
+      if constexpr (PAIR) acc += v.x + v.y;
+      else acc += v;
+    };
+    constexpr int C1 = 1, C2 = LOGB >= 2 ? 2 : 0, C3 = LOGB == 3 ? 4 : 0;   // classes odd in v1, v2, v3
+    if (a.project) {
+      add(m[0], W * s[0]);
+      add(m[1], W * V1 * s[C1]);
+      add(m[2], W * V2 * s[C2]);
+      add(m[3], W * V3 * s[C3]);
+      add(m[4], W * vsq * s[0]);
+    }
+    const T w13 = 2.0 * W * V1 * V3, w23 = 2.0 * W * V2 * V3;
+    add(m[5], w13 * s[C1 | C3]);
+    add(m[6], w13 * hk[C1 | C3]);
+    add(m[7], w23 * s[C2 | C3]);
+    add(m[8], w23 * hk[C2 | C3]);
   }
 }
 
+// pairs: every row, and the class rows, in 16-byte pairs (lh may be offset by 8 bytes)
+template <int LOGB>
+__global__ __launch_bounds__(256) void finish_class_kernel(FinishArgs a) {
+  const int64_t row = blockIdx.x;
+  if (a.active && !a.active[row / a.nsp]) return;
+  double m[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) m[k] = 0.0;
+  const uintptr_t align = reinterpret_cast<uintptr_t>(a.h) | reinterpret_cast<uintptr_t>(a.rhs) |
+                          reinterpret_cast<uintptr_t>(a.lh);
+  // (eight images of a pair would not fit the registers)
+  bool pairs = false;
+  if constexpr (LOGB < 3) {
+    pairs = a.sym.pairs && (align & 15) == 0;
+    if (pairs) finish_class_row<LOGB, v2d>(a, row, m);
+  }
+  if (!pairs) finish_class_row<LOGB, double>(a, row, m);
+  finish_tail(a, row, m);
+}
+
 // ------------------------------------------------------------------ sweep
-// One thread per velocity pair (v1 > 0 index jp, mirror jm) of one case.
-__global__ __launch_bounds__(256) void finish_kernel(FinishArgs a) { finish_row(a, blockIdx.x, a.splits, a.acc); }
 
 // One thread per (case, species, |v1| > 0 velocity pair): the two marches of a velocity are
 // serial in x1, so the right sides and stencil coefficients of the next kSweepChunk nodes are
@@ -2859,6 +3237,7 @@ __global__ __launch_bounds__(256) void sis1d_persistent_kernel(Persist1DArgs a) 
   const int n_n = (a.n3 + 127) / 128;
   const int n_m = static_cast<int>((a.n_cells + 31) / 32);
   const int n_tiles = n_n * n_m * a.splits;
+  const GemmShape sh{a.n_cells, a.n3, a.n3, a.kps, a.splits, a.n3, a.n3, a.n3, 0, 0, 0, a.n_cells * a.n3};
   const int nbx = (a.sw.n3 / 2 + 255) / 256;
   const int n_sweep = nbx * a.sw.n_cases;
   for (int it = 0; it < a.n_iters; ++it) {
@@ -2866,7 +3245,7 @@ __global__ __launch_bounds__(256) void sis1d_persistent_kernel(Persist1DArgs a) 
     if (!zero) {
       for (int t = blockIdx.x; t < n_tiles; t += G) {
         const int bz = t / (n_n * n_m), r = t - bz * (n_n * n_m);
-        gemm_f64_tile<32, 128, 32, 32>(a.h, a.op, a.acc, a.n_cells, a.n3, a.n3, a.kps, r % n_n, r / n_n, bz);
+        gemm_f64_tile<32, 128, 32, 32>(sh, a.h, a.op, a.acc, r % n_n, r / n_n, bz, SymMap{});
         __syncthreads();
       }
       grid_barrier(a.bar, gen);
@@ -2934,20 +3313,88 @@ hipError_t launch_reduce_operator(const double* op, int64_t ld, double* red, int
 
 int pair_stride(int K) { return (K + 63) / 64 * 64; }
 
-hipError_t launch_split_pairs(const double* X, const double* Xref, int64_t rows, int K, uint16_t* P, int with_lo,
-                              hipStream_t s) {
+hipError_t launch_split_pairs(const double* X, int64_t rows, int K, int ld, uint16_t* P, hipStream_t s) {
   const int Kp = pair_stride(K);
   const int64_t n = rows * Kp;
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(split_pairs_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, X, Xref, rows,
-                     K, Kp, P, with_lo);
+  hipLaunchKernelGGL(split_pairs_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, X, rows, K, ld,
+                     Kp, P);
   return hipGetLastError();
 }
 
-hipError_t launch_convert_x_f32(const double* X, const double* Xref, int64_t count, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(convert_x_f32_kernel, dim3(static_cast<unsigned>((count + 255) / 256)), dim3(256), 0, s, X, Xref,
-                     count, out);
+bool make_sym_map(SymMap& m, int nsp, const int (&dim)[3], const bool (&mirror)[3]) {
+  m = SymMap{};
+  m.nsp = nsp;
+  m.nv = dim[0] * dim[1] * dim[2];
+  int rep[3], axes = 0;
+  bool ok = true;
+  for (int a = 0; a < 3; ++a) {
+    if (mirror[a] && dim[a] % 2) ok = false;
+    rep[a] = mirror[a] ? dim[a] / 2 : dim[a];
+    axes += mirror[a];
+  }
+  // the reflected axes the kernels take: 1; 2 (polar); 1 and 2; all
+  if (axes == 0 || (mirror[2] && axes != 3) || (axes == 2 && !mirror[0])) ok = false;
+  const int64_t nvb = static_cast<int64_t>(rep[0]) * rep[1] * rep[2], d23 = static_cast<int64_t>(rep[1]) * rep[2];
+  if (nvb * d23 >= (int64_t(1) << 32) || nvb > (1 << 28)) ok = false;   // orbit_images divides by multiplication
+  if (!ok) return false;
+  m.logb = axes;
+  m.nvb = static_cast<int>(nvb);
+  m.kb = nsp * m.nvb;
+  m.ld = (m.kb + 7) / 8 * 8;
+  m.d23r = static_cast<int>(d23);
+  m.d3r = rep[2];
+  m.mul23 = static_cast<uint32_t>(((uint64_t(1) << 32) + m.d23r - 1) / m.d23r);
+  m.mul3 = static_cast<uint32_t>(((uint64_t(1) << 32) + m.d3r - 1) / m.d3r);
+  m.s1 = dim[1] * dim[2];
+  m.s2 = dim[2];
+  m.lo1 = mirror[0] ? rep[0] : 0;
+  m.lo2 = mirror[1] ? rep[1] : 0;
+  m.lo3 = mirror[2] ? rep[2] : 0;
+  m.pairs = rep[2] % 2 == 0;
+  return true;
+}
+
+hipError_t launch_class_operator(const SymMap& m, const double* op, double* out, hipStream_t s) {
+  const dim3 grid((m.ld + 255) / 256, m.kb);
+  if (m.logb == 1) hipLaunchKernelGGL(class_operator_kernel<1>, grid, dim3(256), 0, s, m, op, out);
+  else if (m.logb == 2) hipLaunchKernelGGL(class_operator_kernel<2>, grid, dim3(256), 0, s, m, op, out);
+  else if (m.logb == 3) hipLaunchKernelGGL(class_operator_kernel<3>, grid, dim3(256), 0, s, m, op, out);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+namespace {
+template <int LOGB, int OUT>
+hipError_t class_rows(const SymMap& m, const double* X, const double* Xref, const int32_t* active, int64_t cells,
+                      int row_len, void* out, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(cells), (row_len / 2 + 255) / 256);
+  if (m.pairs)
+    hipLaunchKernelGGL((class_rows_kernel<LOGB, OUT, true>), grid, dim3(256), 0, s, m, X, Xref, active, row_len, out);
+  else
+    hipLaunchKernelGGL((class_rows_kernel<LOGB, OUT, false>), grid, dim3(256), 0, s, m, X, Xref, active, row_len, out);
+  return hipGetLastError();
+}
+template <int LOGB>
+hipError_t class_rows_out(const SymMap& m, int precision, const double* X, const double* Xref, const int32_t* active,
+                          int64_t cells, void* out, hipStream_t s) {
+  switch (precision) {
+    case 0: return class_rows<LOGB, 0>(m, X, Xref, active, cells, m.ld, out, s);
+    case 1: return class_rows<LOGB, 1>(m, X, Xref, active, cells, m.ld, out, s);
+    case 2: return class_rows<LOGB, 2>(m, X, Xref, active, cells, pair_stride(m.kb), out, s);
+    default: return class_rows<LOGB, 3>(m, X, Xref, active, cells, pair_stride(m.kb), out, s);
+  }
+}
+}  // namespace
+
+hipError_t launch_class_rows(const SymMap& m, int precision, const double* X, const double* Xref, const int32_t* active,
+                             int64_t cells, void* out, hipStream_t s) {
+  if (cells == 0) return hipSuccess;
+  switch (m.logb) {
+    case 1: return class_rows_out<1>(m, precision, X, Xref, active, cells, out, s);
+    case 2: return class_rows_out<2>(m, precision, X, Xref, active, cells, out, s);
+    default: return class_rows_out<3>(m, precision, X, Xref, active, cells, out, s);
+  }
 }
 
 hipError_t launch_convert_f32(const double* op, float* out, int64_t count, hipStream_t s) {
@@ -2972,78 +3419,109 @@ int gemm_tile_depth(int tile, int precision) {
   return tile >= 3 ? 32 : 16;
 }
 
-bool gemm_wide_fits(int64_t M, int N, int K) {
+bool gemm_wide_fits(int64_t M, int N, int K, int nb) {
   const int64_t row_bytes = 4 * static_cast<int64_t>(pair_stride(K));
-  return M * row_bytes < (int64_t(1) << 32) && N * row_bytes < (int64_t(1) << 32);
+  return M * nb * row_bytes < (int64_t(1) << 32) && N * row_bytes < (int64_t(1) << 32);
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   const int BN = 128;
   const int BM = gemm_tile_rows(g.tile);
-  dim3 grid((g.N + BN - 1) / BN, static_cast<unsigned>((g.M + BM - 1) / BM), g.splits);
+  const int nb = g.sym ? 1 << g.sym->logb : 1;
+  const SymMap sym = g.sym ? *g.sym : SymMap{};
+  // the few-cell tile of FP64 and the bf16 forms reads the cells' own rows
+  const bool own_rows = g.sym && g.cells_own_rows;
+  if (own_rows && (g.tile != 1 || g.precision == 1)) return hipErrorInvalidValue;
   if (g.tile >= 3 && g.precision == 1) return hipErrorInvalidValue;
   if (g.tile == 5 && g.precision != 2) return hipErrorInvalidValue;
   if ((g.tile == 3 || g.tile == 4) && g.precision != 0) return hipErrorInvalidValue;
-  if (g.precision == 0) {
-    if (g.K % 2) return hipErrorInvalidValue;   // rows are loaded in 16-byte k pairs
-    const int kps = gemm_k_per_split(g.K, g.splits);
-    if (g.tile == 0 && g.K <= (1 << 20))
-      hipLaunchKernelGGL(gemm_f64_dma_kernel, grid, dim3(512), 0, s, g.X, g.op64, g.acc, g.M, g.N, g.K, kps);
-    else if (g.tile == 0)
-      hipLaunchKernelGGL((gemm_f64_kernel<128, 128, 64, 64>), grid, dim3(256), 0, s, g.X, g.op64, g.acc, g.M, g.N, g.K, kps);
-    else if (g.tile == 2)
-      hipLaunchKernelGGL((gemm_f64_kernel<64, 128, 32, 64>), grid, dim3(256), 0, s, g.X, g.op64, g.acc, g.M, g.N, g.K, kps);
-    else if (g.tile == 3)
-      hipLaunchKernelGGL((gemm_f64_kernel<128, 128, 64, 64, 32, 1, 1>), grid, dim3(256), 0, s, g.X, g.op64, g.acc, g.M, g.N, g.K, kps);
-    else if (g.tile == 4)
-      hipLaunchKernelGGL((gemm_f64_kernel<64, 128, 32, 64, 32, 1, 1>), grid, dim3(256), 0, s, g.X, g.op64, g.acc, g.M, g.N, g.K, kps);
-    else
-      hipLaunchKernelGGL((gemm_f64_kernel<32, 128, 32, 32>), grid, dim3(256), 0, s, g.X, g.op64, g.acc, g.M, g.N, g.K, kps);
-  } else if (g.precision == 1) {
-    const int kps = gemm_k_per_split(g.K, g.splits);
-    if (!g.X32) return hipErrorInvalidValue;
-    if (g.tile == 0)
-      hipLaunchKernelGGL((gemm_f32_kernel<128, 128, 64, 64>), grid, dim3(256), 0, s, g.X32, g.op32, g.acc, g.M, g.N, g.K, kps);
-    else if (g.tile == 2)
-      hipLaunchKernelGGL((gemm_f32_kernel<64, 128, 32, 64>), grid, dim3(256), 0, s, g.X32, g.op32, g.acc, g.M, g.N, g.K, kps);
-    else
-      hipLaunchKernelGGL((gemm_f32_kernel<32, 128, 32, 32>), grid, dim3(256), 0, s, g.X32, g.op32, g.acc, g.M, g.N, g.K, kps);
+  GemmShape sh{};
+  sh.M = g.M;
+  sh.splits = g.splits > 0 ? g.splits : 1;
+  if (g.sym) {
+    sh.N = sym.kb;
+    sh.ldc = nb * sym.ld;
+    sh.cs = sym.ld;
   } else {
-    // bf16 forms: operands in the pair layout, k running over the padded Kp (zeros past K); with
-    // no cell operand in that layout (Xp null) the 32-row tile splits X (minus Xref) itself
-    if (!g.opp) return hipErrorInvalidValue;
-    const bool fused = !g.Xp;
-    if (fused && (g.tile != 1 || !g.X || g.K % 2)) return hipErrorInvalidValue;
-    const int Kp = pair_stride(g.K);
-    const int kps = gemm_k_per_split(Kp, g.splits);
-    if (g.precision == 3) {
-      if (fused)
-        hipLaunchKernelGGL((gemm_bf16x3_kernel<32, 128, 32, 32, 1, true>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps, g.X, g.Xref, g.K);
-      else if (g.tile == 0)
-        hipLaunchKernelGGL((gemm_bf16x3_kernel<128, 128, 64, 64, 1>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps, nullptr, nullptr, 0);
-      else if (g.tile == 2)
-        hipLaunchKernelGGL((gemm_bf16x3_kernel<64, 128, 32, 64, 1>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps, nullptr, nullptr, 0);
-      else
-        hipLaunchKernelGGL((gemm_bf16x3_kernel<32, 128, 32, 32, 1>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps, nullptr, nullptr, 0);
-    } else if (g.tile == 5) {
-      if (!gemm_wide_fits(g.M, g.N, g.K)) return hipErrorInvalidValue;
-      dim3 wgrid((g.N + 255) / 256, static_cast<unsigned>((g.M + 255) / 256), g.splits);
-      hipLaunchKernelGGL(gemm_bf16x3_wide_kernel, wgrid, dim3(512), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps);
-    } else if (fused) {
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<32, 128, 32, 32, 3, true>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps, g.X, g.Xref, g.K);
-    } else if (g.tile == 0) {
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<128, 128, 64, 64>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps, nullptr, nullptr, 0);
-    } else if (g.tile == 2) {
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<64, 128, 32, 64>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps, nullptr, nullptr, 0);
-    } else {
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<32, 128, 32, 32>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, g.M, g.N, Kp, kps, nullptr, nullptr, 0);
-    }
+    sh.N = g.N;
+    sh.ldc = g.N;
   }
+  sh.cz = sh.M * sh.ldc;
+  const dim3 grid((sh.N + BN - 1) / BN, static_cast<unsigned>((g.M + BM - 1) / BM), sh.splits * nb);
+  if (g.precision <= 1) {
+    // block rows are padded with zeros to ld (a multiple of 8)
+    sh.K = !g.sym ? g.K : g.precision == 1 ? sym.ld : (sym.kb + 1) / 2 * 2;
+    sh.kps = gemm_k_per_split(g.sym ? sym.kb : g.K, sh.splits);
+    sh.ldo = g.sym ? sym.ld : g.K;
+    sh.ldx = own_rows ? sym.nsp * sym.nv : g.sym ? nb * sym.ld : g.K;
+    sh.xs = g.sym ? sym.ld : 0;
+    sh.os = g.sym ? static_cast<int64_t>(sym.kb) * sym.ld : 0;
+  } else {
+    const int Kp = pair_stride(g.sym ? sym.kb : g.K);
+    sh.K = Kp;
+    sh.kps = gemm_k_per_split(Kp, sh.splits);
+    sh.ldo = 2 * Kp;
+    sh.ldx = 2 * Kp * nb;
+    sh.xs = 2 * Kp;
+    sh.os = static_cast<int64_t>(sh.N) * 2 * Kp;
+  }
+#define SIS_GEMM(kernel, threads, ...) hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, __VA_ARGS__, g.acc, sh)
+  if (g.precision == 0) {
+    if (sh.K % 2 || sh.ldx % 2 || sh.ldo % 2) return hipErrorInvalidValue;   // rows are loaded in 16-byte k pairs
+#define SIS_F64(...) hipLaunchKernelGGL((gemm_f64_kernel<__VA_ARGS__>), grid, dim3(256), 0, s, g.X, g.op64, g.acc, sh, sym)
+    if (g.tile == 0 && sh.ldx <= (1 << 20) && sh.ldo <= (1 << 20)) SIS_GEMM(gemm_f64_dma_kernel, 512, g.X, g.op64);
+    else if (g.tile == 0) SIS_F64(128, 128, 64, 64);
+    else if (g.tile == 2) SIS_F64(64, 128, 32, 64);
+    else if (g.tile == 3) SIS_F64(128, 128, 64, 64, 32, 1, 1);
+    else if (g.tile == 4) SIS_F64(64, 128, 32, 64, 32, 1, 1);
+    else if (!own_rows) SIS_F64(32, 128, 32, 32);
+    else if (sym.logb == 1) SIS_F64(32, 128, 32, 32, kBK, 2, kPad, 1);
+    else if (sym.logb == 2) SIS_F64(32, 128, 32, 32, kBK, 2, kPad, 2);
+    else SIS_F64(32, 128, 32, 32, kBK, 2, kPad, 3);
+#undef SIS_F64
+  } else if (g.precision == 1) {
+    if (!g.X32 || !g.op32) return hipErrorInvalidValue;
+    if (g.tile == 0) SIS_GEMM((gemm_f32_kernel<128, 128, 64, 64>), 256, g.X32, g.op32);
+    else if (g.tile == 2) SIS_GEMM((gemm_f32_kernel<64, 128, 32, 64>), 256, g.X32, g.op32);
+    else SIS_GEMM((gemm_f32_kernel<32, 128, 32, 32>), 256, g.X32, g.op32);
+  } else {
+    // bf16 forms: operands in the pair layout, k running over the padded Kp (zeros past K)
+    if (!g.opp || (own_rows ? !g.X : !g.Xp)) return hipErrorInvalidValue;
+#define SIS_BF(...) \
+  hipLaunchKernelGGL((gemm_bf16x3_kernel<__VA_ARGS__>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, sh, g.X, g.Xref, sym)
+    if (g.tile == 5) {
+      if (!gemm_wide_fits(g.M, sh.N, g.sym ? sym.kb : g.K, nb)) return hipErrorInvalidValue;
+      const dim3 wgrid((sh.N + 255) / 256, static_cast<unsigned>((g.M + 255) / 256), sh.splits * nb);
+      hipLaunchKernelGGL(gemm_bf16x3_wide_kernel, wgrid, dim3(512), 0, s, g.Xp, g.opp, g.acc, sh);
+    } else if (g.precision == 3) {
+      if (own_rows) {
+        if (sym.logb == 1) SIS_BF(32, 128, 32, 32, 1, 1);
+        else if (sym.logb == 2) SIS_BF(32, 128, 32, 32, 1, 2);
+        else SIS_BF(32, 128, 32, 32, 1, 3);
+      } else if (g.tile == 0) SIS_BF(128, 128, 64, 64, 1);
+      else if (g.tile == 2) SIS_BF(64, 128, 32, 64, 1);
+      else SIS_BF(32, 128, 32, 32, 1);
+    } else if (own_rows) {
+      if (sym.logb == 1) SIS_BF(32, 128, 32, 32, 3, 1);
+      else if (sym.logb == 2) SIS_BF(32, 128, 32, 32, 3, 2);
+      else SIS_BF(32, 128, 32, 32, 3, 3);
+    } else if (g.tile == 0) SIS_BF(128, 128, 64, 64);
+    else if (g.tile == 2) SIS_BF(64, 128, 32, 64);
+    else SIS_BF(32, 128, 32, 32);
+#undef SIS_BF
+  }
+#undef SIS_GEMM
   return hipGetLastError();
 }
 
 hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(finish_kernel, dim3(static_cast<unsigned>(a.n_cells)), dim3(256), 0, s, a);
+  const dim3 grid(static_cast<unsigned>(a.n_cells));
+  switch (a.sym.logb) {
+    case 0: hipLaunchKernelGGL(finish_kernel, grid, dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL(finish_class_kernel<1>, grid, dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL(finish_class_kernel<2>, grid, dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL(finish_class_kernel<3>, grid, dim3(256), 0, s, a); break;
+  }
   return hipGetLastError();
 }
 
