@@ -187,29 +187,30 @@ struct sis_plan {
   Scratch ws_acc, ws_x;  // split-K partials, low-precision cell operand
   bool timing = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
-  // per-cell transform path (sis_collide_fsm; one gas, Cartesian grid): factor matrices and
-  // f_eq fields [T][nv] from plan creation, multipliers and L+ of the correction shape on
-  // first use
+  // per-cell transform path (sis_collide_fsm; one gas, Cartesian grid): factors, multipliers and
+  // f_eq fields from plan creation, L+ of the correction shape on first use
   bool fsm_ok = false, fsm_ready = false;
   sis::FsmDims fsm_d{};
-  sis::FsmFactors fsm_f{};
+  sis::FsmClassDims fsm_c{};
   int fsm_slab = 0;
-  double* fsm_fac = nullptr;    // the 12 planar factor arrays
-  double* fsm_field = nullptr;  // [T][nv]
-  double* fsm_mult = nullptr;   // [T][Q][L][L]
+  double* fsm_E = nullptr;      // cosine and sine factors
+  double* fsm_cmult = nullptr;  // [T][rows][Q^2], then the fields
+  double* fsm_field = nullptr;  // [T][rows][H^2]
+  int* fsm_part = nullptr;      // [T] odd axes of each term's part
+  double* fsm_mult = nullptr;   // [T][Q][L][L], while the plan is built
   double* fsm_Kc = nullptr;     // [nv]
   double* fsm_dirs = nullptr;   // [D][3], then W [D]
   double* fsm_rad = nullptr;    // radial nodes and weights
   sis::RadialRule fsm_rule;
   std::vector<double> fsm_corr; // correction shape 2 v3 f_eq (stored layout)
-  Scratch fsm_S, fsm_acc;
+  Scratch fsm_x, fsm_acc;       // class rows, per-slab sums
   std::vector<std::pair<hipEvent_t, hipEvent_t>> fsm_events;
   // tuned contraction configuration per (cells, precision): tile id, split-K
   std::map<std::pair<int64_t, int>, std::pair<int, int>> gemm_choice;
   ~sis_plan() {
     for (auto& e : events) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
     for (auto& e : fsm_events) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
-    dfree(fsm_fac); dfree(fsm_field); dfree(fsm_mult); dfree(fsm_Kc); dfree(fsm_dirs); dfree(fsm_rad);
+    dfree(fsm_E); dfree(fsm_cmult); dfree(fsm_part); dfree(fsm_mult); dfree(fsm_Kc); dfree(fsm_dirs); dfree(fsm_rad);
     dfree(op); dfree(opb); dfree(op32); dfree(opp);
     dfree(v1d); dfree(feq); dfree(nu); dfree(Kc); dfree(gram_inv);
     dfree(vnode); dfree(wnode); dfree(d_vr); dfree(d_cth); dfree(d_sth); dfree(vtab); dfree(wtab);
@@ -689,34 +690,34 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
   return SIS_OK;
 }
 
-// Per-cell transform path: cells in chunks (spectra and per-slab partial sums in the plan's
-// scratch, at most ~2 GiB per chunk): forward DFTs, the inverse DFTs of every term with their
-// field products, then finish_kernel sums the slabs' partials and applies the epilogue.
+// Per-cell transform path: cells in chunks (class rows and per-slab sums in the plan's
+// scratch, at most ~2 GiB per chunk): class rows, the transforms of every term with their
+// field products, then finish_class_kernel sums the slabs and applies the epilogue.
 sis_status run_fsm_chunks(sis_plan* p, int64_t n_cells, const double* h, const double* dU, const double* delta,
                           const int32_t* flow, int project, double* rhs, double* lh, double* amom,
                           const double* Kc, hipStream_t s) {
-  const sis::FsmDims& d = p->fsm_d;
+  const sis::FsmClassDims& d = p->fsm_c;
   const int slabs = sis::fsm_slab_count(d, p->fsm_slab);
-  const int64_t per_s = static_cast<int64_t>(d.L) * 2 * d.Q * d.L;
-  const int64_t per_a = static_cast<int64_t>(slabs) * d.nv;
-  // cells per chunk: ~2 GiB of spectra and partials, at most 65535 (the grid's y extent)
-  const int64_t chunk = std::max<int64_t>(
-      1, std::min<int64_t>({n_cells, int64_t(65535), (int64_t(2) << 30) / (8 * (per_s + per_a))}));
-  HIP_TRY(p->fsm_S.ensure(static_cast<size_t>(chunk * per_s) * 8));
-  HIP_TRY(p->fsm_acc.ensure(static_cast<size_t>(chunk * per_a) * 8));
-  double* S = static_cast<double*>(p->fsm_S.p);
-  double* acc = static_cast<double*>(p->fsm_acc.p);
-  const int64_t nv = d.nv;
+  const int64_t row = p->row_len(), nv = p->nv;
+  const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(n_cells, (int64_t(2) << 30) / (8 * row * (slabs + 1))));
+  HIP_TRY(p->fsm_x.ensure(static_cast<size_t>(chunk * row) * 8));
+  double* X = static_cast<double*>(p->fsm_x.p);
   for (int64_t c0 = 0; c0 < n_cells; c0 += chunk) {
     const int64_t nc = std::min(chunk, n_cells - c0);
-    HIP_TRY(sis::launch_fsm_forward(d, p->fsm_f, nc, h + c0 * nv, S, s));
-    HIP_TRY(sis::launch_fsm_inverse(d, p->fsm_f, p->fsm_slab, nc, S, p->fsm_mult, p->fsm_field, acc, s));
+    const int n_sums = sis::fsm_sums(d, p->fsm_slab, nc);   // the last chunk may split its terms
+    HIP_TRY(p->fsm_acc.ensure(static_cast<size_t>(nc * row) * n_sums * 8));
+    double* acc = static_cast<double*>(p->fsm_acc.p);
+    HIP_TRY(sis::launch_class_rows(p->sym, SIS_PREC_FP64, h + c0 * nv, nullptr, nullptr, nc, X, s));
+    HIP_TRY(sis::launch_fsm_class(d, p->fsm_slab, nc, X, p->fsm_E, p->fsm_cmult, p->fsm_field, p->fsm_part, acc,
+                                  nc * row, s));
     sis::FinishArgs f = finish_args(p, nc, h + c0 * nv, dU ? dU + c0 : nullptr, delta + c0, flow ? flow + c0 : nullptr,
                                     project, rhs + c0 * nv, lh ? lh + c0 * nv : nullptr, amom ? amom + c0 * 4 : nullptr,
                                     nullptr, 0, nullptr, nullptr);
     f.Kc = Kc;
-    f.splits = slabs;
+    f.sym = p->sym;
+    f.splits = n_sums;
     f.acc = acc;
+    f.acc_stride = nc * row;
     HIP_TRY(sis::launch_finish(f, s));
   }
   return SIS_OK;
@@ -726,8 +727,7 @@ sis_status run_fsm_chunks(sis_plan* p, int64_t n_cells, const double* h, const d
 // built with the plan).
 sis_status ensure_fsm(sis_plan* p, hipStream_t s) {
   if (p->fsm_ready) return SIS_OK;
-  const sis::FsmDims& d = p->fsm_d;
-  if (!p->fsm_Kc) HIP_TRY(dmalloc(&p->fsm_Kc, d.nv));
+  if (!p->fsm_Kc) HIP_TRY(dmalloc(&p->fsm_Kc, p->nv));
   double *dc = nullptr, *one = nullptr;
   auto cleanup = [&]() { dfree(dc); dfree(one); };
   hipError_t e = upload(&dc, p->fsm_corr, s);
@@ -2281,7 +2281,7 @@ sis_status create_polar_plan(const sis_velocity_desc* desc, hipStream_t stream, 
   return SIS_OK;
 }
 
-// Factor matrices and f_eq fields of the per-cell transform path (one-gas Cartesian plan
+// Factors, multipliers and f_eq fields of the per-cell transform path (one-gas Cartesian plan
 // with the given parity storage).  dX holds the full-grid fields of the assembly,
 // [B_p; A_p] already scaled by 4 b0 W_p; dfeq the full-grid f_eq.
 sis_status build_fsm_static(sis_plan* p, int parity, const double* dX, const double* dfeq, hipStream_t stream) {
@@ -2296,86 +2296,66 @@ sis_status build_fsm_static(sis_plan* p, int parity, const double* dX, const dou
   d.T = 2 * p->D + 1;
   p->fsm_d = d;
   if (sis::fsm_unsupported(d)) return SIS_OK;   // sis_collide_fsm reports it
-  const int n = d.n, P = d.P, L = d.L, Q = d.Q, half = P / 2 - 1;
-  const int o2 = n - d.n2, o3 = n - d.n3;        // first stored node on axes 2, 3
-  const size_t sz[6] = {static_cast<size_t>(L) * n, static_cast<size_t>(L) * d.n2, static_cast<size_t>(Q) * d.n3,
-                        static_cast<size_t>(n) * L, static_cast<size_t>(d.n2) * L, static_cast<size_t>(d.n3) * Q};
-  size_t total = 0;
-  for (size_t k : sz) total += 2 * k;
-  std::vector<double> fac(total);
-  double* a[12];
-  {
-    size_t off = 0;
-    for (int k = 0; k < 6; ++k) {
-      a[2 * k] = fac.data() + off;
-      a[2 * k + 1] = fac.data() + off + sz[k];
-      off += 2 * sz[k];
+  sis::FsmClassDims c{};
+  c.Q = d.Q;
+  c.H = p->n / 2;
+  // one direction of each set of mirror images (the angles' nodes are symmetric about pi/2: node k and
+  // M - 1 - k; reflections of axis 3 act on the first index, of axis 1 on the second), its parts:
+  // the middle node of an odd rule is its own image and has no odd part
+  const int M = p->m_angle;
+  std::vector<int> row, part, src;
+  std::vector<double> coef;
+  const double inv = 1.0 / (static_cast<double>(d.P) * d.P * d.P);
+  // images of the axes stored by parity: the class rows hold one of each pair
+  const double fold = parity == 2 ? 4.0 : parity == 1 ? 2.0 : 1.0;
+  for (int a = 0; a < (M + 1) / 2; ++a)
+    for (int b = 0; b < (M + 1) / 2; ++b) {
+      const int q = a * M + b;
+      const bool mid3 = 2 * a == M - 1, mid1 = 2 * b == M - 1;
+      const int images = (mid3 ? 1 : 2) * (mid1 ? 1 : 2);
+      for (int o3 = 0; o3 < (mid3 ? 1 : 2); ++o3)
+        for (int o1 = 0; o1 < (mid1 ? 1 : 2); ++o1)
+          for (int kind = 0; kind < 2; ++kind) {   // psi_q with B_q, phi_q with A_q
+            row.push_back(2 * q + kind);
+            src.push_back(kind ? p->D + q : q);
+            part.push_back(o1 | ((o1 ^ o3) << 1) | (o3 << 2));
+            coef.push_back(images * inv * fold);
+          }
     }
+  row.push_back(2 * p->D);
+  src.push_back(-1);
+  part.push_back(0);
+  coef.push_back(-inv * fold);
+  c.T = static_cast<int>(row.size());
+  const int HP = (c.H + 15) / 16 * 16;
+  std::vector<double> E(2 * static_cast<size_t>(c.Q) * HP, 0.0);
+  for (int l = 0; l < c.Q; ++l)
+    for (int i = 0; i < c.H; ++i) {
+      double cs, sn;
+      phase_q(static_cast<long>(l) * (2 * i + 1), d.P, cs, sn);
+      const double w = l == 0 ? 1.0 : 2.0;
+      E[static_cast<size_t>(l) * HP + i] = w * cs;
+      E[static_cast<size_t>(c.Q + l) * HP + i] = w * sn;
+    }
+  // one upload each for the factors with the fields' coefficients, and for the terms' indices
+  const size_t nE = E.size(), T = static_cast<size_t>(c.T);
+  E.insert(E.end(), coef.begin(), coef.end());
+  std::vector<int> index(part);
+  index.insert(index.end(), row.begin(), row.end());
+  index.insert(index.end(), src.begin(), src.end());
+  const size_t n_mult = T * sis::fsm_mult_rows(c) * c.Q * c.Q, n_field = T * sis::fsm_field_rows(c) * c.H * c.H;
+  hipError_t e = upload(&p->fsm_E, E, stream);
+  if (e == hipSuccess) e = upload(&p->fsm_part, index, stream);
+  if (e == hipSuccess) e = dmalloc(&p->fsm_cmult, n_mult + n_field);
+  if (e == hipSuccess) {
+    p->fsm_field = p->fsm_cmult + n_mult;
+    e = sis::launch_fsm_fold(d, c, p->fsm_mult, p->fsm_part + T, p->fsm_part, p->fsm_cmult, stream);
   }
-  double c, sn;
-  // forward: F1 [L][n], F2 [L][n2], F3 [Q][n3] with the images folded in
-  for (int li = 0; li < L; ++li)
-    for (int j = 0; j < n; ++j) {
-      fsm_phase(li - half, j, n, P, c, sn);
-      a[0][li * n + j] = c;
-      a[1][li * n + j] = -sn;
-    }
-  for (int li = 0; li < L; ++li)
-    for (int s2 = 0; s2 < d.n2; ++s2) {
-      fsm_phase(li - half, s2 + o2, n, P, c, sn);
-      const bool even = parity == 2;      // images v2 -> -v2 with sign +1
-      a[2][li * d.n2 + s2] = even ? 2.0 * c : c;
-      a[3][li * d.n2 + s2] = even ? 0.0 : -sn;
-    }
-  for (int l3 = 0; l3 < Q; ++l3)
-    for (int s3 = 0; s3 < d.n3; ++s3) {
-      fsm_phase(l3, s3 + o3, n, P, c, sn);
-      const bool odd = parity >= 1;       // images v3 -> -v3 with sign -1
-      a[4][l3 * d.n3 + s3] = odd ? 0.0 : c;
-      a[5][l3 * d.n3 + s3] = odd ? -2.0 * sn : -sn;
-    }
-  // inverse: E1 [n][L], E2 [n2][L], E3 [n3][Q] (2 for l3 > 0: the conjugate half)
-  for (int j = 0; j < n; ++j)
-    for (int li = 0; li < L; ++li) {
-      fsm_phase(li - half, j, n, P, c, sn);
-      a[6][j * L + li] = c;
-      a[7][j * L + li] = sn;
-    }
-  for (int s2 = 0; s2 < d.n2; ++s2)
-    for (int li = 0; li < L; ++li) {
-      fsm_phase(li - half, s2 + o2, n, P, c, sn);
-      a[8][s2 * L + li] = c;
-      a[9][s2 * L + li] = sn;
-    }
-  for (int s3 = 0; s3 < d.n3; ++s3)
-    for (int l3 = 0; l3 < Q; ++l3) {
-      fsm_phase(l3, s3 + o3, n, P, c, sn);
-      const double w = l3 == 0 ? 1.0 : 2.0;
-      a[10][s3 * Q + l3] = w * c;
-      a[11][s3 * Q + l3] = w * sn;
-    }
-  HIP_TRY(upload(&p->fsm_fac, fac, stream));
-  const double* dev[12];
-  for (int k = 0; k < 12; ++k) dev[k] = p->fsm_fac + (a[k] - fac.data());
-  p->fsm_f = sis::FsmFactors{dev[0], dev[1], dev[2], dev[3], dev[4], dev[5],
-                             dev[6], dev[7], dev[8], dev[9], dev[10], dev[11]};
-  // fields [T][nv] of the stored velocities: term 2p (multiplier psi_p) carries B_p, term
-  // 2p + 1 (phi_p) carries A_p, the loss term -f_eq; all / P^3 (the inverse DFT's scale)
-  std::vector<int> src(d.T);
-  for (int q = 0; q < p->D; ++q) {
-    src[2 * q] = q;
-    src[2 * q + 1] = p->D + q;
-  }
-  src[2 * p->D] = -1;
-  int* dsrc = nullptr;
-  HIP_TRY(upload(&dsrc, src, stream));
-  hipError_t e = dmalloc(&p->fsm_field, static_cast<size_t>(d.T) * d.nv);
   if (e == hipSuccess)
-    e = sis::launch_fsm_gather(d, d.T, dX, dsrc, dfeq, 1.0 / (static_cast<double>(P) * P * P), p->fsm_field, stream);
+    e = sis::launch_fsm_fold_fields(c, dX, dfeq, p->fsm_part + 2 * T, p->fsm_part, p->fsm_E + nE, p->fsm_field, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
-  dfree(dsrc);
   if (e != hipSuccess) return fail(SIS_E_DEVICE, "transform path tables: %s", hipGetErrorString(e));
-  p->fsm_slab = sis::fsm_default_slab(d);
+  p->fsm_c = c;
   p->fsm_ok = true;
   return SIS_OK;
 }
@@ -2661,6 +2641,8 @@ sis_status sis_plan_create(const sis_velocity_desc* desc, hipStream_t stream, si
   p->h_nu = t.nu;
   PLAN_TRY(hipMemcpyAsync(p->nu, t.nu.data(), n3 * 8, hipMemcpyHostToDevice, stream));
   if (device_tables) PLAN_ST(build_fsm_static(p, desc->parity, dX, p->feq, stream));
+  dfree(p->fsm_mult);   // folded
+  p->fsm_mult = nullptr;
   const double* dbr = dY + 2 * tabY;
 
   // Gram matrix of the invariants {1, v1, v2, v3, |v|^2} with weight w f_eq
@@ -2729,6 +2711,11 @@ sis_status sis_plan_create(const sis_velocity_desc* desc, hipStream_t stream, si
     return st;
   }
   PLAN_TRY(hipStreamSynchronize(stream));
+  if (p->fsm_ok) {
+    p->fsm_c.nb = p->nb();
+    p->fsm_c.ld = p->sym.ld;
+    p->fsm_slab = sis::fsm_default_slab(p->fsm_c);
+  }
   cleanup();
 #undef PLAN_TRY
 #undef PLAN_ST
@@ -3062,18 +3049,19 @@ sis_status sis_collide_fsm(sis_plan_t p, int64_t n_cells, const double* h, const
 sis_status sis_plan_fsm_info(sis_plan_t p, double* flops_per_cell, int32_t* slab_l1, int64_t* table_bytes) {
   if (sis_status st = check_plan(p)) return st;
   if (!p->fsm_ok) return fail(SIS_E_UNSUPPORTED, "no per-cell transform path on this plan");
-  const sis::FsmDims& d = p->fsm_d;
+  const sis::FsmClassDims& d = p->fsm_c;
   if (flops_per_cell) *flops_per_cell = sis::fsm_flops_per_cell(d, p->fsm_slab);
   if (slab_l1) *slab_l1 = p->fsm_slab;
   if (table_bytes)
-    *table_bytes = 8 * (static_cast<int64_t>(d.T) * d.Q * d.L * d.L + static_cast<int64_t>(d.T) * d.nv);
+    *table_bytes = 8 * static_cast<int64_t>(d.T) * (static_cast<int64_t>(sis::fsm_mult_rows(d)) * d.Q * d.Q +
+                                                    static_cast<int64_t>(sis::fsm_field_rows(d)) * d.H * d.H);
   return SIS_OK;
 }
 
 sis_status sis_plan_set_fsm_slab(sis_plan_t p, int32_t slab_l1) {
   if (sis_status st = check_plan(p)) return st;
   if (!p->fsm_ok) return fail(SIS_E_UNSUPPORTED, "no per-cell transform path on this plan");
-  if (slab_l1 < 1 || slab_l1 > 8 || !sis::fsm_slab_fits(p->fsm_d, slab_l1))
+  if (slab_l1 < 1 || slab_l1 > 8 || !sis::fsm_slab_fits(p->fsm_c, slab_l1))
     return fail(SIS_E_INVALID, "slab_l1 must be in 1..8 with the inverse transforms' LDS within 160 KiB");
   p->fsm_slab = slab_l1;
   return SIS_OK;

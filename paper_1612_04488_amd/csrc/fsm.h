@@ -1,16 +1,11 @@
-// The fast spectral method evaluated per cell on the device: separable pruned
-// DFTs of the velocity grid as small complex GEMMs on the FP64 MFMA, staged in
-// LDS (fsm.hip).  All pointers are device pointers.
+// The fast spectral method on the device: separable pruned DFTs of the velocity grid as
+// small GEMMs on the FP64 MFMA, staged in LDS (fsm.hip), per cell and for the plan's
+// tables.  All pointers are device pointers.
 //
-// Modes: l1, l2 take the P - 1 signed values -(P/2 - 1) .. P/2 - 1 (index
+// Modes of the tables: l1, l2 take the P - 1 signed values -(P/2 - 1) .. P/2 - 1 (index
 // l + P/2 - 1; the Nyquist mode -P/2 carries no multiplier), l3 the Q = P/2
 // values 0 .. P/2 - 1 (half spectrum: h is real, so its transform is
 // Hermitian).  Frequencies xi_l = pi l / L_p, velocities v_j = (j + 1/2 - n/2) dv.
-//
-// Stored velocities follow the plan's parity storage: axis 1 all n nodes,
-// axis 2 the n2 = n or n/2 nodes with v2 > 0 (even images), axis 3 the n3 = n
-// or n/2 nodes with v3 > 0 (odd images).  The forward factors fold the images
-// in, so the stored half transforms to the full-grid spectrum.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -25,14 +20,6 @@ struct FsmDims {
   int n2, n3;   // stored nodes on axes 2, 3
   int nv;       // n * n2 * n3 stored velocities per cell
   int T;        // terms: 2 D gain terms and the loss
-};
-
-// Factor matrices, complex planar (re, im), row-major:
-//   forward  F1 [L][n], F2 [L][n2], F3 [Q][n3]   (images folded in)
-//   inverse  E1 [n][L], E2 [n2][L], E3 [n3][Q]   (E3 carries 1 for l3 = 0, 2 otherwise)
-struct FsmFactors {
-  const double *f1r, *f1i, *f2r, *f2i, *f3r, *f3i;
-  const double *e1r, *e1i, *e2r, *e2i, *e3r, *e3i;
 };
 
 // Multipliers m[T][Q][L][L] (term 2p: psi_p, 2p + 1: phi_p, 2D: beta) of the
@@ -52,24 +39,44 @@ struct FsmMultArgs {
 };
 hipError_t launch_fsm_multipliers(const FsmMultArgs& a, hipStream_t s);
 
-// Forward transform of n_cells cells: h [cells][nv] (stored layout) ->
-// S [cells][L (l1)][2 (re, im)][Q (l3)][L (l2)].
-hipError_t launch_fsm_forward(const FsmDims& d, const FsmFactors& f, int64_t n_cells, const double* h, double* S,
-                              hipStream_t s);
-
-// Inverse transforms of every term with their field products, summed:
-//   acc[slab][cell][i] = sum_t field[t][i] Re sum_{l1 in slab} sum_{l2, l3} E1 E2 E3 mult[t][l] S[cell][l]
-// for the l1 slabs of slab_l1 modes each (n_slabs = ceil(L / slab_l1)); the
-// slabs' partial sums add up to L+ of each cell at delta = 1.
-int fsm_slab_count(const FsmDims& d, int slab_l1);
-int fsm_default_slab(const FsmDims& d);
-// whether the inverse kernel's LDS holds a slab of slab_l1 modes
-bool fsm_slab_fits(const FsmDims& d, int slab_l1);
-// 0 if the dimensions are within what the inverse kernel holds in registers
-// (stage-3 output tiles per wave), else the reason.
+// ---- per-cell transforms on parity classes (see SymMap in kernels.h for the classes and their rows)
+// A function that is even or odd in every velocity axis is given by its values at the H^3 velocities
+// of the octant v > 0 (H = n/2, v = (i + 1/2) dv) and has a real spectrum on the Q^3 modes
+// l >= 0 (Q = n_pad/2, the Nyquist modes dropped) up to a phase per odd axis.  The terms:
+// for a direction e and its mirror images, with psi^k, X^k the parts of the multiplier and field
+// that are odd along the axes of k (none or two axes), sum over the images X (psi * h) =
+// (number of images) sum_k X^k (psi^k * h); every product keeps the class of h.
+struct FsmClassDims {
+  int Q, H;     // modes and velocities per axis
+  int T;        // terms: (direction up to reflection, part k, kind of multiplier), and the loss
+  int nb, ld;   // classes and their row length (SymMap)
+};
+// mult [T][l3][l1][l2], l3 padded with zeros to fsm_mult_rows: part[t] (bits: odd axes 1, 2, 3) of row
+// row[t] of the multipliers m[.][Q][L][L]
+int fsm_mult_rows(const FsmClassDims& d);
+hipError_t launch_fsm_fold(const FsmDims& d, const FsmClassDims& c, const double* mult, const int* row, const int* part,
+                           double* out, hipStream_t s);
+// field [T][i1][i2][i3], i1 padded with zeros to fsm_field_rows: coef[t] times part[t] of the full-grid
+// field in[src[t]] (feq for src[t] < 0)
+int fsm_field_rows(const FsmClassDims& d);
+hipError_t launch_fsm_fold_fields(const FsmClassDims& c, const double* in, const double* feq, const int* src,
+                                  const int* part, const double* coef, double* out, hipStream_t s);
+// Transforms of every term with their field products, summed, from the class rows X [cells][nb][ld]:
+//   acc[s][cell][class][i] = sum_{t in range} field[t][i] sum_{l1 in slab} sum_{l2, l3} mult[t][l] R(l) E E E
+// for the slabs of slab_l1 modes l1 each (n_slabs = ceil(Q / slab_l1)) and, for few cells, ranges of
+// terms; the fsm_sums partial sums (acc_stride elements apart) add up to the class sums of L+ of each
+// cell at delta = 1.  E [2][Q][H rounded up to 16]: w(l) cos, w(l) sin of pi l (2 i + 1) / n_pad, w = 1 for
+// l = 0 and 2 otherwise, zero past H.
+int fsm_sums(const FsmClassDims& d, int slab_l1, int64_t n_cells);
+int fsm_slab_count(const FsmClassDims& d, int slab_l1);
+int fsm_default_slab(const FsmClassDims& d);
+// whether the transform kernel's LDS holds a slab of slab_l1 modes
+bool fsm_slab_fits(const FsmClassDims& d, int slab_l1);
+// null if the grid is within what the path takes, else the reason.
 const char* fsm_unsupported(const FsmDims& d);
-hipError_t launch_fsm_inverse(const FsmDims& d, const FsmFactors& f, int slab_l1, int64_t n_cells, const double* S,
-                              const double* mult, const double* field, double* acc, hipStream_t s);
+hipError_t launch_fsm_class(const FsmClassDims& d, int slab_l1, int64_t n_cells, const double* X, const double* E,
+                            const double* mult, const double* field, const int* part, double* acc, int64_t acc_stride,
+                            hipStream_t s);
 // Per-term pruned inverse DFTs of the multipliers (plan-time tables), times a
 // spectrum X (layout of S, one cell) or X = 1 when X is null:
 //   out[slot[t]][a1][a2][a3] = scale[t] Re sum_l E1(a1, l1) E2(a2, l2) E3(a3, l3) m_t(l) X(l)
@@ -111,13 +118,7 @@ hipError_t launch_separable(int nt, int m, const double* S, const double* w, dou
 hipError_t launch_scale_rows(int nt, int64_t len, const double* in, const int* src, const double* sc, double* out,
                              hipStream_t s);
 
-// Field table of the per-cell path from full-grid rows: for t < nrows,
-//   out[t][v] = scale * (src[t] >= 0 ? in[src[t]][full(v)] : -feq[full(v)])
-// over the stored velocities v of d (full(v): index of v on the n^3 grid).
-hipError_t launch_fsm_gather(const FsmDims& d, int nrows, const double* in, const int* src, const double* feq,
-                             double scale, double* out, hipStream_t s);
-
 // Executed flops of one cell update (every MFMA issued, padding included)
-double fsm_flops_per_cell(const FsmDims& d, int slab_l1);
+double fsm_flops_per_cell(const FsmClassDims& d, int slab_l1);
 
 }  // namespace sis

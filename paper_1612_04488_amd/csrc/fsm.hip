@@ -1,9 +1,9 @@
 // The fast spectral method (the collision evaluation the paper cites for eq.
-// LBE_collision) applied per cell on the device: a pruned forward DFT of each
-// cell's distribution, then for every one of the 2D + 1 terms its multiplier,
-// a pruned inverse DFT back to the stored velocities and the product with the
-// term's f_eq field, summed over the terms.  Every DFT is separable: each axis
-// is a small dense complex GEMM against a factor matrix, run on the FP64 MFMA
+// LBE_collision) on the device: per cell, the forward transform of every parity class
+// of the distribution, then for every one of the 2D + 1 terms its multiplier,
+// the inverse transform back to the velocities and the product with the
+// term's f_eq field, summed over the terms; and the plan's tables.  Every transform is
+// separable: each axis is a small dense GEMM against a factor matrix, run on the FP64 MFMA
 // (v_mfma_f64_16x16x4) with the operands staged in LDS.  Declarations in fsm.h.
 #include "fsm.h"
 
@@ -14,8 +14,6 @@ namespace sis {
 namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) void gbl_void_t;
 constexpr int kThreads = 256;   // four wave64s
 
 __device__ inline v4d mfma(double a, double b, v4d c) {
@@ -127,349 +125,315 @@ __global__ __launch_bounds__(256) void fsm_mult_kernel(FsmMultArgs a) {
   a.mult[static_cast<int64_t>(2 * a.D) * qll + idx] = 4.0 * a.b0 * beta;
 }
 
-// ---------------------------------------------------------------- forward
-// One workgroup per (cell, chunk of B3 l3 modes):
-//   T1(l3, j1, s2) = sum_s3 F3(l3, s3) h(j1, s2, s3)
-//   T2(l3, l2, j1) = sum_s2 F2(l2, s2) T1(l3, j1, s2)
-//   S(l1, l3, l2)  = sum_j1 F1(l1, j1) T2(l3, l2, j1)
-__global__ __launch_bounds__(kThreads) void fsm_forward_kernel(FsmDims d, FsmFactors f, int B3,
-                                                               const double* __restrict__ h,
-                                                               double* __restrict__ S) {
+// ---------------------------------------------------------------- per-cell transforms
+// One workgroup per (range of terms, slab of B modes l1, cell, parity class of the cell's distribution).  A
+// function of one class (even or odd in every velocity axis) lives on the octant v > 0 and has a
+// real spectrum on the octant l >= 0, and the multipliers and fields are split into their own
+// parity parts (launch_fsm_fold), so every transform is real, Q^3 modes to H^3 velocities (H = n/2,
+// cosine or sine factors by the parities), and one term per direction and multiplier kind
+// serves all mirror images of the direction.  With the class sums x of the cell:
+//   forward  R(l) = sum_i x(i) c1(l1, i1) c2(l2, i2) c3(l3, i3)            (the slab's l1 only)
+//   stage 1  T1(l2; b, i3) = sum_l3 m_t(l) R(l) E3(l3, i3)                 (l1 = l10 + b)
+//   stage 2  T2(b; i2, i3) = sum_l2 T1(l2; b, i3) E2(l2, i2)
+//   stage 3  G(i1; i2, i3) += X_t(i) sum_b E1(l1, i1) T2(b; i2, i3)
+// (E = w(l) c(l, .), w = 1 for l = 0 and 2 otherwise; the same table for the three axes).  Bound by
+// the FP64 MFMA: a term of a (24-mode, 12-velocity, B = 8) slab is 126 MFMAs against 37 KB of
+// multipliers from L2.  R stays in LDS for all terms; the waves take stage 1 of a term and stage 3
+// of the one before between the same two barriers, two workgroups share a CU, and the
+// multipliers of the next term are in flight across the barrier.  512 cells of the duct's gas (24^3
+// velocities on the v3 > 0 half, 129 terms): 5.2 ms with the MFMA pipes 57% busy, where complex
+// transforms of the whole spectrum (2.06e9 executed flops per cell, 4.0e8 now) took 33 ms at 39%; one
+// cell 51 us instead of 1.44 ms (its terms split over workgroups).  Six waves per workgroup left one
+// workgroup per CU (7.3 ms): the waves of two do not spread evenly over the SIMDs.
+struct SlabShape {
+  int BQ, BH, HH;        // columns of stage 1 (b, l2), 2 (b, i3) and 3 (i2, i3)
+  int rs, ts, hs;        // LDS row strides of R, T1, T2
+  int t1, t2, t3;        // 16 x 16 tiles of the stages
+  int kb4;               // 4-deep k-steps of stage 3
+};
+__host__ __device__ inline SlabShape slab_shape(const FsmClassDims& d, int B) {
+  SlabShape z;
+  z.BQ = B * d.Q;
+  z.BH = B * d.H;
+  z.HH = d.H * d.H;
+  const int mt = (d.H + 15) / 16;
+  z.t1 = (z.BQ + 15) / 16 * mt;
+  z.t2 = (z.BH + 15) / 16 * mt;
+  z.t3 = (z.HH + 15) / 16 * mt;
+  z.rs = (z.BQ + 15) / 16 * 16 + 16;   // rows k and k + 1 half the banks apart
+  z.ts = (z.BH + 15) / 16 * 16 + 1;    // odd: 16 lanes down a column hit distinct banks
+  z.hs = (z.HH + 15) / 16 * 16;
+  z.kb4 = (B + 3) / 4;   // (LDS rows of T2: 4 per k-step of the kernel, one or two)
+  return z;
+}
+// 4-deep k-steps that the kernel is built for: at least ceil(Q / 4)
+inline int class_ksteps(const FsmClassDims& d) { return d.H > 16 ? 8 : d.Q <= 16 ? 4 : (d.Q + 3) / 4; }
+
+// KS, KB: 4-deep k-steps of stages 1 and 2, and of stage 3 (zeros past Q and B); NT1, NT2, NT3: tiles per
+// wave of the stages; MT: 16-wide tiles along a velocity axis.  Without GUARD the term loop has no
+// branch: a wave without a tile computes one that goes to `trash` (or is never stored).
+template <int KS, int KB, int NT1, int NT2, int NT3, int MT, bool GUARD>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT3 == 2 ? 4 : 2))) void fsm_class_kernel(FsmClassDims d, int B, const double* __restrict__ X,
+                                                        const double* __restrict__ Etab,
+                                                        const double* __restrict__ mult,
+                                                        const double* __restrict__ field,
+                                                        const int* __restrict__ parts, double* __restrict__ accp,
+                                                        int64_t acc_stride) {
   extern __shared__ double sm[];
-  const int64_t cell = blockIdx.y;
-  const int q0 = blockIdx.x * B3;
-  const int nq = min(B3, d.Q - q0);
-  const int n = d.n, n2 = d.n2, n3 = d.n3, L = d.L, Q = d.Q;
-  double* T1r = sm;                      // [B3][n][n2]
-  double* T1i = T1r + B3 * n * n2;
-  double* T2r = T1i + B3 * n * n2;       // [B3][L][n]
-  double* T2i = T2r + B3 * L * n;
-  const double* hc = h + cell * d.nv;
-  {
-    const int M = nq, K = n3, N = n * n2;
-    auto la = [&](int m, int k, double& re, double& im) {
-      const bool ok = m < M && k < K;
-      re = ok ? f.f3r[(q0 + m) * n3 + k] : 0.0;
-      im = ok ? f.f3i[(q0 + m) * n3 + k] : 0.0;
-    };
-    auto lb = [&](int k, int c, double& re, double& im) {
-      re = (k < K && c < N) ? hc[static_cast<int64_t>(c) * n3 + k] : 0.0;
-      im = 0.0;
-    };
-    auto st = [&](int m, int c, double re, double im) {
-      T1r[m * N + c] = re;
-      T1i[m * N + c] = im;
-    };
-    cgemm<2>(M, N, K, la, lb, st);
+  constexpr int HP = 16 * MT, KP = 4 * KS;
+  const SlabShape z = slab_shape(d, B);
+  const int Q = d.Q, H = d.H;
+  double* E = sm;                       // [2][KP][HP]: cosines, sines; zero past Q and H
+  double* R = E + 2 * KP * HP;          // [KP][rs]
+  double* T1 = R + KP * z.rs;           // [KP][ts]
+  double* T2 = T1 + KP * z.ts;          // [4 KB][hs]
+  // then 64 doubles that idle tiles write
+  const int tid = threadIdx.x, nthr = blockDim.x, W = nthr >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, kr = lane >> 4, cc = lane & 15;
+  const int l10 = blockIdx.y * B;
+  const int64_t cell = blockIdx.x / d.nb;
+  const int cls = static_cast<int>(blockIdx.x - cell * d.nb);
+  // parity of the class along each axis; the axes stored by parity carry theirs
+  const int x1 = cls & 1, x2 = d.nb >= 4 ? (cls >> 1) & 1 : 0, x3 = d.nb == 8 ? (cls >> 2) & 1 : 1;
+  const double* xr = X + (cell * d.nb + cls) * static_cast<int64_t>(d.ld);
+
+  for (int i = tid; i < 2 * KP * HP; i += nthr) {
+    const int l = (i / HP) % KP;
+    E[i] = l < Q ? Etab[((i >= KP * HP ? Q : 0) + l) * HP + i % HP] : 0.0;
+  }
+  for (int i = tid; i < KP * (z.rs + z.ts) + 4 * KB * z.hs + 64; i += nthr) R[i] = 0.0;
+  __syncthreads();
+  // forward: E carries w(l), taken out again by halving (exact)
+  auto fac = [&](int odd, int l, int i) { return (l == 0 ? 1.0 : 0.5) * E[(odd * KP + l) * HP + i]; };
+  for (int o = tid; o < B * z.HH; o += nthr) {
+    const int b = o / z.HH, r = o - b * z.HH;
+    if (l10 + b < Q) {
+      double a = 0.0;
+      for (int i = 0; i < H; ++i) a += fac(x1, l10 + b, i) * xr[i * z.HH + r];
+      T2[b * z.hs + r] = a;
+    }
   }
   __syncthreads();
-  {
-    const int M = L, K = n2, N = nq * n;   // column c = (l3c, j1)
-    auto la = [&](int m, int k, double& re, double& im) {
-      const bool ok = m < M && k < K;
-      re = ok ? f.f2r[m * n2 + k] : 0.0;
-      im = ok ? f.f2i[m * n2 + k] : 0.0;
-    };
-    auto lb = [&](int k, int c, double& re, double& im) {
-      const bool ok = k < K && c < N;
-      re = ok ? T1r[c * n2 + k] : 0.0;
-      im = ok ? T1i[c * n2 + k] : 0.0;
-    };
-    auto st = [&](int m, int c, double re, double im) {
-      const int l3c = c / n, j1 = c - l3c * n;
-      T2r[(l3c * L + m) * n + j1] = re;
-      T2i[(l3c * L + m) * n + j1] = im;
-    };
-    cgemm<2>(M, N, K, la, lb, st);
+  for (int o = tid; o < B * Q * H; o += nthr) {
+    const int i3 = o % H, l2 = (o / H) % Q, b = o / (H * Q);
+    double a = 0.0;
+    for (int i = 0; i < H; ++i) a += fac(x2, l2, i) * T2[b * z.hs + i * H + i3];
+    T1[l2 * z.ts + b * H + i3] = a;
   }
   __syncthreads();
-  {
-    const int M = L, K = n, N = nq * L;    // column c = (l3c, l2)
-    auto la = [&](int m, int k, double& re, double& im) {
-      const bool ok = m < M && k < K;
-      re = ok ? f.f1r[m * n + k] : 0.0;
-      im = ok ? f.f1i[m * n + k] : 0.0;
-    };
-    auto lb = [&](int k, int c, double& re, double& im) {
-      const bool ok = k < K && c < N;
-      re = ok ? T2r[c * n + k] : 0.0;
-      im = ok ? T2i[c * n + k] : 0.0;
-    };
-    double* Sc = S + cell * static_cast<int64_t>(L) * 2 * Q * L;
-    auto st = [&](int m, int c, double re, double im) {
-      const int l3c = c / L, l2 = c - l3c * L;
-      const int64_t o = (static_cast<int64_t>(m) * 2 * Q + (q0 + l3c)) * L + l2;
-      Sc[o] = re;
-      Sc[o + static_cast<int64_t>(Q) * L] = im;
-    };
-    cgemm<2>(M, N, K, la, lb, st);
+  for (int o = tid; o < Q * z.BQ; o += nthr) {
+    const int c = o % z.BQ, l3 = o / z.BQ, b = c / Q, l2 = c - b * Q;
+    double a = 0.0;
+    for (int i = 0; i < H; ++i) a += fac(x3, l3, i) * T1[l2 * z.ts + b * H + i];
+    R[l3 * z.rs + c] = a;
+  }
+  __syncthreads();
+
+  // This wave's tiles of the stages and the lane's addresses in them, once for all terms (the index
+  // divisions would cost more than a term's MFMAs): tile (c0, i0) = (column, velocity) origin.
+  // Stage 1: multiplier offset (clamped in bounds: the slab's columns are contiguous in a row of the
+  // table, and the last slab may end inside them), R column, T1 slots of the lane's four results.
+  // Stage 2: T1 column and T2 slots.  Stage 3: T2 column, field offsets (clamped), E column.
+  const int Q2 = Q * Q;
+  const int ct1 = z.t1 / MT, ct2 = z.t2 / MT, ct3 = z.t3 / MT;
+  // (all as offsets: LDS ones from sm)
+  const int oR = 2 * KP * HP, oT1 = oR + KP * z.rs, oT2 = oT1 + KP * z.ts, trash = oT2 + 4 * KB * z.hs + lane;
+  int mcol[NT1], rcol[NT1], tcol[NT2], ycol[NT3], e3col[NT1], e2col[NT2], e1col[NT3];
+  int slot1[NT1][4], slot2[NT2][4];
+#pragma unroll
+  for (int j = 0; j < NT1; ++j) {
+    const int tile = min(wave + W * j, z.t1 - 1);
+    const int m = MT == 1 ? 0 : tile / ct1, c0 = (tile - m * ct1) * 16, i3 = m * 16 + cc;
+    rcol[j] = oR + kr * z.rs + c0 + cc;
+    e3col[j] = kr * HP + i3;
+    mcol[j] = (kr * Q2 + min(l10 * Q + min(c0 + cc, z.BQ - 1), Q2 - 1)) * 8;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = c0 + kr + 4 * r, b = c / Q, l2 = c - b * Q;
+      slot1[j][r] = wave + W * j < z.t1 && c < z.BQ && i3 < H ? oT1 + l2 * z.ts + b * H + i3 : trash;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NT2; ++j) {
+    const int tile = min(wave + W * j, z.t2 - 1);
+    const int m = MT == 1 ? 0 : tile / ct2, c0 = (tile - m * ct2) * 16, i2 = m * 16 + cc;
+    tcol[j] = oT1 + kr * z.ts + c0 + cc;
+    e2col[j] = kr * HP + i2;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = c0 + kr + 4 * r, b = c / H, i3 = c - b * H;
+      slot2[j][r] = wave + W * j < z.t2 && c < z.BH && i2 < H ? oT2 + b * z.hs + i2 * H + i3 : trash;
+    }
+  }
+  int foff[NT3];
+#pragma unroll
+  for (int q = 0; q < NT3; ++q) {
+    const int tile = min(wave + W * q, z.t3 - 1);
+    const int m = MT == 1 ? 0 : tile / ct3, c0 = (tile - m * ct3) * 16;
+    ycol[q] = oT2 + kr * z.hs + c0 + cc;
+    e1col[q] = min(l10 + kr, KP - 1) * HP + m * 16 + cc;   // rows of T2 past the slab are zero
+    foff[q] = ((m * 16 + kr) * z.HH + min(c0 + cc, z.HH - 1)) * 8;
+  }
+  const int e1step = KB == 2 ? (min(l10 + 4 + kr, KP - 1) - min(l10 + kr, KP - 1)) * HP : 0;
+  double mv[NT1][KS], fv[NT3][4];
+  // a scalar base (the tables' rows are padded to whole k-steps and tiles) and a 32-bit byte offset
+  auto at = [](const double* base, int off) {
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(base) + static_cast<unsigned>(off));
+  };
+  const int64_t mterm = static_cast<int64_t>(KP) * Q2, fterm = static_cast<int64_t>(HP) * z.HH;
+  auto load_mult = [&](int t) {
+    const double* mt = mult + t * mterm;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int j = 0; j < NT1; ++j) mv[j][ks] = at(mt + 4 * ks * Q2, mcol[j]);
+  };
+  auto load_field = [&](int t) {
+    const double* ft = field + t * fterm;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int q = 0; q < NT3; ++q) fv[q][r] = at(ft + 4 * r * z.HH, foff[q]);
+  };
+  v4d G[NT3];
+#pragma unroll
+  for (int q = 0; q < NT3; ++q) G[q] = v4d{0.0, 0.0, 0.0, 0.0};
+  auto stage1 = [&](int part) {
+    const int e = (x3 ^ ((part >> 2) & 1)) * KP * HP;
+    v4d o[NT1];
+#pragma unroll
+    for (int j = 0; j < NT1; ++j) o[j] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int j = 0; j < NT1; ++j)
+        if (!GUARD || wave + W * j < z.t1) o[j] = mfma(mv[j][ks] * sm[rcol[j] + 4 * ks * z.rs], sm[e3col[j] + e + 4 * ks * HP], o[j]);
+#pragma unroll
+    for (int j = 0; j < NT1; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sm[slot1[j][r]] = o[j][r];
+  };
+  auto stage2 = [&](int part) {
+    const int e = (x2 ^ ((part >> 1) & 1)) * KP * HP;
+    v4d o[NT2];
+#pragma unroll
+    for (int j = 0; j < NT2; ++j) o[j] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int j = 0; j < NT2; ++j)
+        if (!GUARD || wave + W * j < z.t2) o[j] = mfma(sm[tcol[j] + 4 * ks * z.ts], sm[e2col[j] + e + 4 * ks * HP], o[j]);
+#pragma unroll
+    for (int j = 0; j < NT2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sm[slot2[j][r]] = o[j][r];
+  };
+  auto stage3 = [&](int part) {
+    const int e = (x1 ^ (part & 1)) * KP * HP;
+    // i^(odd axes after - odd axes before): the phases of the sine axes
+    const int after = (x1 ^ (part & 1)) + (x2 ^ ((part >> 1) & 1)) + (x3 ^ ((part >> 2) & 1));
+    const double sgn = after == x1 + x2 + x3 ? 1.0 : -1.0;
+    v4d o[NT3];
+#pragma unroll
+    for (int q = 0; q < NT3; ++q) o[q] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int q = 0; q < NT3; ++q)
+        if (!GUARD || wave + W * q < z.t3) o[q] = mfma(sm[e1col[q] + e + kb * e1step], sm[ycol[q] + 4 * kb * z.hs], o[q]);
+#pragma unroll
+    for (int q = 0; q < NT3; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) G[q][r] += fv[q][r] * (sgn * o[q][r]);
+  };
+  // Between two barriers: stage 1 of a term with stage 3 of the one before, then stage 2.  The next
+  // term's multipliers are loaded once stage 1 has used this term's, its fields before stage 2; the
+  // scheduler must not pull their first use across the barrier (it would wait for them there).
+  const int t0 = static_cast<int>(static_cast<int64_t>(d.T) * blockIdx.z / gridDim.z);
+  const int last = static_cast<int>(static_cast<int64_t>(d.T) * (blockIdx.z + 1) / gridDim.z) - 1;
+  load_mult(t0);
+  int part = parts[t0];
+  stage1(part);
+  load_mult(min(t0 + 1, last));
+  __syncthreads();
+  for (int t = t0; t < last; ++t) {
+    const int next = parts[t + 1];
+    load_field(t);
+    stage2(part);
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    stage1(next);
+    load_mult(min(t + 2, last));
+    stage3(part);
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    part = next;
+  }
+  load_field(last);
+  stage2(part);
+  __syncthreads();
+  stage3(part);
+  double* out = accp + (blockIdx.z * gridDim.y + blockIdx.y) * acc_stride + (cell * d.nb + cls) * static_cast<int64_t>(d.ld);
+#pragma unroll
+  for (int q = 0; q < NT3; ++q) {
+    const int tile = wave + W * q;
+    if (tile < z.t3) {
+      const int c = (tile % ct3) * 16 + cc, i0 = (tile / ct3) * 16 + kr;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (c < z.HH && i0 + 4 * r < H) out[(i0 + 4 * r) * z.HH + c] = G[q][r];
+    }
   }
 }
 
-// ---------------------------------------------------------------- inverse
-// One workgroup per (cell, slab of B1 l1 modes).  The slab of the spectrum and the
-// factor matrices stay in LDS for all terms; per term t:
-//   stage 1  Y1(s3, b, l2) = sum_l3 E3(s3, l3) m_t(l3, l1, l2) S(l1, l3, l2)
-//   stage 2  Y2(b, s2, s3) = sum_l2 Y1(s3, b, l2) E2(s2, l2)      (rows (s3, b))
-//   stage 3  G(j1, s2, s3) += field_t(j1, s2, s3) Re sum_b E1(j1, l1) Y2(b, s2, s3)
-// (l1 = l10 + b).  Each block's operands for all its k-steps (stage 1) or four
-// k-steps at a time (stage 2) are loaded before its MFMAs, so one load latency is
-// paid per block or chunk, not per k-step.  G stays in registers: stage-3 tile q
-// of wave w is tile w + 8q.
-constexpr int kKs1 = 8;   // stage-1 k-steps held in registers: Q <= 32 (n_pad <= 64)
+// Parity parts of the multipliers and fields (see launch_fsm_fold): part k of term t, odd along
+// the axes of the bits of part[t] (none or two; every table is even under inversion), is the mean over
+// the images (l1, l2, l3), (-l1, l2, l3), (l1, l2, -l3), (-l1, l2, -l3) with the signs of axes 1 and 3.
+__global__ __launch_bounds__(256) void fsm_fold_mult_kernel(FsmDims d, int T, int rows, const double* __restrict__ mult,
+                                                            const int* __restrict__ row, const int* __restrict__ part,
+                                                            double* __restrict__ out) {
+  const int Q = d.Q, L = d.L, half = d.P / 2 - 1;
+  const int64_t len = static_cast<int64_t>(rows) * Q * Q;
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= T * len) return;
+  const int t = static_cast<int>(i / len);
+  const int r = static_cast<int>(i - t * len);
+  const int l2 = r % Q, l1 = (r / Q) % Q, l3 = r / (Q * Q);
+  if (l3 >= Q) {
+    out[i] = 0.0;
+    return;
+  }
+  const double* m = mult + static_cast<int64_t>(row[t]) * Q * L * L;
+  auto at = [&](int a, int b) { return m[(static_cast<int64_t>(l3) * L + half + a) * L + half + b]; };
+  const double s1 = part[t] & 1 ? -1.0 : 1.0, s3 = part[t] & 4 ? -1.0 : 1.0;
+  // (-l1, l2, l3); (l1, l2, -l3) ~ (-l1, -l2, l3); (-l1, l2, -l3) ~ (l1, -l2, l3)
+  out[i] = 0.25 * ((at(l1, l2) + s1 * at(-l1, l2)) + s3 * (at(-l1, -l2) + s1 * at(l1, -l2)));
+}
 
-constexpr int kInvWaves = 8;
-constexpr int kInvThreads = 64 * kInvWaves;
-
-template <int MAXG>
-__global__ __launch_bounds__(kInvThreads) void fsm_inverse_kernel(FsmDims d, FsmFactors f, int B1,
-                                                               const double* __restrict__ S,
-                                                               const double* __restrict__ mult,
-                                                               const double* __restrict__ field,
-                                                               double* __restrict__ accp, int64_t n_cells) {
-  extern __shared__ double sm[];
-  const int slab = blockIdx.x;
-  const int64_t cell = blockIdx.y;
-  const int n = d.n, n2 = d.n2, n3 = d.n3, L = d.L, Q = d.Q;
-  const int l10 = slab * B1, nb = min(B1, L - l10);
-  const int NB = B1 * L;
-  const int N3c = n2 * n3;
-  double* Sr = sm;                 // [Q][B1][L]
-  double* Si = Sr + Q * NB;
-  double* Y1r = Si + Q * NB;       // [n3][B1][L]
-  double* Y1i = Y1r + n3 * NB;
-  // Rows padded by one double where 16 lanes read (or write) down a column: E3 (stride Q, 32 at
-  // n_pad 64), Y2 (stride n3) and E1 (stride B1) would otherwise put those lanes on a few banks.
-  const int Qp = Q + 1, n3p = n3 + 1, B1p = B1 + 1;
-  const int N3p = n2 * n3p;
-  double* Y2r = Y1i + n3 * NB;     // [B1][n2][n3 + 1]
-  double* Y2i = Y2r + B1 * N3p;
-  double* E3r = Y2i + B1 * N3p;    // [n3][Q + 1]
-  double* E3i = E3r + n3 * Qp;
-  double* E2r = E3i + n3 * Qp;     // [n2][L]
-  double* E2i = E2r + n2 * L;
-  double* E1r = E2i + n2 * L;      // [n][B1 + 1] (the slab's columns)
-  double* E1i = E1r + n * B1p;
-  double* pf = E1i + n * B1p;      // 256 B that the multiplier prefetch writes and nothing reads
-  // wave index as a scalar: the per-wave block and tile loops below branch uniformly
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
-
-  const double* Sc = S + (cell * L + l10) * 2 * static_cast<int64_t>(Q) * L;
-  for (int i = threadIdx.x; i < nb * 2 * Q * L; i += kInvThreads) {
-    const int l2 = i % L;
-    int r = i / L;
-    const int l3 = r % Q;
-    r /= Q;
-    const int ri = r & 1, b = r >> 1;
-    (ri ? Si : Sr)[l3 * NB + b * L + l2] = Sc[i];
+__global__ __launch_bounds__(256) void fsm_fold_field_kernel(int n, int T, int rows, const double* __restrict__ in,
+                                                             const double* __restrict__ feq,
+                                                             const int* __restrict__ src, const int* __restrict__ part,
+                                                             const double* __restrict__ coef,
+                                                             double* __restrict__ out) {
+  const int H = n / 2;
+  const int64_t len = static_cast<int64_t>(rows) * H * H;
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= T * len) return;
+  const int t = static_cast<int>(i / len);
+  const int r = static_cast<int>(i - t * len);
+  const int i3 = r % H, i2 = (r / H) % H, i1 = r / (H * H);
+  if (i1 >= H) {
+    out[i] = 0.0;
+    return;
   }
-  for (int i = threadIdx.x; i < n3 * Q; i += kInvThreads) {
-    const int o = (i / Q) * Qp + i % Q;
-    E3r[o] = f.e3r[i];
-    E3i[o] = f.e3i[i];
-  }
-  for (int i = threadIdx.x; i < n2 * L; i += kInvThreads) {
-    E2r[i] = f.e2r[i];
-    E2i[i] = f.e2i[i];
-  }
-  for (int i = threadIdx.x; i < n * B1; i += kInvThreads) {
-    const int j1 = i / B1, b = i - j1 * B1;
-    E1r[j1 * B1p + b] = b < nb ? f.e1r[j1 * L + l10 + b] : 0.0;
-    E1i[j1 * B1p + b] = b < nb ? f.e1i[j1 * L + l10 + b] : 0.0;
-  }
-  __syncthreads();
-
-  const int nb3 = (N3c + 15) / 16;
-  const int tiles3 = ((n + 15) / 16) * nb3;
-  v4d G[MAXG];
-#pragma unroll
-  for (int q = 0; q < MAXG; ++q) G[q] = v4d{0.0, 0.0, 0.0, 0.0};
-  const int64_t LL = static_cast<int64_t>(L) * L;
-  const int64_t qll = static_cast<int64_t>(Q) * LL;
-  const int nks1 = (Q + 3) / 4, nks2 = (L + 3) / 4;
-  // Stage 2 has few 16 x 16 tiles (2 for 32^3 velocities on the v2, v3 > 0 quarter).  When two
-  // per tile fit in the waves, each tile's k-steps are split in two halves taken by different
-  // waves, which evens out the four SIMDs' work: both halves add into the zeroed Y2, and
-  // 0 + x + y rounds the same in either order, so the result does not depend on which wave adds
-  // first.  The split costs a zeroing pass and a barrier per term, so it is used only then.
-  const int mb2 = (n3 * B1 + 15) / 16, nbk2 = (n2 + 15) / 16;
-  const bool ksplit = 2 * mb2 * nbk2 <= kInvWaves;
-
-  for (int t = 0; t < d.T; ++t) {
-    const double* mt = mult + t * qll + static_cast<int64_t>(l10) * L;
-    // with the split, Y2 is accumulated by stage 2; nothing reads or writes it during stage 1
-    if (ksplit)
-      for (int i = threadIdx.x; i < 2 * B1 * N3p; i += kInvThreads) Y2r[i] = 0.0;
-    {
-      // stage 1: M = n3, N = nb L, K = Q
-      const int M = n3, N = nb * L;
-      const int mb = (M + 15) / 16, nbk = (N + 15) / 16;
-      for (int blk = wave; blk < mb * nbk; blk += kInvWaves) {
-        const int m0 = (blk / nbk) * 16, n0 = (blk % nbk) * 16;
-        const int m = m0 + cc, c = n0 + cc;
-        // Loads from clamped (in-bounds) addresses, masked after the load: no lane-divergent
-        // branch between them, so all of a block's loads are in flight together.
-        const int mcl = min(m, M - 1), ccl = min(c, N - 1);
-        // All loads first, nothing computed from them until every one is issued (one latency per block).
-        double ar[kKs1], ai[kKs1], mv[kKs1], br[kKs1], bi[kKs1];
-#pragma unroll
-        for (int ks = 0; ks < kKs1; ++ks) {
-          ar[ks] = ai[ks] = mv[ks] = br[ks] = bi[ks] = 0.0;
-          if (ks < nks1) {
-            const int kcl = min(ks * 4 + kr, Q - 1);
-            ar[ks] = E3r[mcl * Qp + kcl];
-            ai[ks] = E3i[mcl * Qp + kcl];
-            mv[ks] = mt[kcl * LL + ccl];
-            br[ks] = Sr[kcl * NB + ccl];
-            bi[ks] = Si[kcl * NB + ccl];
-          }
-        }
-        v4d cr = v4d{0.0, 0.0, 0.0, 0.0}, ci = cr;
-#pragma unroll
-        for (int ks = 0; ks < kKs1; ++ks)
-          if (ks < nks1) {
-            const int k = ks * 4 + kr;
-            const bool oka = k < Q && m < M, okb = k < Q && c < N;
-            const double xr = oka ? ar[ks] : 0.0;
-            const double xi = oka ? -ai[ks] : 0.0;   // negated: the imaginary product enters cr with a minus
-            const double yr = okb ? mv[ks] * br[ks] : 0.0;
-            const double yi = okb ? mv[ks] * bi[ks] : 0.0;
-            cr = mfma(xr, yr, cr);
-            ci = mfma(xr, yi, ci);
-            cr = mfma(xi, yi, cr);
-            ci = mfma(-xi, yr, ci);
-          }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = m0 + kr + 4 * r;
-          if (row < M && c < N) {
-            Y1r[row * NB + c] = cr[r];
-            Y1i[row * NB + c] = ci[r];
-          }
-        }
-      }
-    }
-    __syncthreads();
-    if (t + 1 < d.T) {
-      // Prefetch into L2 the multiplier lines that the stage-1 blocks read in the next term
-      // (otherwise each block's first loads wait on a table of 55 MB to 0.3 GB in MALL or HBM):
-      // one dword per line, lanes 0..31 the first and lanes 32..63 the last line of each row's
-      // 16 columns.  The dwords land in pf through the LDS DMA path, so no register holds them.
-      // The waves that stage 2 leaves idle issue it, so it does not delay stage 2.
-      const double* mn = mult + (t + 1) * qll + static_cast<int64_t>(l10) * L;
-      const int N1 = nb * L, nbk1 = (N1 + 15) / 16;
-      const int kp = min(lane & 31, Q - 1);
-      const int items2 = (ksplit ? 2 : 1) * mb2 * nbk2, nidle = kInvWaves - items2;
-      const int first = nidle > 0 ? wave - items2 : wave, step = nidle > 0 ? nidle : kInvWaves;
-      for (int blk = first; blk >= 0 && blk < ((n3 + 15) / 16) * nbk1; blk += step) {
-        const int n0 = (blk % nbk1) * 16;
-        const int c = lane < 32 ? n0 : min(n0 + 15, N1 - 1);
-        __builtin_amdgcn_global_load_lds((gbl_void_t*)(mn + kp * LL + c), (lds_void_t*)pf, 4, 0, 0);
-      }
-    }
-    {
-      // stage 2: rows r = (s3, b) (M = n3 B1), columns s2 (N = n2), K = L
-      const int M = n3 * B1, N = n2, nbk = nbk2;
-      const int kh = ksplit ? (nks2 + 1) / 2 : nks2;
-      for (int it = wave; it < (ksplit ? 2 : 1) * mb2 * nbk2; it += kInvWaves) {
-        const int blk = ksplit ? it >> 1 : it;
-        const int kb = ksplit && (it & 1) ? kh : 0, ke = ksplit && !(it & 1) ? kh : nks2;
-        const int m0 = (blk / nbk) * 16, n0 = (blk % nbk) * 16;
-        const int r = m0 + cc, s2 = n0 + cc;
-        const bool rowok = r < M && (r % B1) < nb, colok = s2 < N;
-        const int rcl = min(r, M - 1), s2cl = min(s2, N - 1);
-        v4d cr = v4d{0.0, 0.0, 0.0, 0.0}, ci = cr;
-        for (int kc = kb; kc < ke; kc += 4) {
-          double ar[4], ai[4], br[4], bi[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int k = (kc + u) * 4 + kr, kcl = min(k, L - 1);
-            const bool ok = kc + u < ke && k < L;
-            const double yr = Y1r[rcl * L + kcl], yi = Y1i[rcl * L + kcl];
-            const double er = E2r[s2cl * L + kcl], ei = E2i[s2cl * L + kcl];
-            ar[u] = ok && rowok ? yr : 0.0;
-            ai[u] = ok && rowok ? yi : 0.0;
-            br[u] = ok && colok ? er : 0.0;
-            bi[u] = ok && colok ? ei : 0.0;
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (kc + u < ke) {
-              cr = mfma(ar[u], br[u], cr);
-              ci = mfma(ar[u], bi[u], ci);
-              cr = mfma(-ai[u], bi[u], cr);
-              ci = mfma(ai[u], br[u], ci);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int row = m0 + kr + 4 * q, col = n0 + cc;
-          const int s3 = row / B1, b = row - s3 * B1;
-          if (row < M && b < nb && col < N) {
-            const int o = (b * n2 + col) * n3p + s3;
-            if (ksplit) {
-              __hip_atomic_fetch_add(&Y2r[o], cr[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-              __hip_atomic_fetch_add(&Y2i[o], ci[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            } else {
-              Y2r[o] = cr[q];
-              Y2i[o] = ci[q];
-            }
-          }
-        }
-      }
-    }
-    __syncthreads();
-    {
-      const double* ft = field + static_cast<int64_t>(t) * d.nv;
-#pragma unroll
-      for (int q = 0; q < MAXG; ++q) {
-        const int tile = wave + kInvWaves * q;
-        if (tile < tiles3) {
-          const int m0 = (tile / nb3) * 16, n0 = (tile % nb3) * 16;
-          const int col = n0 + cc, ccl = min(col, N3c - 1);
-          // Unmasked loads from clamped addresses (finite values): rows or columns outside the grid
-          // accumulate into entries of G that are never stored, and a masked load would be turned
-          // into a branch with its own wait.
-          double fv[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) fv[r] = ft[min(m0 + kr + 4 * r, n - 1) * N3c + ccl];
-          v4d o = v4d{0.0, 0.0, 0.0, 0.0};
-          // the lane's column s2 n3 + s3 of the tile in the padded Y2 rows
-          const int s2c = ccl / n3, colp = s2c * n3p + (ccl - s2c * n3);
-          const int mcl = min(m0 + cc, n - 1);
-          for (int k0 = 0; k0 < 2 * B1; k0 += 4) {
-            const int kk = min(k0 + kr, 2 * B1 - 1);
-            const int ri = kk / B1, b = kk - ri * B1;
-            const bool okk = k0 + kr < 2 * B1 && b < nb;
-            const double e = (ri ? E1i : E1r)[mcl * B1p + b];
-            const double y = (ri ? Y2i : Y2r)[b * N3p + colp];
-            const double av = okk && m0 + cc < n ? (ri ? -e : e) : 0.0;
-            const double bv = okk && col < N3c ? y : 0.0;
-            o = mfma(av, bv, o);
-          }
-#pragma unroll
-          for (int r = 0; r < 4; ++r) G[q][r] += fv[r] * o[r];
-        }
-      }
-    }
-    if (ksplit) __syncthreads();   // every read of Y2 done before the next term zeroes it
-  }
-  // no prefetch into pf may still be in flight when the workgroup's LDS is released
-  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
-  double* out = accp + (static_cast<int64_t>(slab) * n_cells + cell) * d.nv;
-#pragma unroll
-  for (int q = 0; q < MAXG; ++q) {
-    const int tile = wave + kInvWaves * q;
-    if (tile < tiles3) {
-      const int m0 = (tile / nb3) * 16, n0 = (tile % nb3) * 16;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int j1 = m0 + kr + 4 * r, c = n0 + cc;
-        if (j1 < n && c < N3c) out[j1 * N3c + c] = G[q][r];
-      }
-    }
-  }
+  const double* f = src[t] >= 0 ? in + static_cast<int64_t>(src[t]) * n * n * n : feq;
+  auto at = [&](int m1, int m3) {   // reflected along axes 1, 3
+    const int a = m1 ? H - 1 - i1 : H + i1, c = m3 ? H - 1 - i3 : H + i3;
+    return f[(static_cast<int64_t>(a) * n + H + i2) * n + c];
+  };
+  const double s1 = part[t] & 1 ? -1.0 : 1.0, s3 = part[t] & 4 ? -1.0 : 1.0;
+  out[i] = coef[t] * 0.25 * ((at(0, 0) + s1 * at(1, 0)) + s3 * (at(0, 1) + s1 * at(1, 1)));
 }
 
 // ---------------------------------------------------------------- plan tables
@@ -569,18 +533,6 @@ __global__ __launch_bounds__(kThreads) void fsm_table_kernel(FsmTableArgs a, int
   }
 }
 
-__global__ void fsm_gather_kernel(FsmDims d, int nrows, const double* __restrict__ in, const int* __restrict__ src,
-                                  const double* __restrict__ feq, double scale, double* __restrict__ out) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= static_cast<int64_t>(nrows) * d.nv) return;
-  const int t = static_cast<int>(i / d.nv), v = static_cast<int>(i - static_cast<int64_t>(t) * d.nv);
-  const int s3 = v % d.n3, s2 = (v / d.n3) % d.n2, j1 = v / (d.n3 * d.n2);
-  const int n = d.n;
-  const int64_t full = (static_cast<int64_t>(j1) * n + s2 + (n - d.n2)) * n + s3 + (n - d.n3);
-  const int r = src[t];
-  out[i] = scale * (r >= 0 ? in[static_cast<int64_t>(r) * n * n * n + full] : -feq[full]);
-}
-
 __global__ void fsm_shift_factor_kernel(int nt, int m, int nl, int lmin, int doubled, const int* __restrict__ base,
                                         const double* __restrict__ shift, int shift_stride, int P,
                                         double* __restrict__ er, double* __restrict__ ei) {
@@ -641,30 +593,30 @@ size_t table_lds_bytes(const FsmDims& d, int m2, int K1) {
   return static_cast<size_t>(2 * K1 * d.Q * d.L + 2 * K1 * d.Q * m2) * sizeof(double);
 }
 
-int stage3_tiles_per_wave(const FsmDims& d) {
-  const int tiles = ((d.n + 15) / 16) * ((d.n2 * d.n3 + 15) / 16);
-  return (tiles + kInvWaves - 1) / kInvWaves;
+size_t class_lds_bytes(const FsmClassDims& d, int B) {
+  const SlabShape z = slab_shape(d, B);
+  const int KP = 4 * class_ksteps(d);
+  return (static_cast<size_t>(KP) * (z.rs + z.ts) + 8 * z.hs +
+          2 * static_cast<size_t>(KP) * ((d.H + 15) / 16 * 16) + 64) * sizeof(double);
 }
 
-size_t forward_lds_bytes(const FsmDims& d, int B3) {
-  return static_cast<size_t>(2 * B3 * d.n * d.n2 + 2 * B3 * d.L * d.n) * sizeof(double);
-}
-
-// l3 modes per forward workgroup: the most (up to 4) whose LDS fits two workgroups per CU
-int forward_chunk(const FsmDims& d) {
-  int B3 = 4;
-  while (B3 > 1 && forward_lds_bytes(d, B3) > 80 * 1024) --B3;
-  return B3;
-}
-
-size_t inverse_lds_bytes(const FsmDims& d, int B1) {
-  const size_t NB = static_cast<size_t>(B1) * d.L;
-  // Y2, E3 and E1 rows padded by one double (bank spread of the column-wise lane accesses)
-  // (+ 32 doubles written by the multiplier prefetch)
-  return (2 * d.Q * NB + 2 * d.n3 * NB + 2 * static_cast<size_t>(B1) * d.n2 * (d.n3 + 1) +
-          2 * static_cast<size_t>(d.n3) * (d.Q + 1) + 2 * static_cast<size_t>(d.n2) * d.L +
-          2 * static_cast<size_t>(d.n) * (B1 + 1) + 32) *
-         sizeof(double);
+// Kernel of a slab and its waves (4 or 8: a whole number per SIMD, so that two workgroups share a CU), by
+// the tiles per wave of the stages: four waves with up to (3, 2, 3) tiles for slabs of more than 4 and
+// (2, 1, 4) for narrower ones (the default slabs of 16 to 24 and of 25 to 32 modes), else eight with up to
+// (2, 1, 2); velocity axes of more than 16 nodes have a kernel of their own.  W = 0: none.
+struct ClassKernel {
+  int W, kind;
+  bool exact;   // every wave has its full share: no guards
+};
+ClassKernel class_kernel(const FsmClassDims& d, int B) {
+  const SlabShape z = slab_shape(d, B);
+  auto fits = [&](int w, int n1, int n2, int n3) { return z.t1 <= n1 * w && z.t2 <= n2 * w && z.t3 <= n3 * w; };
+  const int ks = class_ksteps(d);
+  if (d.H > 16) return {fits(8, 4, 3, 6) ? 8 : 0, 3, false};
+  if (fits(4, 2, 1, 2)) return {4, 0, false};
+  if (z.kb4 == 2 && ks <= 6 && fits(4, 3, 2, 3)) return {4, 1, z.t1 > 8 && z.t2 > 4 && z.t3 > 8 && z.t1 % 4 == 0};
+  if (z.kb4 == 1 && ks >= 7 && fits(4, 2, 1, 4)) return {4, 2, z.t1 == 8 && z.t2 == 4 && z.t3 > 12};
+  return {fits(8, 2, 1, 2) ? 8 : 0, 0, false};
 }
 
 constexpr size_t kLdsMax = 160 * 1024;
@@ -677,23 +629,24 @@ hipError_t launch_fsm_multipliers(const FsmMultArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_fsm_forward(const FsmDims& d, const FsmFactors& f, int64_t n_cells, const double* h, double* S,
-                              hipStream_t s) {
-  if (n_cells <= 0) return hipSuccess;
-  const int B3 = forward_chunk(d);
-  const size_t lds = forward_lds_bytes(d, B3);
-  if (lds > kLdsMax) return hipErrorInvalidValue;
-  dim3 grid((d.Q + B3 - 1) / B3, static_cast<unsigned>(n_cells));
-  hipLaunchKernelGGL(fsm_forward_kernel, grid, dim3(kThreads), lds, s, d, f, B3, h, S);
+int fsm_mult_rows(const FsmClassDims& d) { return 4 * class_ksteps(d); }
+int fsm_field_rows(const FsmClassDims& d) { return (d.H + 15) / 16 * 16; }
+
+hipError_t launch_fsm_fold(const FsmDims& d, const FsmClassDims& c, const double* mult, const int* row, const int* part,
+                           double* out, hipStream_t s) {
+  const int rows = fsm_mult_rows(c);
+  const int64_t total = static_cast<int64_t>(c.T) * rows * c.Q * c.Q;
+  hipLaunchKernelGGL(fsm_fold_mult_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s, d, c.T, rows,
+                     mult, row, part, out);
   return hipGetLastError();
 }
 
-hipError_t launch_fsm_gather(const FsmDims& d, int nrows, const double* in, const int* src, const double* feq,
-                             double scale, double* out, hipStream_t s) {
-  const int64_t total = static_cast<int64_t>(nrows) * d.nv;
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fsm_gather_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s, d, nrows,
-                     in, src, feq, scale, out);
+hipError_t launch_fsm_fold_fields(const FsmClassDims& c, const double* in, const double* feq, const int* src,
+                                  const int* part, const double* coef, double* out, hipStream_t s) {
+  const int rows = fsm_field_rows(c);
+  const int64_t total = static_cast<int64_t>(c.T) * rows * c.H * c.H;
+  hipLaunchKernelGGL(fsm_fold_field_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s, 2 * c.H,
+                     c.T, rows, in, feq, src, part, coef, out);
   return hipGetLastError();
 }
 
@@ -745,73 +698,85 @@ hipError_t launch_fsm_tables(const FsmTableArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-int fsm_slab_count(const FsmDims& d, int slab_l1) { return (d.L + slab_l1 - 1) / slab_l1; }
+int fsm_slab_count(const FsmClassDims& d, int slab_l1) { return (d.Q + slab_l1 - 1) / slab_l1; }
 
-int fsm_default_slab(const FsmDims& d) {
-  int B1 = 4;
-  while (B1 > 1 && inverse_lds_bytes(d, B1) > kLdsMax) --B1;
-  return B1;
+int fsm_default_slab(const FsmClassDims& d) {
+  // the widest (up to 8) of which two workgroups fit a CU's LDS and four waves hold the tiles
+  int B = 8;
+  auto good = [&](int b) {
+    const int W = class_kernel(d, b).W;
+    return b <= d.Q && class_lds_bytes(d, b) <= kLdsMax / 2 && (W == 4 || (W && d.H > 16));
+  };
+  while (B > 1 && !good(B)) --B;
+  return B;
 }
 
-bool fsm_slab_fits(const FsmDims& d, int slab_l1) {
-  return slab_l1 >= 1 && slab_l1 <= d.L && inverse_lds_bytes(d, slab_l1) <= kLdsMax;
+bool fsm_slab_fits(const FsmClassDims& d, int slab_l1) {
+  return slab_l1 >= 1 && slab_l1 <= 8 && class_lds_bytes(d, slab_l1) <= kLdsMax && class_kernel(d, slab_l1).W;
 }
 
 const char* fsm_unsupported(const FsmDims& d) {
-  if (stage3_tiles_per_wave(d) > 8)
-    return "the per-cell transform path holds at most 64 x 16 x 16 outputs per cell (use parity storage)";
-  if (d.Q > 4 * kKs1) return "the per-cell transform path takes n_pad <= 64";
-  if (inverse_lds_bytes(d, 1) > kLdsMax || forward_lds_bytes(d, 1) > kLdsMax)
-    return "velocity grid too large for the per-cell transform path";
+  const int tiles = ((d.n + 15) / 16) * ((d.n2 * d.n3 + 15) / 16);
+  if (tiles > 64) return "the per-cell transform path holds at most 64 x 16 x 16 outputs per cell (use parity storage)";
+  if (d.Q > 32) return "the per-cell transform path takes n_pad <= 64";
   return nullptr;
 }
 
-hipError_t launch_fsm_inverse(const FsmDims& d, const FsmFactors& f, int slab_l1, int64_t n_cells, const double* S,
-                              const double* mult, const double* field, double* acc, hipStream_t s) {
+int fsm_sums(const FsmClassDims& d, int slab_l1, int64_t n_cells) {
+  // few cells: the terms are split over workgroups (at least four each) until two fit every CU twice
+  const int slabs = fsm_slab_count(d, slab_l1);
+  const int64_t groups = n_cells * d.nb * slabs;
+  return slabs * static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({1024 / std::max<int64_t>(groups, 1), 16, d.T / 4})));
+}
+
+hipError_t launch_fsm_class(const FsmClassDims& d, int slab_l1, int64_t n_cells, const double* X, const double* E,
+                            const double* mult, const double* field, const int* part, double* acc, int64_t acc_stride,
+                            hipStream_t s) {
   if (n_cells <= 0) return hipSuccess;
-  const size_t lds = inverse_lds_bytes(d, slab_l1);
-  if (lds > kLdsMax) return hipErrorInvalidValue;
-  dim3 grid(fsm_slab_count(d, slab_l1), static_cast<unsigned>(n_cells));
-  const int g = stage3_tiles_per_wave(d);
-  if (g <= 2)
-    hipLaunchKernelGGL(fsm_inverse_kernel<2>, grid, dim3(kInvThreads), lds, s, d, f, slab_l1, S, mult, field, acc,
-                       n_cells);
-  else if (g <= 4)
-    hipLaunchKernelGGL(fsm_inverse_kernel<4>, grid, dim3(kInvThreads), lds, s, d, f, slab_l1, S, mult, field, acc,
-                       n_cells);
-  else if (g <= 6)
-    hipLaunchKernelGGL(fsm_inverse_kernel<6>, grid, dim3(kInvThreads), lds, s, d, f, slab_l1, S, mult, field, acc,
-                       n_cells);
-  else if (g <= 8)
-    hipLaunchKernelGGL(fsm_inverse_kernel<8>, grid, dim3(kInvThreads), lds, s, d, f, slab_l1, S, mult, field, acc,
-                       n_cells);
-  else
-    return hipErrorInvalidValue;
+  const SlabShape z = slab_shape(d, slab_l1);
+  const size_t lds = class_lds_bytes(d, slab_l1);
+  const ClassKernel k = class_kernel(d, slab_l1);
+  const int ks = class_ksteps(d);
+  if (lds > kLdsMax || d.Q > 4 * ks || ks > 8 || d.H > 32 || !k.W) return hipErrorInvalidValue;
+  // consecutive workgroups take the same slab: the CUs of an XCD read the same multipliers
+  const int slabs = fsm_slab_count(d, slab_l1);
+  const dim3 grid(static_cast<unsigned>(n_cells * d.nb), slabs, fsm_sums(d, slab_l1, n_cells) / slabs);
+#define SIS_FSM(...)                                                                                                  \
+  hipLaunchKernelGGL((fsm_class_kernel<__VA_ARGS__>), grid, dim3(64 * k.W), lds, s, d, slab_l1, X, E, mult, field, part, \
+                     acc, acc_stride)
+  if (k.kind == 3) {
+    SIS_FSM(8, 2, 4, 3, 6, 2, true);
+  } else if (k.kind == 1) {
+    if (ks == 4) SIS_FSM(4, 2, 3, 2, 3, 1, true);
+    else if (ks == 5) SIS_FSM(5, 2, 3, 2, 3, 1, true);
+    else if (!k.exact) SIS_FSM(6, 2, 3, 2, 3, 1, true);
+    else SIS_FSM(6, 2, 3, 2, 3, 1, false);
+  } else if (k.kind == 2) {
+    if (ks == 7) SIS_FSM(7, 1, 2, 1, 4, 1, true);
+    else if (!k.exact) SIS_FSM(8, 1, 2, 1, 4, 1, true);
+    else SIS_FSM(8, 1, 2, 1, 4, 1, false);
+  } else if (ks == 4) {
+    SIS_FSM(4, 2, 2, 1, 2, 1, true);
+  } else if (ks == 5) {
+    SIS_FSM(5, 2, 2, 1, 2, 1, true);
+  } else if (ks == 6) {
+    SIS_FSM(6, 2, 2, 1, 2, 1, true);
+  } else if (ks == 7) {
+    SIS_FSM(7, 2, 2, 1, 2, 1, true);
+  } else {
+    SIS_FSM(8, 2, 2, 1, 2, 1, true);
+  }
+#undef SIS_FSM
   return hipGetLastError();
 }
 
-double fsm_flops_per_cell(const FsmDims& d, int slab_l1) {
-  // MFMAs issued (2048 flops each): forward stages, then per slab and term the three inverse stages
-  auto t16 = [](int x) { return static_cast<double>((x + 15) / 16); };
-  auto k4 = [](int x) { return static_cast<double>((x + 3) / 4); };
-  double fwd = 0.0;
-  const int B3 = forward_chunk(d);
-  for (int q0 = 0; q0 < d.Q; q0 += B3) {
-    const int nq = std::min(B3, d.Q - q0);
-    fwd += t16(nq) * t16(d.n * d.n2) * k4(d.n3) * 4.0;
-    fwd += t16(d.L) * t16(nq * d.n) * k4(d.n2) * 4.0;
-    fwd += t16(d.L) * t16(nq * d.L) * k4(d.n) * 4.0;
-  }
-  double inv = 0.0;
-  const int slabs = fsm_slab_count(d, slab_l1);
-  for (int sl = 0; sl < slabs; ++sl) {
-    const int nb = std::min(slab_l1, d.L - sl * slab_l1);
-    const double s1 = t16(d.n3) * t16(nb * d.L) * k4(d.Q) * 4.0;
-    const double s2 = t16(d.n3 * slab_l1) * t16(d.n2) * k4(d.L) * 4.0;
-    const double s3 = t16(d.n) * t16(d.n2 * d.n3) * k4(2 * slab_l1);
-    inv += d.T * (s1 + s2 + s3);
-  }
-  return 2048.0 * (fwd + inv);
+double fsm_flops_per_cell(const FsmClassDims& d, int slab_l1) {
+  // MFMAs issued (2048 flops each) by every class and slab, and the forward sums
+  const SlabShape z = slab_shape(d, slab_l1);
+  const int ks = class_ksteps(d), slabs = fsm_slab_count(d, slab_l1);
+  const double mfma = static_cast<double>(d.T) * ((z.t1 + z.t2) * ks + z.t3 * z.kb4);
+  const double fwd = 2.0 * d.H * (slab_l1 * z.HH + static_cast<double>(z.BQ) * d.H + static_cast<double>(d.Q) * z.BQ);
+  return d.nb * slabs * (2048.0 * mfma + fwd);
 }
 
 }  // namespace sis

@@ -3369,7 +3369,8 @@ template <int LOGB, int OUT>
 hipError_t class_rows(const SymMap& m, const double* X, const double* Xref, const int32_t* active, int64_t cells,
                       int row_len, void* out, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(cells), (row_len / 2 + 255) / 256);
-  if (m.pairs)
+  const bool aligned = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Xref)) & 15) == 0;
+  if (m.pairs && aligned)
     hipLaunchKernelGGL((class_rows_kernel<LOGB, OUT, true>), grid, dim3(256), 0, s, m, X, Xref, active, row_len, out);
   else
     hipLaunchKernelGGL((class_rows_kernel<LOGB, OUT, false>), grid, dim3(256), 0, s, m, X, Xref, active, row_len, out);
