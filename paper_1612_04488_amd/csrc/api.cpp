@@ -409,6 +409,9 @@ size_t class_row_bytes(const sis_plan* p, int precision) {
   return static_cast<size_t>(p->nb()) * sis::pair_stride(p->sym.kb) * 4;
 }
 
+// Bytes of a contraction's sum (the low-precision forms hold FP32)
+size_t sum_bytes(int precision) { return precision == SIS_PREC_FP64 ? 8 : 4; }
+
 // Cells per pass of a collision step: the class rows and one split's sums of a pass stay within
 // 2 GiB each, so that the workspace does not grow with the batch.
 int64_t pass_cells(const sis_plan* p, int64_t n_cells) {
@@ -491,12 +494,12 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
       const int sp = splits[si];
       if (sp > 1 && sis::gemm_k_per_split(K, sp) * (sp - 1) >= K) continue;   // an empty split
       if (sp > 1 && sis::gemm_k_per_split(K, sp) < 64) continue;
-      const double bytes = static_cast<double>(sp) * M * row * 8.0;
+      const double bytes = static_cast<double>(sp) * M * row * sum_bytes(precision);
       if (bytes > 4.0 * (1 << 30)) continue;
       err = ws_acc->ensure(static_cast<size_t>(bytes));
       if (err != hipSuccess) break;
       set_gemm_operands(p, precision, tiles[ti], h, nullptr, ws_x->p, g);
-      g.acc = static_cast<double*>(ws_acc->p);
+      g.acc = ws_acc->p;
       g.splits = sp;
       err = sis::launch_gemm(g, s);
       if (err == hipSuccess) err = hipEventRecord(e0, s);
@@ -515,10 +518,10 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
   if (err != hipSuccess) return fail(SIS_E_DEVICE, "contraction tuning: %s", hipGetErrorString(err));
   std::pair<int, int> best(dt, ds);
   if (!timed.empty()) {
-    // each split-K partial beyond the first costs the finish step one more FP64 row read per
-    // cell (M x row x 8 bytes at the ~4 TB/s that finish_kernel streams): add it to the timing
+    // each split-K partial beyond the first costs the finish step one more row read per
+    // cell (M x row sums at the ~4 TB/s that the finish step streams): add it to the timing
     for (auto& c : timed)
-      c.first += static_cast<float>((c.second.second - 1) * static_cast<double>(M) * row * 8.0 / 4.0e12 * 1e3);
+      c.first += static_cast<float>((c.second.second - 1) * static_cast<double>(M) * row * sum_bytes(precision) / 4.0e12 * 1e3);
     float fastest = timed[0].first;
     for (const auto& c : timed) fastest = std::min(fastest, c.first);
     // within 1% of the fastest: fewest split-K partials, then the larger tile, then the faster
@@ -538,7 +541,7 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
   }
   p->gemm_choice[key] = best;
   // the split-K partials of the kept configuration, not of the largest candidate
-  const size_t keep = static_cast<size_t>(best.second) * M * row * sizeof(double);
+  const size_t keep = static_cast<size_t>(best.second) * M * row * sum_bytes(precision);
   if (ws_acc->shrink(keep) != hipSuccess) return fail(SIS_E_DEVICE, "contraction tuning: scratch reallocation failed");
   return SIS_OK;
 }
@@ -605,7 +608,7 @@ struct CollideArgs {
 };
 
 // Cells [c0, c0 + nc) of a step: class rows, contraction, finish, with the workspace given.
-sis_status collide_pass(sis_plan* p, const CollideArgs& c, int64_t c0, int64_t nc, void* xrows, double* acc,
+sis_status collide_pass(sis_plan* p, const CollideArgs& c, int64_t c0, int64_t nc, void* xrows, void* acc,
                         bool capturing, hipStream_t s) {
   const int64_t nd = p->ndof, row = p->row_len();
   const double* h = c.h + c0 * nd;
@@ -627,7 +630,8 @@ sis_status collide_pass(sis_plan* p, const CollideArgs& c, int64_t c0, int64_t n
                                   c.accref ? c.accref + c0 * row : nullptr);
   f.sym = p->sym;
   f.splits = c.splits;
-  f.acc = acc;
+  f.acc = static_cast<double*>(acc);
+  f.acc_f32 = c.precision != SIS_PREC_FP64;
   f.acc_stride = nc * row;
   HIP_TRY(sis::launch_finish(f, s));
   return SIS_OK;
@@ -657,7 +661,7 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
                 anchor_mode, xref, accref, 0, 0};
   gemm_config(p, n_cells, c.precision, &c.tile, &c.splits);
   const int64_t pass = pass_cells(p, n_cells);
-  const size_t acc_bytes = static_cast<size_t>(c.splits) * pass * p->row_len() * 8;
+  const size_t acc_bytes = static_cast<size_t>(c.splits) * pass * p->row_len() * sum_bytes(c.precision);
   const size_t x_bytes = own_rows(c.precision, c.tile) ? 0 : class_row_bytes(p, c.precision) * pass;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIP_TRY(hipStreamIsCapturing(s, &cs));
@@ -684,8 +688,7 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
   HIP_TRY(ws_x->ensure(x_bytes));
   if (capturing) ws_acc->captured = ws_x->captured = true;
   for (int64_t c0 = 0; c0 < n_cells; c0 += pass)
-    if (sis_status st = collide_pass(p, c, c0, std::min(pass, n_cells - c0), ws_x->p, static_cast<double*>(ws_acc->p),
-                                     capturing, s))
+    if (sis_status st = collide_pass(p, c, c0, std::min(pass, n_cells - c0), ws_x->p, ws_acc->p, capturing, s))
       return st;
   return SIS_OK;
 }
@@ -2991,7 +2994,7 @@ sis_status sis_collide_noalloc(sis_plan_t p, int64_t n_cells, const double* h, c
   // passes of cells whose class rows and partial sums fit the workspace (the rows first); the
   // split count is lowered while the partial sums keep the batch from one pass
   const size_t x_cell = own_rows(c.precision, c.tile) ? 0 : class_row_bytes(p, c.precision);
-  const size_t sum_cell = static_cast<size_t>(p->row_len()) * sizeof(double);
+  const size_t sum_cell = static_cast<size_t>(p->row_len()) * sum_bytes(c.precision);
   auto cells_that_fit = [&](int splits) {
     return static_cast<int64_t>((kStaticScratchBytes - 256) / (x_cell + splits * sum_cell));
   };
@@ -3005,7 +3008,7 @@ sis_status sis_collide_noalloc(sis_plan_t p, int64_t n_cells, const double* h, c
     if (e != hipSuccess) return fail(SIS_E_DEVICE, "workspace address: %s", hipGetErrorString(e));
   }
   unsigned char* ws = static_cast<unsigned char*>(base);
-  double* acc = reinterpret_cast<double*>(ws + (x_cell * pass + 255) / 256 * 256);
+  void* acc = ws + (x_cell * pass + 255) / 256 * 256;
   for (int64_t c0 = 0; c0 < n_cells; c0 += pass)
     if (sis_status st = collide_pass(p, c, c0, std::min(pass, n_cells - c0), ws, acc, true, stream)) return st;
   return SIS_OK;
@@ -3424,7 +3427,7 @@ sis_status sis_state_create(sis_plan_t p, sis_geom_t g, const sis_solve_opts* o,
     const int64_t pass = pass_cells(p, nc);
     for (const int prec : {static_cast<int>(SIS_PREC_FP64), p->precision}) {
       const auto [tile, splits] = p->gemm_choice[std::make_pair(nc, prec)];
-      ST_TRY(b->ws_acc.ensure(static_cast<size_t>(splits) * pass * p->row_len() * 8));
+      ST_TRY(b->ws_acc.ensure(static_cast<size_t>(splits) * pass * p->row_len() * sum_bytes(prec)));
       if (!own_rows(prec, tile)) ST_TRY(b->ws_x.ensure(class_row_bytes(p, prec) * pass));
     }
   }

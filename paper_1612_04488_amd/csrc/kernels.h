@@ -70,8 +70,7 @@ struct GemmShape {
 // Contraction acc[z][m][n] = sum_{k in split z} X[m][k] * op[n][k]  (op stored n x k), or with sym
 // the nb blocks of the classes: acc [z][m][nb][ld].
 // precision: 0 fp64 (op64), 1 fp32 (op32), 2 bf16x3, 3 bf16 (hi products only)
-// (Xp, opp in the pair layout).  Accumulators are written as double for every
-// precision.
+// (Xp, opp in the pair layout).
 struct GemmArgs {
   int precision;
   const double* X;         // FP64 cell operand (precision 0; with cells_own_rows the cells' rows)
@@ -81,7 +80,7 @@ struct GemmArgs {
   const double* op64;      // the matrix, or with sym its blocks (launch_class_operator)
   const float* op32;
   const uint16_t* opp;     // precisions 2, 3: the operator in the pair layout
-  double* acc;
+  void* acc;               // sums: doubles for precision 0, else floats (what the MFMA holds)
   int64_t M;
   int N, K;                // without sym
   const SymMap* sym;       // null: a plain product
@@ -115,6 +114,7 @@ struct FinishArgs {
   int splits;              // split-K partial sums in acc (0: the contraction is zero)
   const double* acc;       // [splits][rows][n3]; with classes (sym.logb > 0) [splits][cells][nb][ld]
   int64_t acc_stride;      // with classes: elements between splits
+  int acc_f32;             // with classes: acc holds floats
   SymMap sym;
   const double* h;         // [rows][n3]
   const double* dU;        // [rows] or null

@@ -755,10 +755,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void g
 }
 
 // ------------------------------------------------------------------ FP32 MFMA GEMM
-// Both operands are stored as float (class_rows_kernel rounds the cells' class sums).
+// Both operands are stored as float (class_rows_kernel rounds the cells' class sums), and so are the
+// sums, which the MFMA holds in FP32 (finish_class_kernel adds splits and anchors in FP64).
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ X0, const float* __restrict__ Op0,
-                                                       double* __restrict__ C0, GemmShape sh) {
+                                                       float* __restrict__ C0, GemmShape sh) {
   constexpr int BK = 32;
   constexpr int WAVES_N = BN / WN;
   constexpr int TM = WM / 16, TN = WN / 16;
@@ -780,7 +781,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   const int kend = min(sh.K, kbeg + sh.kps);
   const float* X = X0 + block * sh.xs;
   const float* Op = Op0 + block * sh.os;
-  double* Cz = C0 + split * sh.cz + block * sh.cs;
+  float* Cz = C0 + split * sh.cz + block * sh.cs;
 
   float4 ra[A_LD];
   float4 rb[B_LD];
@@ -876,7 +877,135 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       for (int r = 0; r < 4; ++r) {
         const int64_t gm = m0 + wm + i * 16 + kr * 4 + r;
         const int gn = n0 + wn + j * 16 + cc;
-        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = static_cast<double>(acc[i][j][r]);
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = acc[i][j][r];
+      }
+}
+
+// FP32 contraction on 128 x 128 tiles with LDS-DMA staging: the form of gemm_f64_dma_kernel with 16-byte
+// slots of four k values (quad p of a 32-deep stage, row r), so that a step of four MFMAs reads as
+// many LDS bytes per MFMA cycle as its pairs: lane (kq, c) of a block reads quad kq + 4 h and feeds
+// element e to the e-th MFMA (k = 4 kq + 16 h + e over the lane groups).  Waves, buffers, barriers, issue
+// order, padding by the buffer descriptors and tile order as there.  Bound by the FP32 MFMA: 808 cells
+// against two blocks of 4096^2 in 0.45-0.48 ms (113-120 of 157 TFLOP/s), where register-staged 64 x 128
+// and 128 x 128 tiles took 0.60-0.75 ms.
+// Preconditions (checked by the launcher): K, kps and the row strides multiples of 4, strides <= 2^21.
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void gemm_f32_dma_kernel(
+    const float* __restrict__ X0, const float* __restrict__ Op0, float* __restrict__ C0, GemmShape sh) {
+  __shared__ float4 buf0[2048];   // [operand][quad 0..7][row 0..127]
+  __shared__ float4 buf1[2048];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int2 tile = xcd_tile<8>();
+  const int64_t M = sh.M;
+  const int N = sh.N, ldx = sh.ldx, ldo = sh.ldo;
+  const int64_t m0 = static_cast<int64_t>(tile.y) * 128;
+  const int n0 = tile.x * 128;
+  const int block = blockIdx.z / sh.splits, split = blockIdx.z - block * sh.splits;
+  const int kbeg = split * sh.kps;
+  const int kend = min(sh.K, kbeg + sh.kps);
+  const int nk = kend > kbeg ? (kend - kbeg + 31) / 32 : 0;
+  const float* X = X0 + block * sh.xs;
+  const float* Op = Op0 + block * sh.os;
+  float* Cz = C0 + split * sh.cz + block * sh.cs;
+
+  const int rows_a = static_cast<int>(min<int64_t>(128, M - m0));
+  const int rows_b = min(128, N - n0);
+  const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(X + m0 * ldx), 0, ((rows_a - 1) * ldx + sh.K) * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(Op + static_cast<int64_t>(n0) * ldo), 0, ((rows_b - 1) * ldo + sh.K) * 4, 0x00020000);
+  uint32_t roff_a[2], roff_b[2];
+  int pj[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int slot = (8 * j + wave) * 64 + lane;
+    pj[j] = slot >> 7;
+    roff_a[j] = static_cast<uint32_t>(((slot & 127) * ldx + 4 * pj[j]) * 4);
+    roff_b[j] = static_cast<uint32_t>(((slot & 127) * ldo + 4 * pj[j]) * 4);
+  }
+  auto issue = [&](float4* buf, int k0) {
+    const int krem = kend - k0;
+    const uint32_t kb = static_cast<uint32_t>(k0) * 4u;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t vo = 4 * pj[j] < krem ? roff_a[j] + kb : 0x80000000u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_void_t*)&buf[(8 * j + wave) * 64], 16, vo, 0, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t vo = 4 * pj[j] < krem ? roff_b[j] + kb : 0x80000000u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_void_t*)&buf[1024 + (8 * j + wave) * 64], 16, vo, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  const int kq = lane >> 4, cc = lane & 15;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
+  v4f acc[2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  v4f a0[2], b0[4], a1[2], b1[4];
+  auto lread = [&](const float4* buf, int h, v4f* ar, v4f* br) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      ar[i] = *reinterpret_cast<const v4f*>(&buf[(kq + 4 * h) * 128 + wm + 16 * i + cc]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      br[j] = *reinterpret_cast<const v4f*>(&buf[1024 + (kq + 4 * h) * 128 + wn + 16 * j + cc]);
+  };
+  auto mfma = [&](const v4f* ar, const v4f* br) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[i][e], br[j][e], acc[i][j], 0, 0, 0);
+  };
+  auto stage = [&](float4* cur, float4* nxt, int k_dma) {
+    lread(cur, 1, a1, b1);
+    mfma(a0, b0);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    __syncthreads();
+    lread(nxt, 0, a0, b0);
+    __builtin_amdgcn_sched_barrier(0);
+    issue(cur, k_dma);
+    __builtin_amdgcn_s_setprio(0);
+    mfma(a1, b1);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  if (nk > 0) {
+    issue(buf0, kbeg);
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    __syncthreads();
+    issue(buf1, kbeg + (nk > 1 ? 32 : 0));
+    lread(buf0, 0, a0, b0);
+  }
+  int s = 0;
+  for (; s + 1 < nk; s += 2) {
+    stage(buf0, buf1, kbeg + (s + 2 < nk ? s + 2 : 0) * 32);
+    stage(buf1, buf0, kbeg + (s + 3 < nk ? s + 3 : 0) * 32);
+  }
+  if (s < nk) {
+    lread(buf0, 1, a1, b1);
+    mfma(a0, b0);
+    mfma(a1, b1);
+  }
+  // drain the clamped DMA before the workgroup can end
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t gm = m0 + wm + i * 16 + kq * 4 + r;
+        const int gn = n0 + wn + j * 16 + cc;
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = acc[i][j][r];
       }
 }
 
@@ -898,7 +1027,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // Row strides and block offsets of Xp and Op (sh.ldx, ldo, xs, os) are in bf16.
 template <int BM, int BN, int WM, int WN, int NPROD = 3, int LOGB = -1>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_bf16x3_kernel(
-    const uint16_t* __restrict__ Xp0, const uint16_t* __restrict__ Op0, double* __restrict__ C0, GemmShape sh,
+    const uint16_t* __restrict__ Xp0, const uint16_t* __restrict__ Op0, float* __restrict__ C0, GemmShape sh,
     const double* __restrict__ X, const double* __restrict__ Xref, SymMap sym) {
   constexpr bool FUSED = LOGB >= 0;
   constexpr int BK = 64;                      // two MFMA k-steps per stage
@@ -938,7 +1067,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   const int kend = min(sh.K, kbeg + sh.kps);
   const uint16_t* Xp = Xp0 + block * sh.xs;
   const uint16_t* Op = Op0 + block * sh.os;
-  double* Cz = C0 + split * sh.cz + block * sh.cs;
+  float* Cz = C0 + split * sh.cz + block * sh.cs;
 
   // (native vectors: HIP's uint4 struct copies from global memory kept the staging in scratch)
   u32x4 ra[2][A_LD], rb[2][B_LD];
@@ -1060,7 +1189,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
       for (int r = 0; r < 4; ++r) {
         const int64_t gm = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
         const int gn = n0 + wn + j * 16 + (lane & 15);
-        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = static_cast<double>(acc[i][j][r]);
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = acc[i][j][r];
       }
 }
 
@@ -1088,7 +1217,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 // both operands (32-bit DMA offsets).
 
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void gemm_bf16x3_wide_kernel(
-    const uint16_t* __restrict__ Xp0, const uint16_t* __restrict__ Op0, double* __restrict__ C0, GemmShape sh) {
+    const uint16_t* __restrict__ Xp0, const uint16_t* __restrict__ Op0, float* __restrict__ C0, GemmShape sh) {
   __shared__ uint4 buf0[512][8];
   __shared__ uint4 buf1[512][8];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1105,7 +1234,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
   const int kbeg = split * sh.kps;
   const int kend = min(sh.K, kbeg + sh.kps);
   const int nk = kend > kbeg ? (kend - kbeg) / 32 : 0;
-  double* Cz = C0 + split * sh.cz + block * sh.cs;
+  float* Cz = C0 + split * sh.cz + block * sh.cs;
 
   // DMA sources: waves 0-3 fill buffer rows 0-255 (cells), waves 4-7 rows 256-511
   // (operator rows), eight runs of eight rows each; rows past M or N read the last
@@ -1238,7 +1367,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
       for (int r = 0; r < 4; ++r) {
         const int64_t gm = m0 + wm + i * 16 + q * 4 + r;
         const int gn = n0 + wn + j * 16 + rr;
-        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = static_cast<double>(acc[i][j][r]);
+        if (gm < M && gn < N) Cz[gm * sh.ldc + gn] = acc[i][j][r];
       }
 }
 
@@ -1459,7 +1588,8 @@ __global__ __launch_bounds__(256) void finish_kernel(FinishArgs a) { finish_row(
 // once per velocity (24 576 cells of 6912, one split: 0.74 ms = 5.5 TB/s, where finish_row on
 // the whole matrix took 0.96 ms; 808 cells of 8192: 59 us with two splits, 76 us with four before).
 // T: v2d (pairs) or double.
-template <int LOGB, class T>
+// A: double, or float for the sums of the low-precision contractions.
+template <int LOGB, class T, class A>
 __device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t row, double (&m)[9]) {
   constexpr int NB = 1 << LOGB;
   constexpr bool PAIR = sizeof(T) == 16;
@@ -1487,6 +1617,17 @@ __device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t ro
   double* lh = a.lh ? a.lh + row * nv : nullptr;
   const int64_t cr = cell * static_cast<int64_t>(NB) * y.ld + static_cast<int64_t>(sp) * y.nvb;  // class row of this species
   auto ld = [](const double* p) { return *reinterpret_cast<const T*>(p); };
+  auto sum = [&](int64_t i) {
+    const A* p = reinterpret_cast<const A*>(a.acc) + i;
+    if constexpr (sizeof(A) == 8) {
+      return *reinterpret_cast<const T*>(p);
+    } else if constexpr (PAIR) {
+      const float2 f = *reinterpret_cast<const float2*>(p);
+      return T{f.x, f.y};
+    } else {
+      return static_cast<T>(*p);
+    }
+  };
   for (int k = threadIdx.x * STEP; k < y.nvb; k += blockDim.x * STEP) {
     int off[NB];
     orbit_images<LOGB>(y, k, off);
@@ -1517,7 +1658,7 @@ __device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t ro
 #pragma unroll
       for (int u = 0; u < UZ; ++u)
 #pragma unroll
-        for (int b = 0; b < NB; ++b) t[u][b] = ld(a.acc + (z + u) * a.acc_stride + cr + static_cast<int64_t>(b) * y.ld + k);
+        for (int b = 0; b < NB; ++b) t[u][b] = sum((z + u) * a.acc_stride + cr + static_cast<int64_t>(b) * y.ld + k);
 #pragma unroll
       for (int u = 0; u < UZ; ++u)
 #pragma unroll
@@ -1525,7 +1666,7 @@ __device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t ro
     }
     for (; z < a.splits; ++z)
 #pragma unroll
-      for (int b = 0; b < NB; ++b) s[b] += ld(a.acc + z * a.acc_stride + cr + static_cast<int64_t>(b) * y.ld + k);
+      for (int b = 0; b < NB; ++b) s[b] += sum(z * a.acc_stride + cr + static_cast<int64_t>(b) * y.ld + k);
     if (a.anchor_mode) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
@@ -1580,7 +1721,7 @@ __device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t ro
 }
 
 // pairs: every row, and the class rows, in 16-byte pairs (lh may be offset by 8 bytes)
-template <int LOGB>
+template <int LOGB, class A>
 __global__ __launch_bounds__(256) void finish_class_kernel(FinishArgs a) {
   const int64_t row = blockIdx.x;
   if (a.active && !a.active[row / a.nsp]) return;
@@ -1593,9 +1734,9 @@ __global__ __launch_bounds__(256) void finish_class_kernel(FinishArgs a) {
   bool pairs = false;
   if constexpr (LOGB < 3) {
     pairs = a.sym.pairs && (align & 15) == 0;
-    if (pairs) finish_class_row<LOGB, v2d>(a, row, m);
+    if (pairs) finish_class_row<LOGB, v2d, A>(a, row, m);
   }
-  if (!pairs) finish_class_row<LOGB, double>(a, row, m);
+  if (!pairs) finish_class_row<LOGB, double, A>(a, row, m);
   finish_tail(a, row, m);
 }
 
@@ -3466,11 +3607,13 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     sh.xs = 2 * Kp;
     sh.os = static_cast<int64_t>(sh.N) * 2 * Kp;
   }
-#define SIS_GEMM(kernel, threads, ...) hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, __VA_ARGS__, g.acc, sh)
+#define SIS_GEMM(kernel, threads, ...) hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, __VA_ARGS__, sh)
+  double* acc64 = static_cast<double*>(g.acc);
+  float* acc32 = static_cast<float*>(g.acc);
   if (g.precision == 0) {
     if (sh.K % 2 || sh.ldx % 2 || sh.ldo % 2) return hipErrorInvalidValue;   // rows are loaded in 16-byte k pairs
-#define SIS_F64(...) hipLaunchKernelGGL((gemm_f64_kernel<__VA_ARGS__>), grid, dim3(256), 0, s, g.X, g.op64, g.acc, sh, sym)
-    if (g.tile == 0 && sh.ldx <= (1 << 20) && sh.ldo <= (1 << 20)) SIS_GEMM(gemm_f64_dma_kernel, 512, g.X, g.op64);
+#define SIS_F64(...) hipLaunchKernelGGL((gemm_f64_kernel<__VA_ARGS__>), grid, dim3(256), 0, s, g.X, g.op64, acc64, sh, sym)
+    if (g.tile == 0 && sh.ldx <= (1 << 20) && sh.ldo <= (1 << 20)) SIS_GEMM(gemm_f64_dma_kernel, 512, g.X, g.op64, acc64);
     else if (g.tile == 0) SIS_F64(128, 128, 64, 64);
     else if (g.tile == 2) SIS_F64(64, 128, 32, 64);
     else if (g.tile == 3) SIS_F64(128, 128, 64, 64, 32, 1, 1);
@@ -3482,18 +3625,19 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
 #undef SIS_F64
   } else if (g.precision == 1) {
     if (!g.X32 || !g.op32) return hipErrorInvalidValue;
-    if (g.tile == 0) SIS_GEMM((gemm_f32_kernel<128, 128, 64, 64>), 256, g.X32, g.op32);
-    else if (g.tile == 2) SIS_GEMM((gemm_f32_kernel<64, 128, 32, 64>), 256, g.X32, g.op32);
-    else SIS_GEMM((gemm_f32_kernel<32, 128, 32, 32>), 256, g.X32, g.op32);
+    if (sh.ldx % 4 || sh.ldo % 4 || sh.K % 4 || sh.ldx > (1 << 21) || sh.ldo > (1 << 21)) return hipErrorInvalidValue;
+    if (g.tile == 0) SIS_GEMM(gemm_f32_dma_kernel, 512, g.X32, g.op32, acc32);
+    else if (g.tile == 2) SIS_GEMM((gemm_f32_kernel<64, 128, 32, 64>), 256, g.X32, g.op32, acc32);
+    else SIS_GEMM((gemm_f32_kernel<32, 128, 32, 32>), 256, g.X32, g.op32, acc32);
   } else {
     // bf16 forms: operands in the pair layout, k running over the padded Kp (zeros past K)
     if (!g.opp || (own_rows ? !g.X : !g.Xp)) return hipErrorInvalidValue;
 #define SIS_BF(...) \
-  hipLaunchKernelGGL((gemm_bf16x3_kernel<__VA_ARGS__>), grid, dim3(256), 0, s, g.Xp, g.opp, g.acc, sh, g.X, g.Xref, sym)
+  hipLaunchKernelGGL((gemm_bf16x3_kernel<__VA_ARGS__>), grid, dim3(256), 0, s, g.Xp, g.opp, acc32, sh, g.X, g.Xref, sym)
     if (g.tile == 5) {
       if (!gemm_wide_fits(g.M, sh.N, g.sym ? sym.kb : g.K, nb)) return hipErrorInvalidValue;
       const dim3 wgrid((sh.N + 255) / 256, static_cast<unsigned>((g.M + 255) / 256), sh.splits * nb);
-      hipLaunchKernelGGL(gemm_bf16x3_wide_kernel, wgrid, dim3(512), 0, s, g.Xp, g.opp, g.acc, sh);
+      hipLaunchKernelGGL(gemm_bf16x3_wide_kernel, wgrid, dim3(512), 0, s, g.Xp, g.opp, acc32, sh);
     } else if (g.precision == 3) {
       if (own_rows) {
         if (sym.logb == 1) SIS_BF(32, 128, 32, 32, 1, 1);
@@ -3517,12 +3661,16 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(a.n_cells));
+#define SIS_FINISH(LOGB)                                                                              \
+  if (a.acc_f32) hipLaunchKernelGGL((finish_class_kernel<LOGB, float>), grid, dim3(256), 0, s, a);    \
+  else hipLaunchKernelGGL((finish_class_kernel<LOGB, double>), grid, dim3(256), 0, s, a)
   switch (a.sym.logb) {
     case 0: hipLaunchKernelGGL(finish_kernel, grid, dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL(finish_class_kernel<1>, grid, dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(finish_class_kernel<2>, grid, dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL(finish_class_kernel<3>, grid, dim3(256), 0, s, a); break;
+    case 1: SIS_FINISH(1); break;
+    case 2: SIS_FINISH(2); break;
+    default: SIS_FINISH(3); break;
   }
+#undef SIS_FINISH
   return hipGetLastError();
 }
 
