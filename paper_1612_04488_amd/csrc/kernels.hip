@@ -15,6 +15,8 @@
 //                convergence test
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace sis {
@@ -30,6 +32,16 @@ __device__ inline double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
+}
+
+// num / den where inv = 1 / den is known: the quotient by inv corrected by its own remainder
+// (rounded as a division is, but for the last bit now and then), so that a chain of divisions
+// by denominators known beforehand waits for three multiply-adds each.  Where the remainder has
+// no value (infinities, den = 0) the plain product stands, which is then what a division gives.
+__device__ __forceinline__ double div_known(double num, double den, double inv) {
+  const double q = num * inv;
+  const double r = __builtin_fma(__builtin_fma(-den, q, num), inv, q);
+  return r == r ? r : q;
 }
 
 // Block-wide sum of K values per thread, fixed order.  Result in out[] for all threads.
@@ -1742,119 +1754,154 @@ __global__ __launch_bounds__(256) void finish_class_kernel(FinishArgs a) {
 
 // ------------------------------------------------------------------ sweep
 
-// One thread per (case, species, |v1| > 0 velocity pair): the two marches of a velocity are
-// serial in x1, so the right sides and stencil coefficients of the next kSweepChunk nodes are
-// loaded while the current ones are processed (the dependency chain then holds arithmetic
-// only).  Moments are taken afterwards by moments_kernel.
-constexpr int kSweepChunk = 8;
+// One thread per (case, species, |v1| > 0 velocity pair).  The two marches of a velocity are
+// serial in x1 and there are few threads (a wave or less for each SIMD), so what bounds it is
+// latency, of memory and of the instructions of a node.  Each thread keeps the right sides of
+// the next AHEAD nodes in flight, for the second march from the start.  Waits for one of
+// them count the loads and stores issued after it, so the code between them has no branches
+// (else the counts are those of the shortest path through them): whole chunks of AHEAD nodes,
+// then the remainder, for which nothing is left to load.  The stencil coefficients, which the
+// workgroup shares, come through LDS, the next chunk's loaded while this one is marched, and
+// the diagonals of kSweepGroup nodes are inverted before the march through them.
+// With the division on the chain, 8 nodes in flight and branches among them: 51 us for 8
+// cases of 101 nodes at 32^3, 106 us for the mixture's 16 cases of up to 201 at 24^3, 8.1 us for
+// 17 nodes at 16^3; now 27, 52 and 5.0.
+// Moments are taken afterwards by moments_kernel.
+constexpr int kSweepNT = 64;      // a wave a workgroup, over all compute units
+constexpr int kSweepAhead = 24;
+constexpr int kSweepGroup = 8;
 
+// One march: node i of it, counted from its first one, is cell first + dir * i (dir = +-1).
+// The pointers walk from row to row (a row's address as a product of 64 bits takes more
+// scalar instructions than the node itself).
+template <int NT, int AHEAD>   // NT: threads of the workgroup
+struct SweepMarch {
+  static constexpr int kPer = (3 * AHEAD + NT - 1) / NT;
+  const char* rhs;      // row of this species at the first node, advanced by the loads
+  char* h;              // the same of h, advanced by the stores
+  const double* coef;   // the direction's three coefficients at the first node
+  int64_t step;         // bytes from node to node of rhs and h
+  int dir, count;
+  uint32_t off;         // bytes of the velocity
+  double v1, dn;        // its speed, and its collision frequency times delta
+
+  // the right side of node i, then on to the next (which stays at the last one)
+  __device__ __forceinline__ double load(int i) {
+    const double x = *reinterpret_cast<const double*>(rhs + off);
+    rhs += i < count - 1 ? step : 0;
+    return x;
+  }
+  __device__ __forceinline__ void load(double (&r)[AHEAD]) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) r[u] = load(u);
+  }
+  // the coefficients of a chunk (what is left over of the threads repeats the last ones)
+  __device__ __forceinline__ void stage(int base, double (&c)[kPer]) const {
+#pragma unroll
+    for (int p = 0; p < kPer; ++p) {
+      const int e = min(static_cast<int>(threadIdx.x) + p * NT, 3 * AHEAD - 1);
+      c[p] = coef[dir * min(base + e / 3, count - 1) * 6 + e % 3];
+    }
+  }
+  __device__ __forceinline__ void put(double x) {
+    *reinterpret_cast<double*>(h + off) = x;
+    h += step;
+  }
+
+  // nodes base .. of a chunk: NODES of them (TAIL: `left`, with nothing more to load)
+  template <bool TAIL>
+  __device__ __forceinline__ void chunk(int base, int left, const double* sh, double& h1, double& h2,
+                                        double (&r)[AHEAD]) {
+#pragma unroll
+    for (int g0 = 0; g0 < AHEAD; g0 += kSweepGroup) {
+      if (TAIL && g0 >= left) break;
+      double den[kSweepGroup], inv[kSweepGroup], b[kSweepGroup], c[kSweepGroup];
+#pragma unroll
+      for (int u = 0; u < kSweepGroup; ++u) {
+        den[u] = __builtin_fma(v1, sh[3 * (g0 + u)], dn);
+        b[u] = sh[3 * (g0 + u) + 1];
+        c[u] = sh[3 * (g0 + u) + 2];
+      }
+#pragma unroll
+      for (int u = 0; u < kSweepGroup; ++u) inv[u] = 1.0 / den[u];
+#pragma unroll
+      for (int u = 0; u < kSweepGroup; ++u) asm volatile("" : "+v"(inv[u]));   // all of them before the march
+#pragma unroll
+      for (int u = 0; u < kSweepGroup; ++u) {
+        if (TAIL && g0 + u >= left) break;
+        const double val = div_known(r[g0 + u] - v1 * (b[u] * h1 + c[u] * h2), den[u], inv[u]);
+        put(val);
+        h2 = h1;
+        h1 = val;
+        if (!TAIL) r[g0 + u] = load(base + g0 + u + AHEAD);
+      }
+    }
+  }
+
+  // Marches from the values h1, h2 of the two nodes before the first; r holds the first right
+  // sides, next the first coefficients.
+  __device__ __forceinline__ void run(double& h1, double& h2, double (&r)[AHEAD], double (&next)[kPer], double* sh) {
+    auto staged = [&] {
+      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < kPer; ++p) sh[min(static_cast<int>(threadIdx.x) + p * NT, 3 * AHEAD - 1)] = next[p];
+      __syncthreads();
+    };
+    int base = 0;
+    for (; base + AHEAD <= count; base += AHEAD) {
+      staged();
+      stage(base + AHEAD, next);
+      chunk<false>(base, AHEAD, sh, h1, h2, r);
+    }
+    if (base < count) {
+      staged();
+      chunk<true>(base, count - base, sh, h1, h2, r);
+    }
+  }
+};
+
+template <int NT, int AHEAD>
 __device__ __forceinline__ void sweep1d_block(const SweepArgs& a, int bx, int cs, int sp) {
+  __shared__ double sh[3 * AHEAD];
   const int nsp = a.nsp;
-  if (a.case_active && !a.case_active[cs]) return;
+  if (a.case_active && !a.case_active[cs]) return;   // uniform over the workgroup
   const int half = a.n3 / 2, n3 = a.n3;
-  const int t = bx * blockDim.x + threadIdx.x;
-  if (t >= half) return;
   const int64_t c0 = a.node_off[cs];
   const int nodes = static_cast<int>(a.node_off[cs + 1] - c0);
+  // threads beyond the last velocity march it once more (and store the same values)
+  const int t = min(bx * NT + static_cast<int>(threadIdx.x), half - 1);
   const int d23 = a.d2 * a.d3;
   const int j1h = t / d23, r = t % d23;
   const int jp = a.n / 2 + j1h, jm = a.n / 2 - 1 - j1h;
   const int vp = jp * d23 + r, vm = jm * d23 + r;
-  const double v1 = a.v1d[jp];
-  const double del = a.delta_case[cs];
   const double* nu = a.nu + static_cast<int64_t>(sp) * n3;
-  const double dnp = del * nu[vp], dnm = del * nu[vm];
-  const double* __restrict__ rhs = a.rhs;
-  double* __restrict__ h = a.h;
-  const double* __restrict__ coef = a.coef;
-  // row of (cell, species) in the [cell][species][n3] arrays
-  auto row = [&](int64_t cell) { return (cell * nsp + sp) * static_cast<int64_t>(n3); };
-  double rc[kSweepChunk], ac[kSweepChunk], bc[kSweepChunk], cc[kSweepChunk];
-  double rn[kSweepChunk], an[kSweepChunk], bn[kSweepChunk], cn[kSweepChunk];
-  // v1 > 0: wall value 0, march towards the symmetry plane (nodes 1 .. nodes-1)
-  h[row(c0) + vp] = 0.0;
+  const double v1 = a.v1d[jp], del = a.delta_case[cs], dnp = del * nu[vp], dnm = del * nu[vm];
+  const uint32_t op = vp * 8u, om = vm * 8u;
+  // v1 > 0: wall value 0, march towards the symmetry plane (nodes 1 .. nodes-1); v1 < 0:
+  // specular reflection at the last node, march to the wall (nodes nodes-2 .. 0)
+  const int64_t step = static_cast<int64_t>(nsp) * n3 * 8, row0 = (c0 * nsp + sp) * n3 * 8;
+  const int64_t row1 = row0 + step, row2 = row0 + (nodes - 2) * step;
+  const char* rhs = reinterpret_cast<const char*>(a.rhs);
+  char* h = reinterpret_cast<char*>(a.h);
+  using March = SweepMarch<NT, AHEAD>;
+  March out = {rhs + row1, h + row0, a.coef + (c0 + 1) * 6, step, 1, nodes - 1, op, v1, dnp};
+  March in = {rhs + row2, h + row2 + step, a.coef + (c0 + nodes - 2) * 6 + 3, -step, -1, nodes - 1, om, v1, dnm};
+  double r_out[AHEAD], r_in[AHEAD], c_out[March::kPer], c_in[March::kPer];
+  out.stage(0, c_out);
+  out.load(r_out);
+  in.stage(0, c_in);
+  in.load(r_in);
   double h1 = 0.0, h2 = 0.0;
-#pragma unroll
-  for (int u = 0; u < kSweepChunk; ++u) {
-    const int i = 1 + u;
-    const int64_t cell = c0 + (i < nodes ? i : 0);
-    rc[u] = rhs[row(cell) + vp];
-    ac[u] = coef[cell * 6 + 0];
-    bc[u] = coef[cell * 6 + 1];
-    cc[u] = coef[cell * 6 + 2];
-  }
-  for (int base = 1; base < nodes; base += kSweepChunk) {
-#pragma unroll
-    for (int u = 0; u < kSweepChunk; ++u) {
-      const int i = base + kSweepChunk + u;
-      const int64_t cell = c0 + (i < nodes ? i : 0);
-      rn[u] = rhs[row(cell) + vp];
-      an[u] = coef[cell * 6 + 0];
-      bn[u] = coef[cell * 6 + 1];
-      cn[u] = coef[cell * 6 + 2];
-    }
-#pragma unroll
-    for (int u = 0; u < kSweepChunk; ++u) {
-      const int i = base + u;
-      if (i < nodes) {
-        const double val = (rc[u] - v1 * (bc[u] * h1 + cc[u] * h2)) / (dnp + v1 * ac[u]);
-        h[row(c0 + i) + vp] = val;
-        h2 = h1;
-        h1 = val;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kSweepChunk; ++u) {
-      rc[u] = rn[u];
-      ac[u] = an[u];
-      bc[u] = bn[u];
-      cc[u] = cn[u];
-    }
-  }
-  // v1 < 0: specular reflection at the last node, march to the wall (nodes nodes-2 .. 0)
-  const int64_t last = c0 + nodes - 1;
-  double g1 = h1, g2 = 0.0;
-  h[row(last) + vm] = g1;
-#pragma unroll
-  for (int u = 0; u < kSweepChunk; ++u) {
-    const int i = nodes - 2 - u;
-    const int64_t cell = c0 + (i >= 0 ? i : 0);
-    rc[u] = rhs[row(cell) + vm];
-    ac[u] = coef[cell * 6 + 3];
-    bc[u] = coef[cell * 6 + 4];
-    cc[u] = coef[cell * 6 + 5];
-  }
-  for (int base = nodes - 2; base >= 0; base -= kSweepChunk) {
-#pragma unroll
-    for (int u = 0; u < kSweepChunk; ++u) {
-      const int i = base - kSweepChunk - u;
-      const int64_t cell = c0 + (i >= 0 ? i : 0);
-      rn[u] = rhs[row(cell) + vm];
-      an[u] = coef[cell * 6 + 3];
-      bn[u] = coef[cell * 6 + 4];
-      cn[u] = coef[cell * 6 + 5];
-    }
-#pragma unroll
-    for (int u = 0; u < kSweepChunk; ++u) {
-      const int i = base - u;
-      if (i >= 0) {
-        const double val = (rc[u] - v1 * (bc[u] * g1 + cc[u] * g2)) / (dnm + v1 * ac[u]);
-        h[row(c0 + i) + vm] = val;
-        g2 = g1;
-        g1 = val;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kSweepChunk; ++u) {
-      rc[u] = rn[u];
-      ac[u] = an[u];
-      bc[u] = bn[u];
-      cc[u] = cn[u];
-    }
-  }
+  out.put(0.0);
+  out.run(h1, h2, r_out, c_out, sh);
+  h2 = 0.0;
+  in.put(h1);
+  in.run(h1, h2, r_in, c_in, sh);
 }
 
-__global__ __launch_bounds__(256) void sweep1d_kernel(SweepArgs a) { sweep1d_block(a, blockIdx.x, blockIdx.y, blockIdx.z); }
+__global__ __launch_bounds__(kSweepNT) void sweep1d_kernel(SweepArgs a) {
+  sweep1d_block<kSweepNT, kSweepAhead>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+}
 
 // Calls f(v1, v2, v3, h) for every unknown of row `row` (n3 values): in 16-byte pairs for
 // rows of even length (the moment kernels are bound by their count of memory instructions).
@@ -1907,82 +1954,105 @@ __global__ __launch_bounds__(256) void moments_kernel(int n3, int nsp, double ms
 }
 
 // ------------------------------------------------------------------ diffusion (1-D)
-// One workgroup per case.  The march from the wall is a serial recurrence, so one
-// lane carries it; the per-node inputs (moments, source, stencil) are staged into LDS
-// by the whole workgroup in coalesced chunks and the outputs written back the same
-// way, so the march itself waits on LDS only.
+// One workgroup per case.  The march from the wall is a serial recurrence, so one lane
+// carries it, and nothing but it: the whole workgroup stages the nodes' equations into LDS
+// with the inverses of their diagonals, and takes the outputs and the flow-rate integrals
+// from the lane's values afterwards.  101 nodes: 9 us, and 26 with all of it on the lane.
 constexpr int kDiffChunk = 256;
 
 __device__ __forceinline__ void diffusion1d_case(const DiffusionArgs& a, int cs) {
-  __shared__ double in[8][kDiffChunk];    // Uh, qh, G1, source, ca, cb, cc, x
-  __shared__ double out[4][kDiffChunk];   // U, dU, q, U of the new iterate
+  __shared__ double in[9][kDiffChunk];    // Uh, qh, G1, x, and a y_i = s - b y_{i-1} - c y_{i-2}: s, b, c, a, 1/a
+  __shared__ double ys[kDiffChunk];       // y
+  __shared__ double prev[3];              // x, U3 and q3 of the node before the chunk
+  __shared__ double red[4 * 2];
   if (a.case_active && !a.case_active[cs]) return;   // uniform over the workgroup
   const int64_t c0 = a.node_off[cs];
   const int nodes = static_cast<int>(a.node_off[cs + 1] - c0);
   const double del = a.delta_case[cs];
   const bool pois = a.flow_case[cs] == 1;
   double y1 = 0.0, y2 = 0.0;
-  double Mr = 0.0, Qr = 0.0, Up = 0.0, qp = 0.0, xp = 0.0;
+  double flow[2] = {0.0, 0.0};            // M, Q integrals
   for (int base = 0; base < nodes; base += kDiffChunk) {
     const int cnt = min(kDiffChunk, nodes - base);
     for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
       const int64_t cell = c0 + base + t;
-      in[0][t] = a.mom[cell * 4 + 0];
+      const double Uh = a.mom[cell * 4 + 0], G1 = a.mom[cell * 4 + 2], x = a.x[cell];
+      in[0][t] = Uh;
       in[1][t] = a.mom[cell * 4 + 1];
-      in[2][t] = a.mom[cell * 4 + 2];
-      const double x = a.x[cell];
-      in[7][t] = x;
-      if (a.sis && base + t > 0) {
-        double A1 = 0.0;
-        if (a.amom) A1 = a.amom[cell * 4 + 0] + a.N * del * a.amom[cell * 4 + 1];
-        in[3][t] = A1 - (pois ? a.N * del * x : 0.0);
-        in[4][t] = a.coef[cell * 6 + 0];
-        in[5][t] = a.coef[cell * 6 + 1];
-        in[6][t] = a.coef[cell * 6 + 2];
+      in[2][t] = G1;
+      in[3][t] = x;
+      if (a.sis) {
+        double s = Uh + G1, b = 0.0, c = 0.0, ca = 1.0;
+        if (base + t > 0) {
+          double A1 = 0.0;
+          if (a.amom) A1 = a.amom[cell * 4 + 0] + a.N * del * a.amom[cell * 4 + 1];
+          s = A1 - (pois ? a.N * del * x : 0.0);
+          ca = a.coef[cell * 6 + 0];
+          b = a.coef[cell * 6 + 1];
+          c = a.coef[cell * 6 + 2];
+        }
+        in[4][t] = s;
+        in[5][t] = b;
+        in[6][t] = c;
+        in[7][t] = ca;
+        in[8][t] = 1.0 / ca;
       }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && a.sis) {
+#pragma unroll 8
       for (int t = 0; t < cnt; ++t) {
-        const int i = base + t;
-        const double Uh = in[0][t], qh = in[1][t], G1 = in[2][t];
-        double dU = 0.0, Usol = Uh;
-        if (a.sis) {
-          const double y = i == 0 ? Uh + G1 : (in[3][t] - in[5][t] * y1 - in[6][t] * y2) / in[4][t];
-          y2 = y1;
-          y1 = y;
-          Usol = y - G1;
-          dU = Usol - Uh;
-        }
-        // moments of h^{k+1} = h^{k+1/2} + dU 2 v3 f_eq (eq. guided)
-        const double Un = Uh + dU * a.cU, qn = qh + dU * a.cq;
-        out[0][t] = Usol;
-        out[1][t] = dU;
-        out[2][t] = qn;
-        out[3][t] = Un;
-        const double x = in[7][t];
-        if (i > 0) {
-          Mr += 0.5 * (Un + Up) * (x - xp);
-          Qr += 0.5 * (qn + qp) * (x - xp);
-        }
-        Up = Un;
-        qp = qn;
-        xp = x;
+        const double y = div_known((in[4][t] - in[6][t] * y2) - in[5][t] * y1, in[7][t], in[8][t]);
+        y2 = y1;
+        y1 = y;
+        ys[t] = y;
       }
     }
     __syncthreads();
+    // moments of h^{k+1} = h^{k+1/2} + dU 2 v3 f_eq (eq. guided)
+    auto moved = [&](int t, double& U, double& dU, double& Un, double& qn) {
+      const double Uh = in[0][t];
+      U = a.sis ? ys[t] - in[2][t] : Uh;
+      dU = U - Uh;
+      Un = Uh + dU * a.cU;
+      qn = in[1][t] + dU * a.cq;
+    };
     for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
       const int64_t cell = c0 + base + t;
-      if (a.U) a.U[cell] = out[0][t];
-      if (a.dU) a.dU[cell] = out[1][t];
-      if (a.qfield) a.qfield[cell] = out[2][t];
-      if (a.ufield) a.ufield[cell] = out[3][t];
+      double U, dU, Un, qn;
+      moved(t, U, dU, Un, qn);
+      if (a.U) a.U[cell] = U;
+      if (a.dU) a.dU[cell] = dU;
+      if (a.qfield) a.qfield[cell] = qn;
+      if (a.ufield) a.ufield[cell] = Un;
+      if (base + t > 0) {
+        double xp, Up, qp;
+        if (t > 0) {
+          double u_, d_;
+          moved(t - 1, u_, d_, Up, qp);
+          xp = in[3][t - 1];
+        } else {
+          xp = prev[0];
+          Up = prev[1];
+          qp = prev[2];
+        }
+        flow[0] += 0.5 * (Un + Up) * (in[3][t] - xp);
+        flow[1] += 0.5 * (qn + qp) * (in[3][t] - xp);
+      }
     }
-    // the next chunk's staging writes only in[]; the march that rewrites out[] starts
-    // after the next barrier, which every lane reaches after its stores above
+    if (base + cnt < nodes) {
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        double u_, d_;
+        moved(cnt - 1, u_, d_, prev[1], prev[2]);
+        prev[0] = in[3][cnt - 1];
+      }
+      __syncthreads();
+    }
   }
+  block_sum<2>(flow, red);
   if (threadIdx.x == 0 && a.state) {
-    const double M = 2.0 * Mr, Q = 2.0 * Qr;
+    const double M = 2.0 * flow[0], Q = 2.0 * flow[1];
     double* st = a.state + cs * 4;
     const double dM = fabs(M - st[0]) / fmax(fabs(M), 1e-300);
     const double dQ = fabs(Q - st[1]) / fmax(fabs(Q), 1e-300);
@@ -2019,13 +2089,14 @@ __global__ __launch_bounds__(kDiffChunk) void diffusion1d_kernel(DiffusionArgs a
 // stress) and A (total stress minus B's), integrated once from the symmetry
 // plane and marched from the wall; rows are (cell, species) with species A
 // first.  mom[row][4] = {int v3 h, q, G1, P13}; U is per unit molar fraction.
-// The two species march independently (lane s carries species s); inputs and outputs
-// are staged through LDS as in diffusion1d_kernel.
+// The two species march independently (lane s carries species s); staging, outputs and
+// integrals as in diffusion1d_case.
 __device__ __forceinline__ void diffusion1d_mix_case(const DiffusionArgs& a, int cs) {
-  __shared__ double in_s[2][4][kDiffChunk];   // per species: Uh, qh, G, source
-  __shared__ double in_c[4][kDiffChunk];      // per node: ca, cb, cc, x
-  __shared__ double out[2][4][kDiffChunk];    // per species: U, dU, q, U of the new iterate
-  __shared__ double red[2][2];                // per species: M, Q integrals
+  __shared__ double in_s[2][4][kDiffChunk];   // per species: Uh, qh, G, s
+  __shared__ double in_c[5][kDiffChunk];      // per node: x, and b, c, a, 1/a (as in diffusion1d_case)
+  __shared__ double ys[2][kDiffChunk];        // per species: y
+  __shared__ double prev[5];                  // x, then U3 and q3 per species, of the node before the chunk
+  __shared__ double red[4 * 4];
   if (a.case_active && !a.case_active[cs]) return;   // uniform over the workgroup
   const int64_t c0 = a.node_off[cs];
   const int nodes = static_cast<int>(a.node_off[cs + 1] - c0);
@@ -2033,83 +2104,100 @@ __device__ __forceinline__ void diffusion1d_mix_case(const DiffusionArgs& a, int
   const double pois = a.flow_case[cs] == 1 ? 1.0 : 0.0;
   const int sp = threadIdx.x;                 // marching lane: species sp (lanes 0, 1)
   double y1 = 0.0, y2 = 0.0;
-  double Mr = 0.0, Qr = 0.0, Up = 0.0, qp = 0.0, xp = 0.0;
+  double flow[4] = {0.0, 0.0, 0.0, 0.0};      // (M, Q) integrals per species
   for (int base = 0; base < nodes; base += kDiffChunk) {
     const int cnt = min(kDiffChunk, nodes - base);
     for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
       const int64_t cell = c0 + base + t;
       const double x = a.x[cell];
       const double PB = a.mom[(cell * 2 + 1) * 4 + 3];
-      in_c[3][t] = x;
-      if (a.sis && base + t > 0) {
-        in_c[0][t] = a.coef[cell * 6 + 0];
-        in_c[1][t] = a.coef[cell * 6 + 1];
-        in_c[2][t] = a.coef[cell * 6 + 2];
+      const bool inner = base + t > 0;
+      in_c[0][t] = x;
+      if (a.sis) {
+        const double ca = inner ? a.coef[cell * 6 + 0] : 1.0;
+        in_c[1][t] = inner ? a.coef[cell * 6 + 1] : 0.0;
+        in_c[2][t] = inner ? a.coef[cell * 6 + 2] : 0.0;
+        in_c[3][t] = ca;
+        in_c[4][t] = 1.0 / ca;
       }
+#pragma unroll
       for (int s = 0; s < 2; ++s) {
         const int64_t r = cell * 2 + s;
-        in_s[s][0][t] = a.mom[r * 4 + 0] / a.chi[s];
+        const double Uh = a.mom[r * 4 + 0] / a.chi[s], G = a.mom[r * 4 + 2];
+        in_s[s][0][t] = Uh;
         in_s[s][1][t] = a.mom[r * 4 + 1];
-        in_s[s][2][t] = a.mom[r * 4 + 2];
-        if (a.sis && base + t > 0) {
-          const double Nd = a.Ns[s] * del;
-          double A = 0.0;
-          if (a.amom) A = a.amom[r * 4 + 0] + Nd * a.amom[r * 4 + 1];
-          in_s[s][3][t] = s == 1 ? A - Nd * PB / a.mass_ratio[1] : A - Nd * (pois * x - PB);
-        }
-      }
-    }
-    __syncthreads();
-    if (sp < 2) {
-      const double chi = a.chi[sp];
-      for (int t = 0; t < cnt; ++t) {
-        const int i = base + t;
-        const double Uh = in_s[sp][0][t], qh = in_s[sp][1][t], G = in_s[sp][2][t];
-        double dU = 0.0, Usol = Uh;
+        in_s[s][2][t] = G;
         if (a.sis) {
-          const double y = i == 0 ? chi * Uh + G
-                                  : (in_s[sp][3][t] - in_c[1][t] * y1 - in_c[2][t] * y2) / in_c[0][t];
-          y2 = y1;
-          y1 = y;
-          Usol = (y - G) / chi;
-          dU = Usol - Uh;
+          double q = a.chi[s] * Uh + G;
+          if (inner) {
+            const double Nd = a.Ns[s] * del;
+            double A = 0.0;
+            if (a.amom) A = a.amom[r * 4 + 0] + Nd * a.amom[r * 4 + 1];
+            q = s == 1 ? A - Nd * PB / a.mass_ratio[1] : A - Nd * (pois * x - PB);
+          }
+          in_s[s][3][t] = q;
         }
-        const double Un = Uh + dU * a.cUs[sp], qn = qh + dU * a.cqs[sp];
-        out[sp][0][t] = Usol;
-        out[sp][1][t] = dU;
-        out[sp][2][t] = qn;
-        out[sp][3][t] = Un;
-        const double x = in_c[3][t];
-        if (i > 0) {
-          Mr += 0.5 * (Un + Up) * (x - xp);
-          Qr += 0.5 * (qn + qp) * (x - xp);
-        }
-        Up = Un;
-        qp = qn;
-        xp = x;
       }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 2 * cnt; e += blockDim.x) {
-      const int t = e >> 1, s = e & 1;
-      const int64_t r = (c0 + base + t) * 2 + s;
-      if (a.U) a.U[r] = out[s][0][t];
-      if (a.dU) a.dU[r] = out[s][1][t];
-      if (a.qfield) a.qfield[r] = out[s][2][t];
-      if (a.ufield) a.ufield[r] = out[s][3][t];
+    if (sp < 2 && a.sis) {
+#pragma unroll 8
+      for (int t = 0; t < cnt; ++t) {
+        const double y = div_known((in_s[sp][3][t] - in_c[2][t] * y2) - in_c[1][t] * y1, in_c[3][t], in_c[4][t]);
+        y2 = y1;
+        y1 = y;
+        ys[sp][t] = y;
+      }
+    }
+    __syncthreads();
+    auto moved = [&](int s, int t, double& U, double& dU, double& Un, double& qn) {
+      const double Uh = in_s[s][0][t];
+      U = a.sis ? (ys[s][t] - in_s[s][2][t]) / a.chi[s] : Uh;
+      dU = U - Uh;
+      Un = Uh + dU * a.cUs[s];
+      qn = in_s[s][1][t] + dU * a.cqs[s];
+    };
+    for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
+      const double dx = base + t == 0 ? 0.0 : in_c[0][t] - (t > 0 ? in_c[0][t - 1] : prev[0]);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int64_t r = (c0 + base + t) * 2 + s;
+        double U, dU, Un, qn;
+        moved(s, t, U, dU, Un, qn);
+        if (a.U) a.U[r] = U;
+        if (a.dU) a.dU[r] = dU;
+        if (a.qfield) a.qfield[r] = qn;
+        if (a.ufield) a.ufield[r] = Un;
+        if (base + t > 0) {
+          double Up, qp, u_, d_;
+          if (t > 0) {
+            moved(s, t - 1, u_, d_, Up, qp);
+          } else {
+            Up = prev[1 + 2 * s];
+            qp = prev[2 + 2 * s];
+          }
+          flow[2 * s] += 0.5 * (Un + Up) * dx;
+          flow[2 * s + 1] += 0.5 * (qn + qp) * dx;
+        }
+      }
+    }
+    if (base + cnt < nodes) {
+      __syncthreads();
+      if (sp < 2) {
+        double u_, d_;
+        moved(sp, cnt - 1, u_, d_, prev[1 + 2 * sp], prev[2 + 2 * sp]);
+        if (sp == 0) prev[0] = in_c[0][cnt - 1];
+      }
+      __syncthreads();
     }
   }
-  if (sp < 2) {
-    red[sp][0] = Mr;
-    red[sp][1] = Qr;
-  }
-  __syncthreads();
+  block_sum<4>(flow, red);
   if (threadIdx.x == 0 && a.state) {
     double* st = a.state + cs * 6;  // M_A, M_B, Q_A, Q_B, residual, iterations
     double res = 0.0;
     bool bad = false;
     for (int s = 0; s < 2; ++s) {
-      const double M = 2.0 * a.flow_factor * red[s][0], Q = 2.0 * a.flow_factor * red[s][1];
+      const double M = 2.0 * a.flow_factor * flow[2 * s], Q = 2.0 * a.flow_factor * flow[2 * s + 1];
       res = fmax(res, fmax(fabs(M - st[s]) / fmax(fabs(M), 1e-300), fabs(Q - st[2 + s]) / fmax(fabs(Q), 1e-300)));
       bad = bad || M != M || Q != Q;
       st[s] = M;
@@ -3139,77 +3227,161 @@ __global__ void polar_op2_kernel(int nv, int nm, const double* __restrict__ vnod
 // One workgroup per (case, group of kTubeV (v_r, v_z) pairs).  Inward molecules
 // (th > pi/2) are swept from the wall to the centre, then outward ones from the
 // centre to the wall; in both passes a node depends on its two r-upwind nodes and
-// its two th-upwind (larger th) nodes, so the anti-diagonals of (r, th) are
-// processed in order with a workgroup barrier between them.
+// its two th-upwind (larger th) nodes, so the anti-diagonals of (r, th) are processed
+// in order.  What bounds it is the latency of one diagonal, there being little work in
+// one: a thread keeps to one th column, so that its r-upwind values stay in registers,
+// hands its value to the next columns through LDS (the one barrier of a diagonal), loads
+// what it needs kTubeAhead diagonals before, and has all of the next node's equation but that
+// value, and its inverted diagonal, by the time the value arrives.  150 nodes, 20 columns:
+// 86 us, of which the instructions of a diagonal (70 of four cycles, one wave a SIMD) are
+// about half and the waits for LDS and the barrier a third; 394 us with the values passed on
+// through global memory and the division after them.
+// Two more columns in front hand on the values that the first two depend on: none where the
+// columns begin at th = pi, else those of the columns before, read from h (the outward pass
+// goes on from the inward one, and more columns than kTubeCols are swept in strips).  The
+// coefficients of a node are loaded once for all columns and stay in LDS while they pass it.
 constexpr int kTubeV = 8;
-constexpr int kTubeThreads = 256;
+constexpr int kTubeCols = 62;
+constexpr int kTubeAhead = 24;   // even: LDS holds this diagonal and the one before
+constexpr int kTubeNodes = 128;  // >= kTubeCols + 2 + 2 kTubeAhead
 
-__global__ __launch_bounds__(kTubeThreads) void sweep_tube_kernel(TubeSweepArgs a) {
+struct TubeLds {
+  double ring[2][(kTubeCols + 4) * kTubeV];
+  alignas(16) double node[kTubeNodes][4];   // of node j at j mod kTubeNodes: three coefficients, r
+};
+
+template <bool OUT>
+__device__ __forceinline__ void tube_march(const TubeSweepArgs& a, TubeLds& lds, int64_t n0, int n, double del, int q,
+                                           bool valid, int kk0) {
+  const int nth = a.n_th, half = nth / 2, nvz = a.n_vz, nv = a.nv;
+  const int ivr = q / nvz, iz = q % nvz;
+  const int t = threadIdx.x, kl = t / kTubeV, cols = min(kTubeCols, half - kk0);
+  const bool hand = kl < 2;
+  // column kk of the pass is th node k; columns -1 and -2 of the outward pass are inward ones
+  const int top = (OUT ? half : nth) - 1;
+  const int kk = min(kk0 + kl - 2, half - 1), k = min(top - kk, nth - 1);
+  const bool none = top - kk > nth - 1;   // beyond th = pi
+  const int count = OUT ? n : n - 1;
+  const int diagonals = count + cols + 1;
+  const unsigned stored = valid && !hand && kl < cols + 2 ? count : 0;   // nodes of this thread
+  const double vr = a.vr[ivr], S = vr * a.sth[k] / (2.0 * a.dth), c1 = vr * a.cth[k];
+  auto vix = [&](int kx) { return (ivr * nth + kx) * nvz + iz; };
+  const int v = vix(k);
+  const double dn = del * a.nu[v];
+  // the last column has no th-upwind term, the one before it uses the last twice (4 h - h)
+  const bool last = k == nth - 1, second = k == nth - 2;
+  const double s4 = last ? 0.0 : (second ? 3.0 : 4.0) * S, s2 = last || second ? 0.0 : S, s3 = last ? 0.0 : 3.0 * S;
+  // what the thread loads at its first node, and the bytes to the next: its right side; the
+  // values handed on, 0 (h at the wall, inward) beyond th = pi
+  double* h = a.h + n0 * nv;
+  const int64_t first = OUT ? 0 : n - 2, step = (OUT ? 8 : -8) * static_cast<int64_t>(nv);
+  const char* in = reinterpret_cast<const char*>((hand ? h : a.rhs + n0 * nv) + (none ? n - 1 : first) * nv + v);
+  const int64_t in_step = none ? 0 : step;
+  char* out = reinterpret_cast<char*>(h + first * nv + v);
+  auto load = [&](int d) {   // at diagonal d: the first node until it has come, the last one from then on
+    const double x = *reinterpret_cast<const double*>(in);
+    in += static_cast<unsigned>(d - kl) < static_cast<unsigned>(count - 1) ? in_step : 0;
+    return x;
+  };
+  // coefficients of kTubeAhead nodes from node j on
+  constexpr int kPer = 4 * kTubeAhead / (4 * kTubeV);   // of a thread of the smallest workgroup
+  const double* coef = (OUT ? a.cout : a.cin) + n0 * 3;
+  const double* radius = a.r + n0;
+  auto load_coef = [&](int j, double (&c)[kPer]) {
+#pragma unroll
+    for (int p = 0; p < kPer; ++p) {
+      const int e = t + p * static_cast<int>(blockDim.x), jn = min(j + e / 4, count - 1), i = OUT ? jn : n - 2 - jn;
+      c[p] = 0.0;
+      if (e < 4 * kTubeAhead) c[p] = (e & 3) == 3 ? radius[i] : coef[i * 3 + (e & 3)];
+    }
+  };
+  auto keep_coef = [&](int j, const double (&c)[kPer]) {
+#pragma unroll
+    for (int p = 0; p < kPer; ++p) {
+      const int e = t + p * static_cast<int>(blockDim.x);
+      if (e < 4 * kTubeAhead) lds.node[(j + e / 4) % kTubeNodes][e & 3] = c[p];
+    }
+  };
+  double buf[kTubeAhead], next[kPer];
+  load_coef(0, next);
+#pragma unroll
+  for (int u = 0; u < kTubeAhead; ++u) buf[u] = load(u);
+  double y1 = 0.0, y2 = 0.0;
+  if (OUT) {   // ghosts across the centre hold h(r, pi - th)
+    y1 = h[vix(nth - 1 - k)];
+    y2 = h[nv + vix(nth - 1 - k)];
+  }
+  keep_coef(0, next);
+  load_coef(kTubeAhead, next);
+  keep_coef(kTubeAhead, next);
+  __syncthreads();
+  // the node's equation times r: D h = base + s4 h1, base = r (rhs - c1 (cb y1 + cc y2)) - s2 h2; the first nodes
+  // of the computed columns come at diagonal 2 and later, so what is set up here (and from
+  // slots not yet written) for diagonal 0 is not used
+  double D = 1.0, inv = 1.0, base = 0.0, handed = buf[0];
+  auto slot = [&](int d) { return lds.node[static_cast<unsigned>(d - kl) % kTubeNodes]; };
+  double ca, cb, cc, cr;
+  auto read_coef = [&](int d) {
+    const double* c = slot(d);
+    ca = c[0];
+    cb = c[1];
+    cc = c[2];
+    cr = c[3];
+  };
+  read_coef(1);
+  for (int d0 = 0; d0 < diagonals; d0 += kTubeAhead) {
+    load_coef(d0 + 2 * kTubeAhead, next);
+#pragma unroll
+    for (int u = 0; u < kTubeAhead; ++u) {
+      const int d = d0 + u, j = d - kl;
+      const double* before = lds.ring[(u + 1) % 2] + t;   // diagonal d - 1, two columns of padding in front
+      const double near = before[kTubeV], far = before[0];
+      __builtin_amdgcn_sched_barrier(0);   // the reads first
+      // the next node of this column but for its neighbour's value: the division in the shadow of
+      // the reads
+      const double next_D = __builtin_fma(cr, __builtin_fma(c1, ca, dn), s3);
+      double next_inv = 1.0 / next_D;
+      asm volatile("" : "+v"(next_inv));
+      double val = div_known(__builtin_fma(s4, near, base), D, inv);
+      val = hand ? handed : val;
+      lds.ring[u % 2][t + 2 * kTubeV] = val;
+      y2 = j >= 0 ? y1 : y2;
+      y1 = j >= 0 ? val : y1;
+      const double x = buf[(u + 1) % kTubeAhead];
+      D = next_D;
+      inv = next_inv;
+      handed = x;
+      base = __builtin_fma(-(cr * c1), cb * y1 + cc * y2, __builtin_fma(-s2, far, cr * x));
+      read_coef(d + 2);
+      buf[u] = load(d + kTubeAhead);
+      if (u == kTubeAhead - 1) keep_coef(d0 + 2 * kTubeAhead, next);
+      if (static_cast<unsigned>(j) < stored) {
+        *reinterpret_cast<double*>(out) = val;
+        out += step;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+__global__ __launch_bounds__(kTubeV * (kTubeCols + 2)) void sweep_tube_kernel(TubeSweepArgs a) {
+  __shared__ TubeLds lds;
   const int cs = blockIdx.y;
   if (a.case_active && !a.case_active[cs]) return;
-  const int nth = a.n_th, half = nth / 2, nvz = a.n_vz, nv = a.nv;
-  const int pairs = a.n_vr * nvz;
+  const int nth = a.n_th, half = nth / 2, nvz = a.n_vz;
   const int tq = blockIdx.x * kTubeV + threadIdx.x % kTubeV;
-  const bool valid = tq < pairs;
+  const bool valid = tq < a.n_vr * nvz;
   const int q = valid ? tq : 0;
-  const int ivr = q / nvz, iz = q % nvz;
-  const int slot = threadIdx.x / kTubeV, slots = kTubeThreads / kTubeV;
   const int64_t n0 = a.node_off[cs];
   const int n = static_cast<int>(a.node_off[cs + 1] - n0);
   const double del = a.delta_case[cs];
-  const double vr = a.vr[ivr];
-  const double tc = 1.0 / (2.0 * a.dth);
-  auto vix = [&](int k) { return (ivr * nth + k) * nvz + iz; };
   // wall node, inward velocities: molecules leaving a diffuse wall carry h = 0
-  for (int kk = slot; kk < half; kk += slots)
-    if (valid) a.h[(n0 + n - 1) * nv + vix(half + kk)] = 0.0;
+  for (int k = half + threadIdx.x / kTubeV; k < nth; k += blockDim.x / kTubeV)
+    if (valid) a.h[(n0 + n - 1) * a.nv + ((q / nvz) * nth + k) * nvz + q % nvz] = 0.0;
   __syncthreads();
-  // inward pass: ii = n - 2 - i, kk = n_th - 1 - k
-  for (int d = 0; d <= (n - 2) + (half - 1); ++d) {
-    const int lo = max(0, d - (n - 2)), hi = min(d, half - 1);
-    for (int c0 = lo; c0 <= hi; c0 += slots) {
-      const int kk = c0 + slot;
-      if (valid && kk <= hi) {
-        const int i = n - 2 - (d - kk), k = nth - 1 - kk;
-        const int64_t node = n0 + i;
-        const int v = vix(k);
-        const double c1 = vr * a.cth[k], ct = vr * a.sth[k] / a.r[node];
-        const double* cf = a.cin + node * 3;
-        double up = cf[1] * a.h[(node + 1) * nv + v];
-        if (i < n - 2) up += cf[2] * a.h[(node + 2) * nv + v];
-        double diag = del * a.nu[v] + c1 * cf[0];
-        double src = a.rhs[node * nv + v] - c1 * up;
-        if (k < nth - 1) {
-          const int k2 = min(k + 2, nth - 1);
-          diag += ct * 3.0 * tc;
-          src += ct * (4.0 * a.h[node * nv + vix(k + 1)] - a.h[node * nv + vix(k2)]) * tc;
-        }
-        a.h[node * nv + v] = src / diag;
-      }
-    }
-    __syncthreads();
-  }
-  // outward pass: kk = half - 1 - k; ghosts across the centre hold h(r, pi - th)
-  for (int d = 0; d <= (n - 1) + (half - 1); ++d) {
-    const int lo = max(0, d - (n - 1)), hi = min(d, half - 1);
-    for (int c0 = lo; c0 <= hi; c0 += slots) {
-      const int kk = c0 + slot;
-      if (valid && kk <= hi) {
-        const int i = d - kk, k = half - 1 - kk, km = nth - 1 - k;
-        const int64_t node = n0 + i;
-        const int v = vix(k);
-        const double c1 = vr * a.cth[k], ct = vr * a.sth[k] / a.r[node];
-        const double* cf = a.cout + node * 3;
-        const double y1 = i >= 1 ? a.h[(node - 1) * nv + v] : a.h[n0 * nv + vix(km)];
-        const double y2 = i >= 2 ? a.h[(node - 2) * nv + v] : a.h[(n0 + 1 - i) * nv + vix(km)];
-        const double diag = del * a.nu[v] + c1 * cf[0] + ct * 3.0 * tc;
-        const double src = a.rhs[node * nv + v] - c1 * (cf[1] * y1 + cf[2] * y2) +
-                           ct * (4.0 * a.h[node * nv + vix(k + 1)] - a.h[node * nv + vix(k + 2)]) * tc;
-        a.h[node * nv + v] = src / diag;
-      }
-    }
-    __syncthreads();
-  }
+  for (int kk0 = 0; kk0 < half; kk0 += kTubeCols) tube_march<false>(a, lds, n0, n, del, q, valid, kk0);
+  __syncthreads();
+  for (int kk0 = 0; kk0 < half; kk0 += kTubeCols) tube_march<true>(a, lds, n0, n, del, q, valid, kk0);
 }
 
 __global__ __launch_bounds__(256) void moments_tube_kernel(int nv, const double* __restrict__ vnode,
@@ -3240,12 +3412,12 @@ __global__ __launch_bounds__(256) void moments_tube_kernel(int nv, const double*
 }
 
 // Velocity equation of the tube, one workgroup per case: a march over the radial nodes
-// from the wall inwards (one lane; inputs and outputs staged through LDS in coalesced
-// chunks as in diffusion1d_kernel), outputs, flow rates 2 int_0^1 f r dr and the
-// convergence test.
+// from the wall inwards (staged, carried and finished as in diffusion1d_case), outputs,
+// flow rates 2 int_0^1 f r dr and the convergence test.
 __global__ __launch_bounds__(kDiffChunk) void diffusion_tube_kernel(TubeDiffArgs a) {
-  __shared__ double in[8][kDiffChunk];    // U3, q3, G, source, c0, c1, c2, weight
-  __shared__ double out[4][kDiffChunk];   // U, dU, U and q of the new iterate
+  __shared__ double in[5][kDiffChunk];    // a y_i = s - b y_{i+1} - c y_{i+2}: s, b, c, a, 1/a
+  __shared__ double ys[kDiffChunk];       // y
+  __shared__ double red[4 * 2];
   const int cs = blockIdx.x;
   if (a.case_active && !a.case_active[cs]) return;   // uniform over the workgroup
   const int64_t n0 = a.node_off[cs];
@@ -3253,64 +3425,61 @@ __global__ __launch_bounds__(kDiffChunk) void diffusion_tube_kernel(TubeDiffArgs
   const double del = a.delta_case[cs];
   const bool pois = a.flow_case[cs] == 1;
   const double Nd = a.N * del;
-  double y1 = 0.0, y2 = 0.0, M = 0.0, Q = 0.0;
+  double y1 = 0.0, y2 = 0.0;
+  double flow[2] = {0.0, 0.0};            // M, Q
   for (int end = n; end > 0; end -= kDiffChunk) {
     const int lo = max(0, end - kDiffChunk), cnt = end - lo;
-    for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
-      const int i = lo + t;
-      const int64_t node = n0 + i;
+    const int i = lo + threadIdx.x;       // one node a thread
+    const int64_t node = n0 + i;
+    const bool mine = static_cast<int>(threadIdx.x) < cnt;
+    double U3 = 0.0, q3 = 0.0, G = 0.0;
+    if (mine) {
       const double* m = a.mom + node * 8;
-      in[0][t] = m[0];
-      in[1][t] = m[1];
-      in[2][t] = m[2];
-      in[7][t] = a.tw[node];
-      if (a.sis && i < n - 1) {
-        double A = 0.0;
-        if (a.amom) A = a.amom[node * 4 + 0] + Nd * a.amom[node * 4 + 1];
-        const double r = a.r[node];
-        in[3][t] = A - m[3] / r - (pois ? Nd * r / 2.0 : 0.0);
-        in[4][t] = a.cin[node * 3 + 0];
-        in[5][t] = a.cin[node * 3 + 1];
-        in[6][t] = a.cin[node * 3 + 2];
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int t = cnt - 1; t >= 0; --t) {
-        const int i = lo + t;
-        const double U3 = in[0][t], q3 = in[1][t], G = in[2][t];
-        double dU = 0.0, U = U3;
-        if (a.sis) {
-          double y;
-          if (i == n - 1)
-            y = U3 + G;
-          else if (i == n - 2)
-            y = (in[3][t] - in[5][t] * y1) / in[4][t];
-          else
-            y = (in[3][t] - in[5][t] * y1 - in[6][t] * y2) / in[4][t];
-          y2 = y1;
-          y1 = y;
-          U = y - G;
-          dU = U - U3;
+      U3 = m[0];
+      q3 = m[1];
+      G = m[2];
+      if (a.sis) {
+        double s = U3 + G, b = 0.0, c = 0.0, ca = 1.0;
+        if (i < n - 1) {
+          double A = 0.0;
+          if (a.amom) A = a.amom[node * 4 + 0] + Nd * a.amom[node * 4 + 1];
+          const double r = a.r[node];
+          s = A - m[3] / r - (pois ? Nd * r / 2.0 : 0.0);
+          ca = a.cin[node * 3 + 0];
+          b = a.cin[node * 3 + 1];
+          if (i < n - 2) c = a.cin[node * 3 + 2];
         }
-        const double Un = U3 + dU * a.cU, qn = q3 + dU * a.cq;
-        out[0][t] = U;
-        out[1][t] = dU;
-        out[2][t] = Un;
-        out[3][t] = qn;
-        M += in[7][t] * Un;
-        Q += in[7][t] * qn;
+        in[0][threadIdx.x] = s;
+        in[1][threadIdx.x] = b;
+        in[2][threadIdx.x] = c;
+        in[3][threadIdx.x] = ca;
+        in[4][threadIdx.x] = 1.0 / ca;
       }
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
-      const int64_t node = n0 + lo + t;
-      if (a.U) a.U[node] = out[0][t];
-      if (a.dU) a.dU[node] = out[1][t];
-      if (a.ufield) a.ufield[node] = out[2][t];
-      if (a.qfield) a.qfield[node] = out[3][t];
+    if (threadIdx.x == 0 && a.sis) {
+#pragma unroll 8
+      for (int t = cnt - 1; t >= 0; --t) {
+        const double y = div_known((in[0][t] - in[2][t] * y2) - in[1][t] * y1, in[3][t], in[4][t]);
+        y2 = y1;
+        y1 = y;
+        ys[t] = y;
+      }
+    }
+    __syncthreads();
+    if (mine) {
+      const double U = a.sis ? ys[threadIdx.x] - G : U3;
+      const double dU = U - U3, Un = U3 + dU * a.cU, qn = q3 + dU * a.cq;
+      if (a.U) a.U[node] = U;
+      if (a.dU) a.dU[node] = dU;
+      if (a.ufield) a.ufield[node] = Un;
+      if (a.qfield) a.qfield[node] = qn;
+      flow[0] += a.tw[node] * Un;
+      flow[1] += a.tw[node] * qn;
     }
   }
+  block_sum<2>(flow, red);
+  const double M = flow[0], Q = flow[1];
   if (threadIdx.x == 0 && a.state) {
     double* st = a.state + cs * 4;
     const double dM = fabs(M - st[0]) / fmax(fabs(M), 1e-300);
@@ -3371,7 +3540,7 @@ __device__ inline void grid_barrier(unsigned* bar, unsigned& gen) {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void sis1d_persistent_kernel(Persist1DArgs a) {
+__global__ __launch_bounds__(256, 2) void sis1d_persistent_kernel(Persist1DArgs a) {
   __shared__ int32_t case_flag;
   unsigned gen = 0;
   const int G = gridDim.x;
@@ -3396,7 +3565,7 @@ __global__ __launch_bounds__(256) void sis1d_persistent_kernel(Persist1DArgs a) 
       __syncthreads();
     }
     grid_barrier(a.bar, gen);
-    for (int t = blockIdx.x; t < n_sweep; t += G) sweep1d_block(a.sw, t % nbx, t / nbx, 0);
+    for (int t = blockIdx.x; t < n_sweep; t += G) sweep1d_block<256, 8>(a.sw, t % nbx, t / nbx, 0);
     grid_barrier(a.bar, gen);
     for (int64_t c = blockIdx.x; c < a.n_cells; c += G) {
       moments_row(a.sw.n3, 1, 1.0, 1.0, a.vtab, a.sw.h, a.w, a.mom, c);
@@ -3676,8 +3845,8 @@ hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
 
 hipError_t launch_sweep1d(const SweepArgs& a, hipStream_t s) {
   const int half = a.n3 / 2;
-  dim3 grid((half + 255) / 256, a.n_cases, a.nsp);
-  hipLaunchKernelGGL(sweep1d_kernel, grid, dim3(256), 0, s, a);
+  dim3 grid((half + kSweepNT - 1) / kSweepNT, a.n_cases, a.nsp);
+  hipLaunchKernelGGL(sweep1d_kernel, grid, dim3(kSweepNT), 0, s, a);
   return hipGetLastError();
 }
 
@@ -3856,7 +4025,8 @@ hipError_t launch_sweep_tube(const TubeSweepArgs& a, hipStream_t s) {
   if (a.max_nodes < 3) return hipErrorInvalidValue;
   const int pairs = a.n_vr * a.n_vz;
   dim3 grid((pairs + kTubeV - 1) / kTubeV, a.n_cases);
-  hipLaunchKernelGGL(sweep_tube_kernel, grid, dim3(kTubeThreads), 0, s, a);
+  const int cols = std::min(a.n_th / 2, kTubeCols);
+  hipLaunchKernelGGL(sweep_tube_kernel, grid, dim3(kTubeV * (cols + 2)), 0, s, a);
   return hipGetLastError();
 }
 
