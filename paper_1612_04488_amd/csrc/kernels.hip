@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -2717,6 +2718,313 @@ __global__ __launch_bounds__(64 * kRowWaves) void sweep2d_rows_kernel(
   }
 }
 
+// The same for few cases.  What bounds the form above there is the instructions of a cell (about
+// 80, most of the FP64 ones of four cycles) on the few compute units that it reaches: a case has
+// few quadruples (1728 at 24^3), and one workgroup of 16 waves carries 64 of them through all the
+// cells.  Here a wave takes 16 quadruples by 16 columns: lane 16 g + i carries quadruple i
+// through the four columns of group g, one row behind group g - 1, and a workgroup has a quarter
+// of the quadruples and of the waves.  One 64 x 64 duct at 24^3 (27 workgroups before, 108
+// now): 552 -> 289 us, two of 48 x 47: 370 -> 212.  What is left is latency: one wave a SIMD,
+// 280 instructions a step of four cells and six rounds of LDS, 2400 cycles.  The coefficients
+// that a wave reads from LDS serve 16 quadruples here and 64 above, so where the workgroups
+// above fill the chip that form is the faster one: six ducts 800 against 915 us, two periodic
+// 128 x 128 cells (a workgroup a quadrant) 600 against 820.
+//
+// A workgroup holds W <= 8 waves, side by side along axis 2, of one case and species, and sweeps
+// the four quadrants in the same order (one workgroup per quadrant where no reference is a
+// mirror ghost: then the quadrants do not read each other).  Within a quadrant the cells are
+// taken in the sweep's orientation (row r, column c counted from the upwind corner).  At step s
+// group g is at row s - g of its columns.  The two values left of a group come from the group
+// before through LDS (`carry`, by step parity): from its own wave's step before, or, for the
+// first group, from the last group of wave w - 1, handed on by two counters per wave (rows
+// published, steps whose value has been read) instead of a workgroup barrier.  The two rows
+// above are the lane's registers; only references that leave the grid are read from h: those
+// of rows 0 and 1 (axis 1) when the quadrant starts, those of columns 0 and 1 (axis 2, first
+// group of the first wave) with the right sides.  A row's stencil records and row offsets,
+// uniform over the quadruples, are loaded by the wave, 16 bytes a lane, six rows ahead, put
+// into a ring of eight LDS slots four rows ahead and read from there; the right sides are
+// loaded two rows ahead into registers that alternate between two sets (the loop is unrolled
+// by two), so that no register copy waits for a load.  Rows of h and of the right sides are
+// addressed through buffer descriptors of 2 GiB: a solid or missing cell has an offset beyond
+// the end, where loads return 0 and stores are dropped, and gets a finite placeholder update
+// (a = 1).  Lanes past the last quadruple repeat it (same values, same stores).  The full
+// barrier at the end of a quadrant makes its stores visible to the mirror reads of the next.
+constexpr int kLaneWaves = 8;
+constexpr int kLaneCols = 4;          // columns of a lane
+constexpr int kLaneQuads = 16;        // quadruples of a wave
+constexpr int kLaneWaveCols = 16;     // columns of a wave: kLaneCols by 64 / kLaneQuads groups
+constexpr int kLaneSlots = 8;
+constexpr uint32_t kNoRow = 0x80000000u;   // beyond the descriptors' 2 GiB
+// One wave's share of LDS.
+struct LaneWave {
+  u32x4 rec[kLaneSlots][64];                  // per slot and cell: axis 1 (a, b), (c, references), axis 2 the same
+  uint32_t off[kLaneSlots][kLaneWaveCols];     // byte offsets of the cells' rows
+  double2 carry[2][64];                      // by step parity: the last two columns of the lane's group
+  double row1[kLaneCols][64];                 // second out-of-grid axis-1 reference of row 1
+};
+
+// 1 / x for x > 0 well inside the range of normal numbers (the diagonals of the sweeps).
+__device__ __forceinline__ double reciprocal(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+  return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
+
+__global__ __launch_bounds__(64 * kLaneWaves) void sweep2d_lanes_kernel(
+    Sweep2DArgs a, const uint32_t* __restrict__ grec, const uint32_t* __restrict__ growb,
+    const double* __restrict__ rhs, double* __restrict__ h) {
+  extern __shared__ __align__(16) unsigned char lane_lds[];
+  const int W = blockDim.x >> 6, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  LaneWave* waves = reinterpret_cast<LaneWave*>(lane_lds);
+  LaneWave& me = waves[w];
+  int* published = reinterpret_cast<int*>(waves + W);   // rows whose carry the wave's last group has written
+  int* consumed = published + W;                        // steps whose carry of its left neighbour it has read
+  const int n = a.n, hn = n / 2, n3 = a.n3, d3 = a.d3;
+  const int nsp = a.nsp;
+  const int quads = hn * hn * d3, groups = (quads + kLaneQuads - 1) / kLaneQuads;
+  // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2); numbering
+  // them so that consecutive velocity groups of a case share an XCD lets the cache lines they
+  // share (their 128-byte segments of a row are not line-aligned) be fetched once.
+  const int nwg = gridDim.x, lin = blockIdx.x, per = nwg / 8, rem = nwg % 8, xcd = lin % 8, slot = lin / 8;
+  const int logical = xcd < rem ? xcd * (per + 1) + slot : rem * (per + 1) + (xcd - rem) * per + slot;
+  const int grp = logical % groups, cs = (logical / groups) % a.n_cases;
+  const int sp = (logical / (groups * a.n_cases)) % nsp;
+  // without mirror ghosts the quadrants do not read each other: one workgroup per quadrant
+  const int qsplit = logical / (groups * a.n_cases * nsp);
+  const int q0 = a.quad_split ? qsplit : 0, q1 = a.quad_split ? qsplit + 1 : 4;
+  if (a.case_active && !a.case_active[cs]) return;   // uniform over the workgroup
+  const double* __restrict__ nu = a.nu + static_cast<int64_t>(sp) * n3;
+  const uint32_t row_bytes = static_cast<uint32_t>(nsp * n3 * 8);
+  // rows of species sp (the launcher checks that h fits), the lane's velocity in the offset
+  const __amdgpu_buffer_rsrc_t rs_rhs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(rhs + static_cast<int64_t>(sp) * n3), 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_h =
+      __builtin_amdgcn_make_buffer_rsrc(h + static_cast<int64_t>(sp) * n3, 0, 0x7fffffff, 0x00020000);
+  const int g = lane / kLaneQuads;
+  const int t = min(grp * kLaneQuads + lane % kLaneQuads, quads - 1);
+  const int jq1 = t / (hn * d3), jq2 = (t / d3) % hn, j3 = t % d3;
+  const int n1 = a.n1[cs], n2 = a.n2[cs];
+  const int64_t g0 = a.grid_off[cs];
+  const double del = a.delta_case[cs];
+  const int jb = kLaneWaveCols * w + kLaneCols * g;     // the lane's first column
+  const int steps = (n1 + 64 / kLaneQuads) & ~1;       // an even count, the last group's last row included
+  auto ld = [&](const __amdgpu_buffer_rsrc_t& rs, uint32_t o) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, o, 0, 0));
+  };
+  for (int q = q0; q < q1; ++q) {
+    const int s1 = (q & 1) ? -1 : 1, s2 = (q & 2) ? -1 : 1;
+    const int j1 = s1 > 0 ? hn + jq1 : hn - 1 - jq1;
+    const int j2 = s2 > 0 ? hn + jq2 : hn - 1 - jq2;
+    const int v = (j1 * n + j2) * d3 + j3;
+    const int vm1 = ((n - 1 - j1) * n + j2) * d3 + j3;
+    const int vm2 = (j1 * n + (n - 1 - j2)) * d3 + j3;
+    const uint32_t vb = v * 8u, vm1b = vm1 * 8u, vm2b = vm2 * 8u;
+    const double av1 = fabs(a.v1d[j1]), av2 = fabs(a.v1d[j2]);
+    const double dnu = del * nu[v];
+    const int sg1 = s1 > 0 ? 0 : 1, sg2 = s2 > 0 ? 0 : 1;
+    if (lane == 0) {
+      published[w] = 0;
+      consumed[w] = 0;
+    }
+    __syncthreads();
+    // grid index of column c of oriented row r: rbase(r) + s2 c
+    auto rbase = [&](int r) { return g0 + static_cast<int64_t>(s1 > 0 ? r : n1 - 1 - r) * n2 + (s2 > 0 ? 0 : n2 - 1); };
+    // Staging of row r: lane 4 c + part loads 16 bytes of the records of the wave's column c
+    // (axis part / 2 with the sign of its velocity), and lane c (mod 16) the offset of its row.
+    // Beyond the grid the last row or column is read again, but for its offset: nothing inside
+    // depends on what comes of it there.
+    auto grid_col = [&](int c) { return s2 > 0 ? min(c, n2 - 1) : n2 - 1 - min(c, n2 - 1); };
+    const uint32_t rec_byte = grid_col(kLaneWaveCols * w + (lane >> 2)) * 128 + ((lane & 2) ? 2 + sg2 : sg1) * 32 + (lane & 1) * 16;
+    const int off_col = kLaneWaveCols * w + (lane & 15);
+    const uint32_t off_byte = grid_col(off_col) * 4;
+    auto load_row = [&](int r, u32x4& rec, uint32_t& off) {
+      const int rr = min(r, n1 - 1);
+      const int64_t row = g0 + static_cast<int64_t>(s1 > 0 ? rr : n1 - 1 - rr) * n2;
+      rec = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(grec + row * 32) + rec_byte);
+      off = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(growb + row) + off_byte);
+    };
+    auto put_row = [&](int r, const u32x4& rec, uint32_t off) {
+      me.rec[r % kLaneSlots][lane] = rec;
+      me.off[r % kLaneSlots][lane & 15] = r < n1 && off_col < n2 ? min(off, kNoRow) : kNoRow;
+    };
+    // byte offsets of the lane's row r, and its right sides
+    auto offsets = [&](int r, uint32_t (&o)[kLaneCols]) {
+      const u32x4 ov = *reinterpret_cast<const u32x4*>(&me.off[r & (kLaneSlots - 1)][kLaneCols * g]);
+#pragma unroll
+      for (int k = 0; k < kLaneCols; ++k) o[k] = ov[k] + vb;
+    };
+    auto load_rhs = [&](int r, double (&rr)[kLaneCols]) {
+      uint32_t o[kLaneCols];
+      offsets(r, o);
+#pragma unroll
+      for (int k = 0; k < kLaneCols; ++k) rr[k] = ld(rs_rhs, o[k]);
+    };
+    // value of a reference word (ref << 2 | kind) at the lane's velocity (mirrored for kind 2)
+    auto ref_at = [&](uint32_t x, uint32_t vmir) {
+      const uint32_t o = (x >> 2) * row_bytes + ((x & 3u) == 2 ? vmir : vb);
+      return ld(rs_h, x & 3u ? o : kNoRow);
+    };
+    // out-of-grid axis-2 references of the first group's row r: both of column 0, the second of column 1
+    auto load_edge = [&](int r, double (&ge)[3]) {
+      const u32x4* c = me.rec[r & (kLaneSlots - 1)];
+      ge[0] = ref_at(g == 0 ? c[3][2] : 0u, vm2b);
+      ge[1] = ref_at(g == 0 ? c[3][3] : 0u, vm2b);
+      ge[2] = ref_at(g == 0 ? c[7][3] : 0u, vm2b);
+    };
+    // out-of-grid axis-1 references take the places of rows r - 1, r - 2: both of row 0 in
+    // pr1, pr2, the second one of row 1 in LDS until row 1
+    double pr1[kLaneCols], pr2[kLaneCols];      // rows r - 1, r - 2 of the lane's columns
+#pragma unroll
+    for (int k = 0; k < kLaneCols; ++k) {
+      const bool have = jb + k < n2;
+      const uint32_t* p0 = grec + ((have ? rbase(0) + s2 * (jb + k) : a.grid_none) * 4 + sg1) * 8;
+      const uint32_t* p1 = grec + ((have && n1 > 1 ? rbase(1) + s2 * (jb + k) : a.grid_none) * 4 + sg1) * 8;
+      pr1[k] = ref_at(p0[6], vm1b);
+      pr2[k] = ref_at(p0[7], vm1b);
+      me.row1[k][lane] = ref_at(p1[7], vm1b);
+    }
+    u32x4 sA, sB;                             // staging words of row s + 4 (A / B alternate)
+    uint32_t fA, fB;
+    double rA[kLaneCols], rB[kLaneCols], eA[3] = {}, eB[3] = {};
+    for (int r = 0; r < 4; r += 2) {
+      load_row(r, sA, fA);
+      load_row(r + 1, sB, fB);
+      put_row(r, sA, fA);
+      put_row(r + 1, sB, fB);
+    }
+    // rows -3 .. -1 of the groups that have not begun: no cells (their slots are filled later)
+    for (int r = 5; r < kLaneSlots; ++r) me.off[r][lane & 15] = kNoRow;
+    load_rhs(-g, rA);
+    // of the row to come: right side less the term of the row above, the other three
+    // coefficients, the diagonal and its inverse
+    double acc0[kLaneCols], b2[kLaneCols], c1[kLaneCols], c2[kLaneCols], den[kLaneCols], inv[kLaneCols];
+    auto prepare = [&](int r, const double (&rc)[kLaneCols], const double (&up)[kLaneCols]) {
+      const double2* cf = reinterpret_cast<const double2*>(&me.rec[r & (kLaneSlots - 1)][4 * kLaneCols * g]);
+#pragma unroll
+      for (int k = 0; k < kLaneCols; ++k) {
+        const double2 ab1 = cf[4 * k], ab2 = cf[4 * k + 2];
+        den[k] = dnu + av1 * ab1.x + av2 * ab2.x;
+        inv[k] = reciprocal(den[k]);
+        b2[k] = av2 * ab2.y;
+        c1[k] = av1 * cf[4 * k + 1].x;
+        c2[k] = av2 * cf[4 * k + 3].x;
+        acc0[k] = rc[k] - av1 * ab1.y * up[k];
+      }
+    };
+    prepare(-g, rA, pr1);
+    auto sweep = [&](auto first) {
+      constexpr bool FIRST = decltype(first)::value;   // the wave of column 0
+      const double2* left = g > 0 ? &me.carry[0][lane - kLaneQuads]
+                                  : FIRST ? &me.carry[0][lane] : &waves[w - 1].carry[0][lane + 64 - kLaneQuads];
+      const int* left_rows = FIRST ? published : published + w - 1;
+      const int* right_steps = consumed + min(w + 1, W - 1);
+      // in the order of the loop below: its waits count the loads and stores since the one waited
+      // for, and allow no more of them than there are on the way into the loop
+      load_row(4, sA, fA);
+      if (FIRST) load_edge(0, eA);
+      __builtin_amdgcn_sched_barrier(0);
+      load_rhs(1 - g, rB);
+      __builtin_amdgcn_sched_barrier(0);
+      load_row(5, sB, fB);
+      if (FIRST) load_edge(1, eB);
+      __builtin_amdgcn_sched_barrier(0);
+      load_rhs(2 - g, rA);
+      __builtin_amdgcn_sched_barrier(0);
+      // Step s, prepared by the step before; up1 and up2 hold rows r - 1 and r - 2 and are left
+      // holding r - 1 and r.  While the chain through the row's cells runs, what does not depend
+      // on it: the staging, the next step's coefficients and inverses (its right sides rn) and the
+      // loads of the right sides of the step after the one after it.
+      auto step = [&](int s, double (&rn)[kLaneCols], double (&ec)[3], u32x4& sr, uint32_t& fr, double (&up1)[kLaneCols],
+                      double (&up2)[kLaneCols]) {
+        const int r = s - g;
+        if (s <= 4) {
+#pragma unroll
+          for (int k = 0; k < kLaneCols; ++k) {
+            double x = me.row1[k][lane];
+            asm volatile("" : "+v"(x));   // a value, not one of two addresses
+            up2[k] = r == 1 ? x : up2[k];
+          }
+        }
+        // LDS serves a wave's accesses in order: the carry read after a counter that is high enough
+        // is the one published before it
+        double2 in;
+        for (int it = 0; it < kRowSpinMax; ++it) {
+          const int rows = __hip_atomic_load(left_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+          __builtin_amdgcn_sched_barrier(0);
+          in = left[((s + 1) & 1) * 64];
+          if (FIRST || __builtin_amdgcn_readfirstlane(rows) >= min(s + 1, n1)) break;
+          __builtin_amdgcn_s_sleep(1);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        if (!FIRST) lds_publish(&consumed[w], s + 1);
+        const int taken = __hip_atomic_load(right_steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        put_row(s + 4, sr, fr);
+        load_row(s + 6, sr, fr);
+        uint32_t o[kLaneCols];
+        offsets(r, o);
+        double p1 = in.x, p2 = in.y;            // columns c - 1, c - 2 of this row
+        if (FIRST) {
+          p1 = g == 0 ? ec[0] : p1;
+          p2 = g == 0 ? ec[1] : p2;
+        }
+        const double e2 = ec[2];
+        double hv[kLaneCols];
+#pragma unroll
+        for (int k = 0; k < kLaneCols; ++k) {
+          if (FIRST && k == 1) p2 = g == 0 ? e2 : p2;
+          double acc = acc0[k];
+          acc -= b2[k] * p1;
+          acc -= c1[k] * up2[k];
+          acc -= c2[k] * p2;
+          hv[k] = div_known(acc, den[k], inv[k]);
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, hv[k]), rs_h, o[k], 0, 0);
+          p2 = p1;
+          p1 = hv[k];
+        }
+        if (s < 3) {                            // groups that have not begun keep the references
+#pragma unroll
+          for (int k = 0; k < kLaneCols; ++k) {
+            const double u1 = up1[k], u2 = up2[k];
+            up1[k] = r < 0 ? u2 : u1;
+            up2[k] = r < 0 ? u1 : hv[k];
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < kLaneCols; ++k) up2[k] = hv[k];
+        }
+        if (FIRST) load_edge(s + 2, ec);
+        prepare(r + 1, rn, up2);
+#pragma unroll
+        for (int k = 0; k < kLaneCols; ++k) asm volatile("" : "+v"(acc0[k]), "+v"(inv[k]));   // in this step, rn free
+        load_rhs(r + 3, rn);
+        if (w < W - 1 && __builtin_amdgcn_readfirstlane(taken) < s - 4)
+          lds_wait_at_least(right_steps, s - 4);   // its read of what is overwritten
+        me.carry[s & 1][lane] = make_double2(p1, p2);
+        if (w < W - 1) lds_publish(&published[w], s - 2);
+      };
+      for (int s = 0; s < steps; s += 2) {
+        step(s, rB, eA, sA, fA, pr1, pr2);
+        step(s + 1, rA, eB, sB, fB, pr2, pr1);
+      }
+    };
+    if (w == 0)
+      sweep(std::true_type{});
+    else
+      sweep(std::false_type{});
+    __syncthreads();
+  }
+}
+
+// Few cases: up to six of the lanes kernel's waves a compute unit.  (Four, one a SIMD: 0.53 of the
+// rows kernel's time; ten: 1.14.)
+bool sweep2d_by_lanes(const Sweep2DArgs& a) {
+  const int hn = a.n / 2;
+  const int64_t quads = static_cast<int64_t>(hn) * hn * a.d3;
+  const int W = (a.max_n2 + kLaneWaveCols - 1) / kLaneWaveCols;
+  return (quads + kLaneQuads - 1) / kLaneQuads * a.n_cases * a.nsp * (a.quad_split ? 4 : 1) * W <= 6 * 256;
+}
+
 // Per (cell, species) row: U3, q3 = int (a v^2 - 5/2) v3 h, G1, G12, G2, P13 = 2a int v1 v3 h,
 // P23 = 2a int v2 v3 h (a = m_s / m_A; 1 for one gas).
 __global__ __launch_bounds__(256) void moments2d_kernel(int n3, int nsp, double ms0, double ms1,
@@ -3878,6 +4186,18 @@ hipError_t launch_sweep2d(const Sweep2DArgs& a, hipStream_t s) {
   const int count = hn * hn * a.d3;
   const int form = sweep2d_form(a.max_diag, a.max_n2, a.row_bytes_total);
   if (form == 1) {
+    if (sweep2d_by_lanes(a)) {
+      const int W = (a.max_n2 + kLaneWaveCols - 1) / kLaneWaveCols;
+      const size_t lds = W * (sizeof(LaneWave) + 2 * sizeof(int));
+      if (lds > 65536) {   // has to be asked for
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(sweep2d_lanes_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        if (e != hipSuccess) return e;
+      }
+      dim3 grid(((count + kLaneQuads - 1) / kLaneQuads) * a.n_cases * a.nsp * (a.quad_split ? 4 : 1));
+      hipLaunchKernelGGL(sweep2d_lanes_kernel, grid, dim3(64 * W), lds, s, a, a.grec, a.growb, a.rhs, a.h);
+      return hipGetLastError();
+    }
     const int cwmax = a.max_n2 <= kRowWaves * 4 ? 4 : 8;
     const int W = (a.max_n2 + cwmax - 1) / cwmax;
     dim3 grid(((count + 63) / 64) * a.n_cases * a.nsp * (a.quad_split ? 4 : 1));
