@@ -3125,30 +3125,54 @@ __device__ void d2_fill_work(const Diff2DArgs& a, int cs, int s, double* W, int 
   }
 }
 
+// The fields of that workspace at grid cell g of a case (0 .. 5, 10, 11): as filled, or straight
+// from the moments (the inverse form needs them once, and its cells are then independent).
+struct D2Work {
+  const double* W;
+  __device__ double operator()(int g, int f) const { return W[static_cast<int64_t>(g) * kDiffWork + f]; }
+};
+struct D2Moments {
+  const Diff2DArgs& a;
+  int s;
+  int64_t g0;
+  double chi, Nd;
+  __device__ double operator()(int g, int f) const {
+    const int cell = a.gcell[g0 + g];
+    if (cell < 0) return 0.0;
+    const int64_t row = static_cast<int64_t>(cell) * a.nsp + s;
+    if (f == 0) return a.mom[row * 8] / chi;
+    if (f < 4) return a.mom[row * 8 + f + 1];
+    if (f < 6) return a.amom ? a.amom[row * 4 + 2 * (f - 4)] + Nd * a.amom[row * 4 + 2 * (f - 4) + 1] : 0.0;
+    return a.nsp == 2 ? a.mom[(static_cast<int64_t>(cell) * 2 + 1) * 8 + f - 5] : 0.0;
+  }
+};
+
 // Right side of the finite-volume velocity equation of species s at an unknown grid
 // cell G (Dirichlet neighbours moved to the right) and the diagonal of its row:
 // chi_s lap U_s = source_s - (d11 G1 + 2 d12 G12 + d22 G2) + d1 A1 + d2 A2, with
 // source = -N delta [Poiseuille] for one gas; for mixtures N_A delta (div P_B - [P])
 // (species A) and -N_B delta (m_A/m_B) div P_B (species B).
-__device__ double d2_rhs(const Diff2DArgs& a, int s, int64_t g0, int64_t G, const double* W, bool pois, double del,
+template <class Field>
+__device__ double d2_rhs(const Diff2DArgs& a, int s, int64_t g0, int64_t G, const Field& W, bool pois, double del,
                          double& diag) {
   const int g = static_cast<int>(G - g0);
-  const double* w = W + static_cast<int64_t>(g) * kDiffWork;
   const int32_t* nbr = a.nb + G * 8;
   const int8_t* bits = a.nbm + G * 8;
   const double* np = a.npos + G * 4;
   const double xc = a.cpos[G * 2], yc = a.cpos[G * 2 + 1];
   auto val = [&](int q, int f, int p1, int p2) {
     const int r = nbr[q];
-    return r < 0 ? 0.0 : par_sign(bits[q], p1, p2) * W[static_cast<int64_t>(r) * kDiffWork + f];
+    return r < 0 ? 0.0 : par_sign(bits[q], p1, p2) * W(r, f);
   };
   const double xE = np[0], xW = np[1], yN = np[2], yS = np[3];
   const double w1 = a.width[G * 2], w2 = a.width[G * 2 + 1];
   auto d11 = [&](int f, int p1, int p2) {
-    return ((val(0, f, p1, p2) - w[f]) / (xE - xc) - (w[f] - val(1, f, p1, p2)) / (xc - xW)) / w1;
+    const double w = W(g, f);
+    return ((val(0, f, p1, p2) - w) / (xE - xc) - (w - val(1, f, p1, p2)) / (xc - xW)) / w1;
   };
   auto d22 = [&](int f, int p1, int p2) {
-    return ((val(2, f, p1, p2) - w[f]) / (yN - yc) - (w[f] - val(3, f, p1, p2)) / (yc - yS)) / w2;
+    const double w = W(g, f);
+    return ((val(2, f, p1, p2) - w) / (yN - yc) - (w - val(3, f, p1, p2)) / (yc - yS)) / w2;
   };
   const double Nd = a.Ns[s] * del;
   double rhs = 0.0;
@@ -3172,7 +3196,7 @@ __device__ double d2_rhs(const Diff2DArgs& a, int s, int64_t g0, int64_t G, cons
     if (fw == 0.0) continue;
     const int r = nbr[q];
     diag += fw;
-    if (a.dflag[g0 + r] != 2) b += fw * W[static_cast<int64_t>(r) * kDiffWork + 0];
+    if (a.dflag[g0 + r] != 2) b += fw * W(r, 0);
   }
   return b;
 }
@@ -3180,6 +3204,7 @@ __device__ double d2_rhs(const Diff2DArgs& a, int s, int64_t g0, int64_t G, cons
 // New velocities, corrections, moments of h^{k+1}, flow rates and the convergence
 // test of one case (all species).  usol: the solutions at the unknown cells (null:
 // the CG iterate in the workspace; CIS: no solve).
+template <bool INVERSE>
 __device__ void d2_outputs(const Diff2DArgs& a, int cs, int ng, const double* usol, int it, double* sh) {
   const int64_t g0 = a.grid_off[cs];
   const int nsp = a.nsp;
@@ -3192,10 +3217,9 @@ __device__ void d2_outputs(const Diff2DArgs& a, int cs, int ng, const double* us
       const int cell = a.gcell[G];
       if (cell < 0) continue;
       const int64_t row = static_cast<int64_t>(cell) * nsp + s;
-      const double* w = W + static_cast<int64_t>(g) * kDiffWork;
-      const double Uh = w[0];
+      const double Uh = INVERSE ? a.mom[row * 8] / a.chi[s] : W[static_cast<int64_t>(g) * kDiffWork];
       double U = Uh;
-      if (a.sis && a.dflag[G] == 2) U = usol ? usol[voff + a.uidx[G]] : w[6];
+      if (a.sis && a.dflag[G] == 2) U = INVERSE ? usol[voff + a.uidx[G]] : W[static_cast<int64_t>(g) * kDiffWork + 6];
       const double dU = U - Uh;
       const double Un = Uh + dU * a.cUs[s];
       const double qn = a.mom[row * 8 + 1] + dU * a.cqs[s];
@@ -3211,7 +3235,7 @@ __device__ void d2_outputs(const Diff2DArgs& a, int cs, int ng, const double* us
   if (threadIdx.x == 0) {
     // the CG iterate in the workspace is a valid warm start only after a CG solve (the
     // inverse path leaves the workspace's iterate untouched)
-    if (a.have_x) a.have_x[cs] = (a.sis && !usol) ? 1 : 0;
+    if (a.have_x) a.have_x[cs] = (a.sis && !INVERSE) ? 1 : 0;
     if (a.cg_iters) a.cg_iters[cs] = it;
     if (a.state) {
       double* st = a.state + cs * (2 * nsp + 2);   // M[nsp], Q[nsp], residual, iterations
@@ -3262,7 +3286,7 @@ __global__ __launch_bounds__(kD2Threads) void diffusion2d_kernel(Diff2DArgs a) {
       if (a.dflag[G] != 2) continue;
       double* w = W + static_cast<int64_t>(g) * kDiffWork;
       double diag;
-      const double b = d2_rhs(a, 0, g0, G, W, pois, del, diag);
+      const double b = d2_rhs(a, 0, g0, G, D2Work{W}, pois, del, diag);
       double Ax = 0.0;
       for (int q = 0; q < 4; ++q) {
         const double fw = a.fw[G * 4 + q];
@@ -3332,30 +3356,27 @@ __global__ __launch_bounds__(kD2Threads) void diffusion2d_kernel(Diff2DArgs a) {
       ++it;
     }
   }
-  d2_outputs(a, cs, ng, nullptr, it, sh);
+  d2_outputs<false>(a, cs, ng, nullptr, it, sh);
 }
 
-// Inverse form, step 1: right sides of the unknown cells of every species (compact per case).
-__global__ __launch_bounds__(kD2Threads) void diffusion2d_rhs_kernel(Diff2DArgs a) {
-  const int cs = blockIdx.x;
+// Inverse form, step 1: right sides of the unknown cells of every species (compact per case), by
+// cells over the chip (one workgroup a case, its fields staged in the workspace first: 110 us
+// for a 64 x 64 duct, 390 for two periodic 128 x 128 cells; now 12 and 36).
+__global__ __launch_bounds__(256) void diffusion2d_rhs_kernel(Diff2DArgs a) {
+  const int cs = blockIdx.y, s = blockIdx.z;
   if (a.case_active && !a.case_active[cs]) return;
-  if (!a.direct[cs]) return;
+  if (!a.direct[cs] || !a.sis) return;
   const int64_t g0 = a.grid_off[cs];
   const int ng = static_cast<int>(a.grid_off[cs + 1] - g0);
   const double del = a.delta_case[cs];
   const bool pois = a.flow_case[cs] == 1;
-  for (int s = 0; s < a.nsp; ++s) d2_fill_work(a, cs, s, d2_work(a, cs, s), ng, true);
-  __syncthreads();
-  if (!a.sis) return;
-  for (int s = 0; s < a.nsp; ++s) {
-    const double* W = d2_work(a, cs, s);
-    const int64_t voff = a.nsp * a.uoff[cs] + static_cast<int64_t>(s) * a.n_unknown[cs];
-    for (int g = threadIdx.x; g < ng; g += blockDim.x) {
-      const int64_t G = g0 + g;
-      if (a.dflag[G] != 2) continue;
-      double diag;
-      a.bvec[voff + a.uidx[G]] = d2_rhs(a, s, g0, G, W, pois, del, diag);
-    }
+  const D2Moments W = {a, s, g0, a.chi[s], a.Ns[s] * del};
+  const int64_t voff = a.nsp * a.uoff[cs] + static_cast<int64_t>(s) * a.n_unknown[cs];
+  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < ng; g += gridDim.x * blockDim.x) {
+    const int64_t G = g0 + g;
+    if (a.dflag[G] != 2) continue;
+    double diag;
+    a.bvec[voff + a.uidx[G]] = d2_rhs(a, s, g0, G, W, pois, del, diag);
   }
 }
 
@@ -3409,7 +3430,7 @@ __global__ __launch_bounds__(kD2Threads) void diffusion2d_out_kernel(Diff2DArgs 
   if (!a.direct[cs]) return;
   const int64_t g0 = a.grid_off[cs];
   const int ng = static_cast<int>(a.grid_off[cs + 1] - g0);
-  d2_outputs(a, cs, ng, a.yvec, 0, sh);
+  d2_outputs<true>(a, cs, ng, a.yvec, 0, sh);
 }
 
 // Newton-Schulz steps for the inverse of a Jacobi-scaled SPD matrix (plan time).
@@ -4231,7 +4252,8 @@ hipError_t launch_moments2d(int n3, int nsp, const double* mass_ratio, int64_t n
 hipError_t launch_diffusion2d(const Diff2DArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(diffusion2d_kernel, dim3(a.n_cases), dim3(kD2Threads), 0, s, a);
   if (a.direct) {
-    hipLaunchKernelGGL(diffusion2d_rhs_kernel, dim3(a.n_cases), dim3(kD2Threads), 0, s, a);
+    const unsigned blocks = std::max(1, (a.max_unknown + 255) / 256);
+    hipLaunchKernelGGL(diffusion2d_rhs_kernel, dim3(blocks, a.n_cases, a.nsp), dim3(256), 0, s, a);
     if (a.max_unknown > 0 && a.n_groups > 0)
       hipLaunchKernelGGL(diffusion2d_gemv_kernel, dim3((a.max_unknown + 3) / 4, a.n_groups), dim3(256), 0, s, a);
     hipLaunchKernelGGL(diffusion2d_out_kernel, dim3(a.n_cases), dim3(kD2Threads), 0, s, a);
