@@ -1392,7 +1392,13 @@ template <int NT = 256, int LOGB = -1>   // NT: threads of the workgroup
 __device__ __forceinline__ void finish_tail(const FinishArgs& a, int64_t c, double (&m)[9]) {
   __shared__ double sh[NT / 64 * 9];
   __shared__ double coef[5];
-  block_sum<9>(m, sh);
+  if (a.project) {
+    block_sum<9>(m, sh);
+  } else {   // the last four only: the sums across lanes are a tenth of a short row's time
+    double am[4] = {m[5], m[6], m[7], m[8]};
+    block_sum<4>(am, sh);
+    for (int k = 0; k < 4; ++k) m[5 + k] = am[k];
+  }
   if (a.project) {
     if (threadIdx.x < 5) {
       double s = 0.0;
@@ -1630,12 +1636,12 @@ __global__ __launch_bounds__(256) void finish_kernel(FinishArgs a) { finish_row(
 // the whole matrix took 0.96 ms; 808 cells of 8192: 59 us with two splits, 76 us with four before).
 // T: v2d (pairs) or double.
 // A: double, or float for the sums of the low-precision contractions.
-template <int LOGB, class T, class A>
+// UZ: splits whose loads are in flight together.
+template <int LOGB, class T, class A, int UZ>
 __device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t row, double (&m)[9]) {
   constexpr int NB = 1 << LOGB;
   constexpr bool PAIR = sizeof(T) == 16;
   constexpr int STEP = PAIR ? 2 : 1;
-  constexpr int UZ = LOGB == 1 ? 4 : LOGB == 2 ? 2 : 1;   // splits whose loads are in flight together
   const SymMap& y = a.sym;
   const int nsp = a.nsp, sp = static_cast<int>(row % nsp);
   const int64_t cell = row / nsp;
@@ -1762,9 +1768,11 @@ __device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t ro
 }
 
 // pairs: every row, and the class rows, in 16-byte pairs (lh may be offset by 8 bytes)
-// NT threads a row: 256, or more where there are no more rows than compute units.
-template <int LOGB, class A, int NT>
+// NT threads a row: 256, or more where there are no more rows than compute units; DEEP: more splits in
+// flight, at the price of waves a SIMD that few rows do not have.
+template <int LOGB, class A, int NT, bool DEEP>
 __global__ __launch_bounds__(NT) void finish_class_kernel(FinishArgs a) {
+  constexpr int UZ = (LOGB == 1 ? 4 : LOGB == 2 ? 2 : 1) * (DEEP ? 2 : 1);
   const int64_t row = blockIdx.x;
   if (a.active && !a.active[row / a.nsp]) return;
   double m[9];
@@ -1776,9 +1784,9 @@ __global__ __launch_bounds__(NT) void finish_class_kernel(FinishArgs a) {
   bool pairs = false;
   if constexpr (LOGB < 3) {
     pairs = a.sym.pairs && (align & 15) == 0;
-    if (pairs) finish_class_row<LOGB, v2d, A>(a, row, m);
+    if (pairs) finish_class_row<LOGB, v2d, A, UZ>(a, row, m);
   }
-  if (!pairs) finish_class_row<LOGB, double, A>(a, row, m);
+  if (!pairs) finish_class_row<LOGB, double, A, UZ>(a, row, m);
   finish_tail<NT, LOGB>(a, row, m);
 }
 
@@ -4192,10 +4200,14 @@ hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
   // 1024 threads a row (512 of the 161-register form; 104 rows of 13 824: 43 -> 33 us).  With more rows than
   // units 256 stream as well, and rows of 256 orbits or pairs at most have no use for more.
   const bool wide = a.n_cells <= 256 && a.sym.nvb > 512;
+  // Short rows, few of them, have as many splits as it takes to fill the chip, and a round of loads
+  // for each four of them is what they wait for (17 rows of 1024, eight splits: 7.5 -> 6.1 us).
+  const bool deep = a.n_cells <= 256;
 #define SIS_FINISH_(LOGB, A)                                                                             \
-  if (wide) hipLaunchKernelGGL((finish_class_kernel<LOGB, A, LOGB == 2 ? 512 : 1024>), grid,             \
+  if (wide) hipLaunchKernelGGL((finish_class_kernel<LOGB, A, LOGB == 2 ? 512 : 1024, false>), grid,      \
                                dim3(LOGB == 2 ? 512 : 1024), 0, s, a);                                   \
-  else hipLaunchKernelGGL((finish_class_kernel<LOGB, A, 256>), grid, dim3(256), 0, s, a)
+  else if (deep) hipLaunchKernelGGL((finish_class_kernel<LOGB, A, 256, true>), grid, dim3(256), 0, s, a); \
+  else hipLaunchKernelGGL((finish_class_kernel<LOGB, A, 256, false>), grid, dim3(256), 0, s, a)
 #define SIS_FINISH(LOGB) if (a.acc_f32) { SIS_FINISH_(LOGB, float); } else { SIS_FINISH_(LOGB, double); }
   switch (a.sym.logb) {
     case 0: hipLaunchKernelGGL(finish_kernel, grid, dim3(256), 0, s, a); break;

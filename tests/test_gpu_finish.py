@@ -37,3 +37,22 @@ def test_few_rows_equal_many(parity, project):
             assert (a - b).abs().max() <= 1e-12 * b.abs().max(), k
     a, b = out[few][2], out[many][2][:few]
     assert (a - b).abs().max() <= 1e-12 * b.abs().max()
+
+
+@pytest.mark.parametrize("n,parity,splits", [(16, 2, 8), (16, 2, 11), (12, 1, 9), (12, 0, 3)])
+def test_many_splits_of_few_rows(n, parity, splits):
+    """Few short rows load more splits at once: the same sums in the same order as in a larger batch."""
+    p = sis.Plan(n, 5.0, m_angle=2, parity=parity)
+    few, many = 17, 300
+    g = torch.Generator(device=DEV).manual_seed(splits)
+    h = torch.randn((many, p.n_dof), dtype=torch.float64, device=DEV, generator=g)
+    delta = torch.rand(many, dtype=torch.float64, device=DEV, generator=g) + 0.5
+    out = {}
+    for nc in (few, many):
+        p.set_contraction_config(nc, 128, 16, splits)
+        r = torch.full((nc, p.n_dof), np.nan, dtype=torch.float64, device=DEV)
+        am = torch.full((nc, 4), np.nan, dtype=torch.float64, device=DEV)
+        p.collide(h[:nc], delta[:nc], r, amom_out=am)
+        out[nc] = (r, am)
+    assert torch.equal(out[few][0], out[many][0][:few])
+    assert torch.equal(out[few][1], out[many][1][:few])
