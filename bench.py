@@ -293,13 +293,13 @@ def contraction_roofline(W, precision, reps):
     gemm_ms, launches = plan.timing_read()
     plan.timing(False)
     tile_rows, splits, tuned, k_stage = plan.contraction_config(nc, precision, with_depth=True)
-    avg_ms = gemm_ms / launches
+    avg_ms, passes = gemm_ms / reps, launches // reps   # a batch over 2 GiB of class rows goes in passes
     per_cell = 2.0 * n3 * n3 / classes(W)
     executed = per_cell * nc * (3 if precision == "bf16x3" else 1)
     achieved = executed / (avg_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[precision]
     tile = "256x256" if tile_rows == 256 else f"{tile_rows}x128"
-    log(f"contraction ({precision}): {avg_ms:.3f} ms/launch, {achieved:.1f} TFLOP/s of {peak} peak "
+    log(f"contraction ({precision}): {avg_ms:.3f} ms in {passes} launches, {achieved:.1f} TFLOP/s of {peak} peak "
         f"(tile {tile}, k-stage {k_stage}, split-K {splits}, autotuned {tuned})")
     ck = (W["w"]["name"], W["parity"], precision, tile_rows, splits, k_stage)
     tk, mb = TRAFFIC_KIB.get(ck), MFMA_BUSY.get(ck)
@@ -308,11 +308,11 @@ def contraction_roofline(W, precision, reps):
             "frac": round(achieved / peak, 4), "traffic": (tk[0] + tk[1]) * 1024.0 if tk else None,
             "mfma_busy": mb[0] if mb else None, "clock_ghz_counters": mb[1] if mb else None,
             "counters_source": tk[2] if tk else None,
-            "kernel": f"gemm_{precision}", "avg_launch_ms": round(avg_ms, 4),
-            "tile": tile, "k_stage": k_stage, "split_k": splits, "autotuned": tuned,
+            "kernel": f"gemm_{precision}", "avg_launch_ms": round(avg_ms / passes, 4),
+            "launches_per_step": passes, "tile": tile, "k_stage": k_stage, "split_k": splits, "autotuned": tuned,
             "work_per_unit": f"2 n_dof^2 / {classes(W)} flops per cell update (the operator of L+ applied to one cell, "
                              "block diagonal on the classes of the velocity reflections)",
-            "flops_per_launch": executed, "flops_per_cell_update": per_cell}
+            "flops_per_launch": executed / passes, "flops_per_cell_update": per_cell}
     if not W["mix"] and not W["tube"]:
         fa = fsm_flops(info["n_pad"], info["n_dir"])
         roof["fsm_flops_per_cell_update"] = fa
@@ -578,7 +578,7 @@ def main():
     if not args.no_fsm and not W["mix"] and not W["tube"] and hasattr(W["plan"], "collide_fsm"):
         W["plan"].set_precision("fp64")
         fsm = fsm_path(W, h, delta, max(3, min(reps, 5)))
-        fsm["vs_dense_contraction"] = round(fsm["avg_call_ms"] / roofline["avg_launch_ms"], 2)
+        fsm["vs_dense_contraction"] = round(fsm["avg_call_ms"] / (roofline["avg_launch_ms"] * roofline["launches_per_step"]), 2)
     del h, delta
     ttr = {}
     if not args.no_ttr:
