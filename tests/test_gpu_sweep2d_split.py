@@ -70,3 +70,30 @@ def test_sweep_forms(kind, copies):
         o += len(g.cells)
         ref = duct.sweep_2d(rhs[s], deltas[c] * f.nu, g, f.grid, prev[s])
         assert rel(h[0, s], ref.reshape(len(g.cells), -1)) < 1e-12, c
+
+
+@pytest.mark.parametrize("species,n1,n2", [(1, 47, 44), (1, 46, 45), (2, 50, 43), (2, 9, 5)])
+def test_moments_of_the_swept_cells(species, n1, n2):
+    """2068, 2070, 2150 cells (four cells a workgroup, 0 and 2 left over) and 45 (one): sums of n^3 terms in
+    any order, against the sums of their magnitudes."""
+    n, l_v = 6, 4.0
+    mix = dict(masses=(1.0, 2.0), diameters=(1.0, 0.8), chi=(0.4, 0.6), m_rho=3) if species == 2 else None
+    p = sis.Plan(n, l_v, m_angle=2, mixture=mix)
+    geom = sis.Geometry2D(p, "duct", [(faces(n1), faces(n2), None)], [0.7], [1])
+    nc = n1 * n2
+    g = torch.Generator(device=DEV).manual_seed(n2)
+    rhs = torch.randn((nc, p.n_dof), dtype=torch.float64, device=DEV, generator=g)
+    h, mom = torch.zeros_like(rhs), torch.full((nc, species, 8), np.nan, dtype=torch.float64, device=DEV)
+    sis.transport_sweep(p, geom, rhs, h, mom)
+    torch.cuda.synchronize()
+    vg = VelocityGrid(n, l_v)
+    v1, v2, v3 = (np.broadcast_to(a, (n, n, n)) for a in (vg.V1, vg.V2, vg.V3))
+    h, mom = h.cpu().numpy().reshape(nc, species, n, n, n), mom.cpu().numpy().reshape(nc, species, 8)
+    for s in range(species):
+        ms = (1.0, 2.0)[s]
+        f = [v3, (ms * (v1 ** 2 + v2 ** 2 + v3 ** 2) - 2.5) * v3, v3 * (2 * v1 ** 2 - 1), 2 * v1 * v2 * v3,
+             v3 * (2 * v2 ** 2 - 1), 2 * ms * v1 * v3, 2 * ms * v2 * v3]
+        for k, fk in enumerate(f):
+            ref = np.array([vg.integrate(fk * x) for x in h[:, s]])
+            size = np.array([vg.integrate(np.abs(fk * x)) for x in h[:, s]])
+            assert np.all(np.abs(mom[:, s, k] - ref) <= (n ** 3 + 16) * np.finfo(float).eps * size), (s, k)
