@@ -303,7 +303,13 @@ sis_status sis_geometry_diffusion_info(sis_geom_t geom, int32_t* n_inverse, int3
  * Mixtures: h, rhs_out, lh_out are [n_cells][2][n3], dU is [n_cells][2]
  * (correction h_a += dU_a 2 (m_a/m_A) v3 f_a; the correction of both species
  * enters L+ of each), amom_out is [n_cells][2][4]; S_a = v3 f_a for
- * Poiseuille, 0 otherwise; project must be 0.                               */
+ * Poiseuille, 0 otherwise; project must be 0.
+ * The class rows and split-K sums go to a workspace of the plan that grows on demand, which it
+ * cannot while `stream` is capturing: a captured call takes what earlier calls have made room for
+ * (fewer splits, then the tile without class rows, then passes of at least 256 cells).  With less
+ * than that FP64, and the bf16 forms fixed to the 32-row tile with one split, apply the whole
+ * matrix in FP64, in place and at 2 to 8 times the operations; the others return
+ * SIS_E_UNSUPPORTED.  So run the call once, eagerly, before capturing it.              */
 sis_status sis_collide(sis_plan_t plan, int64_t n_cells, const double* h, const double* dU,
                        const double* delta, const int32_t* flow, int32_t project,
                        double* rhs_out, double* lh_out, double* amom_out, hipStream_t stream);

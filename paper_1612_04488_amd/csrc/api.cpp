@@ -607,6 +607,24 @@ struct CollideArgs {
   int tile, splits;
 };
 
+// While a stream captures nothing can be allocated.  Fits a step to the workspace of acc_bytes and
+// x_bytes that there is: fewer splits, then the tile that reads the cells' own rows where the class
+// rows find no room, then smaller passes.  False where those would be of fewer than 256 cells
+// (anchored iterations, which know no other way, take any).
+bool fit_workspace(const sis_plan* p, int64_t n_cells, size_t acc_bytes, size_t x_bytes, CollideArgs& c, int64_t* pass) {
+  const int64_t whole = *pass;
+  const size_t sum_cell = static_cast<size_t>(p->row_len()) * sum_bytes(c.precision);
+  auto rows_fit = [&]() {
+    return own_rows(c.precision, c.tile) ? n_cells : static_cast<int64_t>(x_bytes / class_row_bytes(p, c.precision));
+  };
+  auto cells_fit = [&]() { return std::min(rows_fit(), static_cast<int64_t>(acc_bytes / (c.splits * sum_cell))); };
+  while (c.splits > 1 && acc_bytes / (c.splits * sum_cell) < static_cast<size_t>(whole)) --c.splits;
+  if (rows_fit() < std::min<int64_t>(whole, 256) && c.precision != SIS_PREC_FP32) c.tile = 1;
+  *pass = std::min(whole, cells_fit());
+  if (*pass < whole && *pass > 256) *pass = *pass / 128 * 128;
+  return *pass >= (c.anchor_mode ? 1 : std::min<int64_t>(n_cells, 256));
+}
+
 // Cells [c0, c0 + nc) of a step: class rows, contraction, finish, with the workspace given.
 sis_status collide_pass(sis_plan* p, const CollideArgs& c, int64_t c0, int64_t nc, void* xrows, void* acc,
                         bool capturing, hipStream_t s) {
@@ -660,14 +678,20 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
                 rhs, lh,   amom,  cell_active, precision < 0 ? p->precision : precision,
                 anchor_mode, xref, accref, 0, 0};
   gemm_config(p, n_cells, c.precision, &c.tile, &c.splits);
-  const int64_t pass = pass_cells(p, n_cells);
+  int64_t pass = pass_cells(p, n_cells);
   const size_t acc_bytes = static_cast<size_t>(c.splits) * pass * p->row_len() * sum_bytes(c.precision);
   const size_t x_bytes = own_rows(c.precision, c.tile) ? 0 : class_row_bytes(p, c.precision) * pass;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIP_TRY(hipStreamIsCapturing(s, &cs));
   const bool capturing = cs != hipStreamCaptureStatusNone;
-  if (capturing && c.precision == SIS_PREC_FP64 && (acc_bytes > ws_acc->bytes || x_bytes > ws_x->bytes)) {
-    // no workspace yet and none can be made: the whole matrix, written over the right side in place
+  const bool in_place = c.precision == SIS_PREC_FP64 || (own_rows(c.precision, c.tile) && c.splits == 1);
+  if (!capturing) {
+    HIP_TRY(ws_acc->ensure(acc_bytes));
+    HIP_TRY(ws_x->ensure(x_bytes));
+  } else if (!fit_workspace(p, n_cells, ws_acc->bytes, ws_x->bytes, c, &pass)) {
+    // no workspace yet and none can be made: the whole matrix in FP64, written over the right side in place
+    if (c.anchor_mode || !in_place)
+      return fail(SIS_E_UNSUPPORTED, "no workspace for this contraction while the stream is capturing: run it once before");
     sis::GemmArgs g{};
     g.X = h;
     g.op64 = p->op;
@@ -684,8 +708,6 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
     HIP_TRY(sis::launch_finish(f, s));
     return SIS_OK;
   }
-  HIP_TRY(ws_acc->ensure(acc_bytes));
-  HIP_TRY(ws_x->ensure(x_bytes));
   if (capturing) ws_acc->captured = ws_x->captured = true;
   for (int64_t c0 = 0; c0 < n_cells; c0 += pass)
     if (sis_status st = collide_pass(p, c, c0, std::min(pass, n_cells - c0), ws_x->p, ws_acc->p, capturing, s))

@@ -1,0 +1,109 @@
+"""The contraction's workspace where it is not what the configuration asks for: captured with less
+(anchored iterations, the low precisions), and batches that go in several passes."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1612_04488_amd import sis
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+UNSUPPORTED = -7
+
+
+def rnd(seed, *shape):
+    return torch.randn(shape, dtype=torch.float64, device=DEV, generator=torch.Generator(device=DEV).manual_seed(seed))
+
+
+def captured(f):
+    """f(stream) recorded into a graph; what it raised, if it did."""
+    g, s, err = torch.cuda.CUDAGraph(), torch.cuda.Stream(), None
+    mark = torch.zeros(1, device=DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        try:
+            f(s.cuda_stream)
+        except sis.SisError as e:
+            err = e
+        mark.add_(1)
+    return g, err
+
+
+@pytest.mark.parametrize("precision", ["bf16x3", "fp32"])
+def test_captured_anchor_iteration_keeps_its_anchor(precision):
+    """The FP64 configuration of the state needs no room for class rows; the one fixed afterwards does.  A
+    captured anchor iteration that stored no anchor would leave the next ones at the low precision's
+    distance from a stale one (1e-6 and more); tiles differ by the rounding of sums of 128 products."""
+    p = sis.Plan(8, 5.0, m_angle=2, parity=2)
+    p.set_precision(precision)
+    x = -0.5 + 0.5 * np.linspace(0.0, 1.0, 30) ** 2
+    x[-1] = 0.0
+    geom = sis.Geometry(p, [x], [1.0], [1])
+    n = geom.n_cells
+    p.set_contraction_config(n, 32, 16, 1)
+    p.set_contraction_config(n, 32, 64 if precision == "bf16x3" else 16, 1, precision=precision)
+    eager, graph = (sis.State(p, geom, eps=0.0, use_graph=False, refresh_every=8) for _ in range(2))
+    p.set_contraction_config(n, 128, 16, 2)
+    for s in (eager, graph):
+        s.step(4)
+    g, err = captured(lambda stream: graph.step(1, stream=stream))      # the anchor of iteration 4
+    assert err is None
+    eager.step(1)
+    g.replay()
+    for s in (eager, graph):
+        s.step(3)
+    a, b = eager.results(), graph.results()
+    for k in ("U", "q"):
+        assert np.abs(a[k] - b[k]).max() <= 1e-12 * np.abs(a[k]).max(), k
+
+
+def test_bf16_capture_before_any_eager_call():
+    """32-row tile, one split: needed no workspace when it was the whole matrix, and still runs."""
+    p = sis.Plan(8, 5.0, m_angle=2)
+    op = p.tables(operator=True)["op"]
+    p.set_precision("bf16x3")
+    nc = 20
+    p.set_contraction_config(nc, 32, 64, 1, precision="bf16x3")
+    h, delta, rhs = rnd(1, nc, p.n_dof), torch.ones(nc, dtype=torch.float64, device=DEV), rnd(2, nc, p.n_dof)
+    g, err = captured(lambda stream: p.collide(h, delta, rhs))
+    assert err is None
+    for it in range(3):
+        h.copy_(rnd(3 + it, nc, p.n_dof))
+        rhs.fill_(np.nan)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        hn = h.cpu().numpy()
+        # 3xBF16: each product short by at most 3 x 2^-18, its sums in FP32
+        assert np.all(np.abs(rhs.cpu().numpy() - hn @ op.T) <= 2.0 ** -15 * (np.abs(hn) @ np.abs(op.T)))
+
+
+def test_capture_without_room_is_refused_cleanly():
+    """FP32 has no form without a workspace: an error before anything is recorded, and the capture goes on.
+    After one eager call of that size the same call is captured, with a smaller batch and fewer splits too."""
+    p = sis.Plan(8, 5.0, m_angle=2, parity=1)
+    op = p.tables(operator=True)["op"]
+    p.set_precision("fp32")
+    big, small = 600, 300
+    h, delta = rnd(1, big, p.n_dof), torch.ones(big, dtype=torch.float64, device=DEV)
+    out = torch.full_like(h, np.nan)
+    for nc in (big, small):
+        p.set_contraction_config(nc, 128, 16, 1, precision="fp32")
+    g, err = captured(lambda stream: p.collide(h, delta, out))
+    assert err is not None and err.code == UNSUPPORTED
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.isnan(out).all()
+    p.collide(h, delta, out)
+    p.set_contraction_config(small, 128, 16, 8, precision="fp32")
+    g, err = captured(lambda stream: p.collide(h[:small], delta[:small], out[:small]))
+    assert err is None
+    for _ in range(3):
+        out.fill_(np.nan)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        hn = h[:small].cpu().numpy()
+        bound = (p.n_dof + 32) * 2.0 ** -24 * (np.abs(hn) @ np.abs(op.T))
+        assert np.all(np.abs(out[:small].cpu().numpy() - hn @ op.T) <= bound)
