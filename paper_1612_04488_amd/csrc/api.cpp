@@ -413,10 +413,13 @@ size_t class_row_bytes(const sis_plan* p, int precision) {
 size_t sum_bytes(int precision) { return precision == SIS_PREC_FP64 ? 8 : 4; }
 
 // Cells per pass of a collision step: the class rows and one split's sums of a pass stay within
-// 2 GiB each, so that the workspace does not grow with the batch.
-int64_t pass_cells(const sis_plan* p, int64_t n_cells) {
-  const int64_t most = (int64_t(2) << 30) / (p->row_len() * 8);
-  return std::min(n_cells, std::max<int64_t>(256, most / 256 * 256));
+// 2 GiB each (the bf16 rows, of 64 entries at least, too) and all splits' sums within 4 GiB, so that the
+// workspace does not grow with the batch, and the pair arrays stay within the 256 x 256 tile's offsets.
+int64_t pass_cells(const sis_plan* p, int64_t n_cells, int precision, int splits) {
+  const int64_t row = std::max<int64_t>(p->row_len() * 8, class_row_bytes(p, precision));
+  const int64_t sums = splits * p->row_len() * static_cast<int64_t>(sum_bytes(precision));
+  const int64_t most = std::max<int64_t>(1, std::min((int64_t(2) << 30) / row, (int64_t(4) << 30) / sums));
+  return std::min(n_cells, most > 256 ? most / 256 * 256 : most);
 }
 
 void set_gemm_operands(const sis_plan* p, int precision, int tile, const double* h, const double* xref, void* xrows,
@@ -457,7 +460,7 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
                      hipStream_t s) {
   const auto key = std::make_pair(n_cells, precision);
   if (p->gemm_choice.count(key)) return SIS_OK;
-  const int64_t M = pass_cells(p, n_cells);
+  const int64_t M = pass_cells(p, n_cells, precision, 1);
   const int64_t row = p->row_len();
   sis::GemmArgs g{};
   g.M = M;
@@ -541,7 +544,7 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
   }
   p->gemm_choice[key] = best;
   // the split-K partials of the kept configuration, not of the largest candidate
-  const size_t keep = static_cast<size_t>(best.second) * M * row * sum_bytes(precision);
+  const size_t keep = static_cast<size_t>(best.second) * pass_cells(p, n_cells, precision, best.second) * row * sum_bytes(precision);
   if (ws_acc->shrink(keep) != hipSuccess) return fail(SIS_E_DEVICE, "contraction tuning: scratch reallocation failed");
   return SIS_OK;
 }
@@ -678,7 +681,7 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
                 rhs, lh,   amom,  cell_active, precision < 0 ? p->precision : precision,
                 anchor_mode, xref, accref, 0, 0};
   gemm_config(p, n_cells, c.precision, &c.tile, &c.splits);
-  int64_t pass = pass_cells(p, n_cells);
+  int64_t pass = pass_cells(p, n_cells, c.precision, c.splits);
   const size_t acc_bytes = static_cast<size_t>(c.splits) * pass * p->row_len() * sum_bytes(c.precision);
   const size_t x_bytes = own_rows(c.precision, c.tile) ? 0 : class_row_bytes(p, c.precision) * pass;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -3446,9 +3449,9 @@ sis_status sis_state_create(sis_plan_t p, sis_geom_t g, const sis_solve_opts* o,
     if (p->precision != SIS_PREC_FP64)
       if (sis_status st = tune_gemm(p, nc, p->precision, b->h, &b->ws_acc, &b->ws_x, stream)) { delete b; return st; }
     // the workspace of both, fixed here: the captured graphs refer to it
-    const int64_t pass = pass_cells(p, nc);
     for (const int prec : {static_cast<int>(SIS_PREC_FP64), p->precision}) {
       const auto [tile, splits] = p->gemm_choice[std::make_pair(nc, prec)];
+      const int64_t pass = pass_cells(p, nc, prec, splits);
       ST_TRY(b->ws_acc.ensure(static_cast<size_t>(splits) * pass * p->row_len() * sum_bytes(prec)));
       if (!own_rows(prec, tile)) ST_TRY(b->ws_x.ensure(class_row_bytes(p, prec) * pass));
     }

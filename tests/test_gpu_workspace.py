@@ -107,3 +107,68 @@ def test_capture_without_room_is_refused_cleanly():
         hn = h[:small].cpu().numpy()
         bound = (p.n_dof + 32) * 2.0 ** -24 * (np.abs(hn) @ np.abs(op.T))
         assert np.all(np.abs(out[:small].cpu().numpy() - hn @ op.T) <= bound)
+
+
+def test_passes_of_a_fixed_split_count_equal_one_pass():
+    """32 split sums of 70 001 cells of 256 unknowns are 4.6 GB: two passes (65 536 and 4465 cells), against
+    the one pass of a single split, with every argument that is addressed by the cell.  Sums of 64 products in
+    another grouping, and per-row sums of 256 terms: 1e-13 of the largest value."""
+    p = sis.Plan(8, 5.0, m_angle=2, parity=1)
+    nc, nd = 70_001, p.n_dof
+    assert 32 * nc * nd * 8 > 2 ** 32
+    h, dU = rnd(1, nc, nd), rnd(2, nc)
+    delta = rnd(3, nc).abs() + 0.5
+    flow = (torch.arange(nc, device=DEV) % 3).to(torch.int32)
+    out = []
+    for splits in (1, 32):
+        p.set_contraction_config(nc, 128, 16, splits)
+        rhs, am = torch.full_like(h, np.nan), torch.full((nc, 4), np.nan, dtype=torch.float64, device=DEV)
+        lh = torch.full((nc * nd + 1,), np.nan, dtype=torch.float64, device=DEV)[1:].reshape(nc, nd)   # 8 bytes off
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        p.collide(h, delta, rhs, dU=dU, flow=flow, project=True, lh_out=lh, amom_out=am)
+        torch.cuda.synchronize()
+        if splits == 32:
+            assert free - torch.cuda.mem_get_info()[0] <= 2 ** 32 + 2 ** 26    # the stated bound on the sums
+        out.append((rhs, lh, am))
+    for k, (a, b) in enumerate(zip(*out)):
+        assert (a - b).abs().max() <= 1e-13 * a.abs().max(), k
+
+
+def test_anchored_state_over_passes():
+    """The same through a state with FP32 iterations and FP64 anchors of two passes each: 1e-12, the sums' rounding
+    through the marches of 101 nodes."""
+    x = -0.5 + 0.5 * np.linspace(0.0, 1.0, 101) ** 2
+    x[-1] = 0.0
+    cases = 694
+    res = []
+    for splits in (1, 32):
+        p = sis.Plan(8, 5.0, m_angle=2, parity=1)
+        p.set_precision("fp32")
+        geom = sis.Geometry(p, [x] * cases, np.linspace(0.5, 5.0, cases), [1] * cases)
+        p.set_contraction_config(geom.n_cells, 128, 16, splits)
+        p.set_contraction_config(geom.n_cells, 128, 16, 1, precision="fp32")
+        s = sis.State(p, geom, eps=0.0, refresh_every=4)
+        s.step(7)                                       # anchors at iterations 0, 2 and 6
+        res.append(s.results())
+        s.close()
+    for k in ("U", "q"):
+        assert np.abs(res[0][k] - res[1][k]).max() <= 1e-12 * np.abs(res[0][k]).max(), k
+
+
+def test_wide_bf16_tile_on_a_small_grid():
+    """4^3 velocities: a class has 8 entries in bf16 rows of 64, so 2 200 000 cells have 4.5 GB of pair rows
+    where the whole matrix had 0.6; the tile's offsets hold 4 GiB."""
+    p = sis.Plan(4, 5.0, m_angle=2)
+    nc = 2_200_000
+    h, rhs = rnd(1, nc, p.n_dof), torch.full((nc, p.n_dof), np.nan, dtype=torch.float64, device=DEV)
+    delta = torch.ones(nc, dtype=torch.float64, device=DEV)
+    p.set_precision("bf16x3")
+    p.set_contraction_config(nc, 256, 32, 1, precision="bf16x3")
+    p.collide(h, delta, rhs)
+    at = torch.tensor([0, 1, 1_048_575, 1_048_576, 2_097_151, 2_097_152, nc - 1], device=DEV)
+    p.set_contraction_config(len(at), 128, 64, 1, precision="bf16x3")
+    ref = torch.full((len(at), p.n_dof), np.nan, dtype=torch.float64, device=DEV)
+    p.collide(h[at].contiguous(), delta[:len(at)], ref)
+    assert torch.equal(rhs[at], ref)                    # the same products in the same order
+    assert bool(torch.isfinite(rhs).all())
