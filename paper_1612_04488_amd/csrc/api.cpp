@@ -727,7 +727,9 @@ sis_status run_fsm_chunks(sis_plan* p, int64_t n_cells, const double* h, const d
   const sis::FsmClassDims& d = p->fsm_c;
   const int slabs = sis::fsm_slab_count(d, p->fsm_slab);
   const int64_t row = p->row_len(), nv = p->nv;
-  const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(n_cells, (int64_t(2) << 30) / (8 * row * (slabs + 1))));
+  // (and at most 65 535 cells: a launch takes fewer than 2^32 threads, up to 4096 a cell)
+  const int64_t chunk =
+      std::max<int64_t>(1, std::min<int64_t>({n_cells, int64_t(65535), (int64_t(2) << 30) / (8 * row * (slabs + 1))}));
   HIP_TRY(p->fsm_x.ensure(static_cast<size_t>(chunk * row) * 8));
   double* X = static_cast<double*>(p->fsm_x.p);
   for (int64_t c0 = 0; c0 < n_cells; c0 += chunk) {

@@ -41,3 +41,20 @@ def test_every_slab_width(n, n_pad, parity):
         p.set_fsm_slab(slab)
         assert p.fsm_info()["slab_l1"] == slab
         compare(p, 5, slab)
+
+
+def test_many_cells_of_the_smallest_grid():
+    """4^3 velocities in eight classes: 2 200 000 cells are more threads than a launch takes (2^32), although
+    their rows and sums are within the 2 GiB of a chunk."""
+    p = sis.Plan(4, 5.0, n_pad=8, m_angle=2)
+    nc = 2_200_000
+    g = torch.Generator(device=DEV).manual_seed(4)
+    h = torch.randn((nc, p.n_dof), dtype=torch.float64, device=DEV, generator=g)
+    delta = torch.rand(nc, dtype=torch.float64, device=DEV, generator=g) + 0.5
+    out = torch.full_like(h, np.nan)
+    p.collide_fsm(h, delta, out)
+    assert bool(torch.isfinite(out).all())
+    at = torch.tensor([0, 65_534, 65_535, 65_536, 131_069, 131_070, 2_097_151, 2_097_152, nc - 1], device=DEV)
+    ref = torch.empty((len(at), p.n_dof), dtype=torch.float64, device=DEV)
+    p.collide(h[at].contiguous(), delta[at].contiguous(), ref)
+    assert (out[at] - ref).abs().max() <= 1e-12 * ref.abs().max()
