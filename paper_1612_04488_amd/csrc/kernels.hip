@@ -3066,7 +3066,7 @@ bool sweep2d_by_lanes(const Sweep2DArgs& a) {
 // P23 = 2a int v2 v3 h (a = m_s / m_A; 1 for one gas).
 // A workgroup takes R cells of one species, whose values share the per-velocity tables: the
 // texture-address units are what a row by itself is bound by (three table loads to one of h).
-// 24 576 cells of 6912: 395 -> 296 us (4.6 TB/s), 4096 cells 65 -> 56.
+// 24 576 cells of 6912: 395 -> 296 us (4.6 TB/s), 4096 cells 65 -> 56 (R = 4; the launcher says where).
 template <int R>
 __global__ __launch_bounds__(256) void moments2d_kernel(int64_t n_cells, int n3, int nsp, double ms0, double ms1,
                                                         const double* __restrict__ vtab,
@@ -4331,7 +4331,13 @@ hipError_t launch_sweep2d(const Sweep2DArgs& a, hipStream_t s) {
 hipError_t launch_moments2d(int n3, int nsp, const double* mass_ratio, int64_t n_cells, const double* vtab,
                             const double* h, double w, const int32_t* cell_active, double* mom, hipStream_t s) {
   const double m0 = mass_ratio[0], m1 = nsp > 1 ? mass_ratio[1] : 1.0;
-  if (n_cells >= 2048)   // else four cells a workgroup leave compute units without one
+  // Four cells a workgroup where the rows come from HBM and are long: rows that the sweep left in the
+  // 256 MB cache come so fast that the 28 sums across lanes at the end of a workgroup decide, at few
+  // workgroups a unit.  Four against one: 3000 cells of 2048 29 against 21 us, 24 576 129 against 110; of 4096
+  // 5929 cells 51 against 43, 8190 66 against 68, 24 576 154 against 199; of 6912 2970 cells 41 against 35, 4096
+  // 48 against 57; 2025 cells of 13 824 49 against 59.
+  const double values = static_cast<double>(n_cells) * nsp * n3;
+  if (n3 >= 5120 ? values >= 25e6 : n3 >= 4000 && values >= 33e6)
     hipLaunchKernelGGL(moments2d_kernel<4>, dim3(static_cast<unsigned>((n_cells + 3) / 4), nsp), dim3(256), 0, s, n_cells,
                        n3, nsp, m0, m1, vtab, h, w, cell_active, mom);
   else

@@ -74,8 +74,8 @@ def test_sweep_forms(kind, copies):
 
 @pytest.mark.parametrize("species,n1,n2", [(1, 47, 44), (1, 46, 45), (2, 50, 43), (2, 9, 5)])
 def test_moments_of_the_swept_cells(species, n1, n2):
-    """2068, 2070, 2150 cells (four cells a workgroup, 0 and 2 left over) and 45 (one): sums of n^3 terms in
-    any order, against the sums of their magnitudes."""
+    """2068, 2070, 2150 cells and 45, short rows (one cell a workgroup): sums of n^3 terms in any order, against
+    the sums of their magnitudes."""
     n, l_v = 6, 4.0
     mix = dict(masses=(1.0, 2.0), diameters=(1.0, 0.8), chi=(0.4, 0.6), m_rho=3) if species == 2 else None
     p = sis.Plan(n, l_v, m_angle=2, mixture=mix)
@@ -97,3 +97,30 @@ def test_moments_of_the_swept_cells(species, n1, n2):
             ref = np.array([vg.integrate(fk * x) for x in h[:, s]])
             size = np.array([vg.integrate(np.abs(fk * x)) for x in h[:, s]])
             assert np.all(np.abs(mom[:, s, k] - ref) <= (n ** 3 + 16) * np.finfo(float).eps * size), (s, k)
+
+
+@pytest.mark.parametrize("n,parity,species,n1,n2", [(24, 1, 1, 77, 47), (24, 1, 1, 47, 76), (16, 0, 1, 74, 109), (16, 0, 2, 37, 109),
+                                                    (16, 0, 1, 74, 108)])
+def test_moments_of_long_rows(n, parity, species, n1, n2):
+    """Rows of 6912 and 4096 values at the size from which four cells share a workgroup: 3619 cells (three left over),
+    3572 (one cell a workgroup); 8066 (two left over), 4033 of two species (one left over), 7992 (one a workgroup)."""
+    l_v = 5.0
+    mix = dict(masses=(1.0, 2.0), diameters=(1.0, 0.8), chi=(0.4, 0.6), m_rho=3) if species == 2 else None
+    p = sis.Plan(n, l_v, m_angle=2, parity=parity, mixture=mix)
+    geom = sis.Geometry2D(p, "duct", [(faces(n1), faces(n2), None)], [0.7], [1])
+    nc, n3 = n1 * n2, p.n_dof // species
+    g = torch.Generator(device=DEV).manual_seed(n2)
+    rhs = torch.randn((nc, p.n_dof), dtype=torch.float64, device=DEV, generator=g)
+    h, mom = torch.zeros_like(rhs), torch.full((nc, species, 8), np.nan, dtype=torch.float64, device=DEV)
+    sis.transport_sweep(p, geom, rhs, h, mom)
+    torch.cuda.synchronize()
+    vg = VelocityGrid(n, l_v)
+    v1, v2, v3 = (np.broadcast_to(a, (n, n, n)).astype(float)[:, :, n // 2 if parity else 0:].reshape(-1) for a in (vg.V1, vg.V2, vg.V3))
+    w = (2 * l_v / n) ** 3 * (2 if parity else 1)
+    h, mom = h.cpu().numpy().reshape(nc, species, n3), mom.cpu().numpy().reshape(nc, species, 8)
+    for s in range(species):
+        ms = (1.0, 2.0)[s]
+        f = w * np.stack([v3, (ms * (v1 ** 2 + v2 ** 2 + v3 ** 2) - 2.5) * v3, v3 * (2 * v1 ** 2 - 1), 2 * v1 * v2 * v3,
+                          v3 * (2 * v2 ** 2 - 1), 2 * ms * v1 * v3, 2 * ms * v2 * v3], 1)
+        ref, size = h[:, s] @ f, np.abs(h[:, s]) @ np.abs(f)
+        assert np.all(np.abs(mom[:, s, :7] - ref) <= (n3 + 16) * np.finfo(float).eps * size), s
