@@ -3053,13 +3053,18 @@ __global__ __launch_bounds__(64 * kLaneWaves) void sweep2d_lanes_kernel(
   }
 }
 
-// Few cases: up to six of the lanes kernel's waves a compute unit.  (Four, one a SIMD: 0.53 of the
-// rows kernel's time; ten: 1.14.)
+// Few cases: up to six of the lanes kernel's waves a compute unit, fewer for the widths whose
+// workgroups then share units unevenly.  Time against the rows kernel over 12, 40 and 100 rows at
+// 16^3 and 24^3 (least and greatest): three and more waves a workgroup 0.45-1.00 up to six waves a
+// unit (1.2-1.7 beyond for three), but five-wave ones (65 to 80 columns) 0.50-0.69 at five and
+// 0.87-1.26 at six; two-wave ones of 17 to 20 columns 0.72-0.95 at two and 0.85-1.10 at three, of 24
+// to 32 columns 0.68-0.94 up to three and a half and 1.05-1.11 at four to six; one wave 0.45-1.03.
 bool sweep2d_by_lanes(const Sweep2DArgs& a) {
   const int hn = a.n / 2;
   const int64_t quads = static_cast<int64_t>(hn) * hn * a.d3;
   const int W = (a.max_n2 + kLaneWaveCols - 1) / kLaneWaveCols;
-  return (quads + kLaneQuads - 1) / kLaneQuads * a.n_cases * a.nsp * (a.quad_split ? 4 : 1) * W <= 6 * 256;
+  const int half_waves = W == 2 ? (a.max_n2 > 24 ? 7 : 4) : W == 5 ? 10 : 12;   // allowed a unit, twice
+  return (quads + kLaneQuads - 1) / kLaneQuads * a.n_cases * a.nsp * (a.quad_split ? 4 : 1) * W * 2 <= half_waves * 256;
 }
 
 // Per (cell, species) row: U3, q3 = int (a v^2 - 5/2) v3 h, G1, G12, G2, P13 = 2a int v1 v3 h,

@@ -32,6 +32,10 @@ def cross_sections(kind):
                 (faces(5), faces(17), None)]
     if kind == "wide":      # 65 and 112 columns: five and seven waves
         return [(faces(6), faces(65), None), (faces(9), faces(112), None)]
+    if kind == "two waves":
+        return [(faces(8), faces(20), None), (faces(11), faces(17), None)]
+    if kind == "five waves":
+        return [(faces(7), faces(70), None)]
     out = []
     for n1, n2 in ((18, 20), (16, 16), (23, 31)):
         mask = np.zeros((n1, n2), bool)
@@ -124,3 +128,10 @@ def test_moments_of_long_rows(n, parity, species, n1, n2):
                           v3 * (2 * v2 ** 2 - 1), 2 * ms * v1 * v3, 2 * ms * v2 * v3], 1)
         ref, size = h[:, s] @ f, np.abs(h[:, s]) @ np.abs(f)
         assert np.all(np.abs(mom[:, s, :7] - ref) <= (n3 + 16) * np.finfo(float).eps * size), s
+
+
+@pytest.mark.parametrize("kind,copies", [("two waves", 16), ("two waves", 17), ("five waves", 32), ("five waves", 33)])
+def test_sweep_forms_at_the_widths_limits(kind, copies):
+    """The last batch that goes by lanes and the first that goes by rows, for workgroups of two and of five waves
+    (8^3 velocities: 8 groups of quadruples a case)."""
+    test_sweep_forms(kind, copies)
