@@ -1767,12 +1767,15 @@ __device__ __forceinline__ void finish_class_row(const FinishArgs& a, int64_t ro
   }
 }
 
+// splits whose loads are in flight together
+constexpr int finish_splits(int logb, bool deep) { return (logb == 1 ? 4 : logb == 2 ? 2 : 1) * (deep ? 2 : 1); }
+
 // pairs: every row, and the class rows, in 16-byte pairs (lh may be offset by 8 bytes)
 // NT threads a row: 256, or more where there are no more rows than compute units; DEEP: more splits in
 // flight, at the price of waves a SIMD that few rows do not have.
 template <int LOGB, class A, int NT, bool DEEP>
 __global__ __launch_bounds__(NT) void finish_class_kernel(FinishArgs a) {
-  constexpr int UZ = (LOGB == 1 ? 4 : LOGB == 2 ? 2 : 1) * (DEEP ? 2 : 1);
+  constexpr int UZ = finish_splits(LOGB, DEEP);
   const int64_t row = blockIdx.x;
   if (a.active && !a.active[row / a.nsp]) return;
   double m[9];
@@ -4239,13 +4242,19 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(a.n_cells));
-  // Few rows leave most compute units without one, and a row's orbits are then a chain of loads:
-  // 1024 threads a row (512 of the 161-register form; 104 rows of 13 824: 43 -> 33 us).  With more rows than
-  // units 256 stream as well, and rows of 256 orbits or pairs at most have no use for more.
-  const bool wide = a.n_cells <= 256 && a.sym.nvb > 512;
-  // Short rows, few of them, have as many splits as it takes to fill the chip, and a round of loads
-  // for each four of them is what they wait for (17 rows of 1024, eight splits: 7.5 -> 6.1 us).
-  const bool deep = a.n_cells <= 256;
+  const int logb = a.sym.logb;
+  const bool few = a.n_cells <= 256;
+  // Few rows leave most compute units without one, and a row's orbits are then a chain of loads: 1024
+  // threads a row (512 of the 161-register form; 104 rows of 13 824: 43 -> 33 us).  With more rows than
+  // units 256 stream as well.  Of two classes, whose orbits go in pairs, rows of 1728 orbits gain 4%
+  // (17 rows) and of 1000 lose 2 to 7%; of eight, 17 rows of 1728 gain 1% and of 1000 lose 2%; of four,
+  // rows of 512 to 4096 gain 1 to 8%.
+  const bool wide = few && a.sym.nvb > (logb == 1 ? 1536 : logb == 2 ? 512 : 1024);
+  // Short rows, few of them, have as many splits as it takes to fill the chip, and the rounds of loads
+  // are what they wait for (17 rows of 1024, eight splits: 7.5 -> 6.1 us) -- where more at once are
+  // fewer rounds: four splits of two classes are one round of four and would be four of one (0.7 us).
+  auto rounds = [&](bool deep) { return a.splits / finish_splits(logb, deep) + a.splits % finish_splits(logb, deep); };
+  const bool deep = few && logb && rounds(true) < rounds(false);
 #define SIS_FINISH_(LOGB, A)                                                                             \
   if (wide) hipLaunchKernelGGL((finish_class_kernel<LOGB, A, LOGB == 2 ? 512 : 1024, false>), grid,      \
                                dim3(LOGB == 2 ? 512 : 1024), 0, s, a);                                   \

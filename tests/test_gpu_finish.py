@@ -56,3 +56,25 @@ def test_many_splits_of_few_rows(n, parity, splits):
         out[nc] = (r, am)
     assert torch.equal(out[few][0], out[many][0][:few])
     assert torch.equal(out[few][1], out[many][1][:few])
+
+
+@pytest.mark.parametrize("n,parity", [(20, 2), (24, 2), (20, 0), (22, 0), (18, 1)])
+@pytest.mark.parametrize("splits", [1, 2, 3, 4, 6, 8])
+def test_rows_and_splits_at_the_forms_limits(n, parity, splits):
+    """1000 and 1728 orbits of two classes, 1000 and 1331 of eight, 729 of four (256 threads below, more above), and
+    split counts of one round or less with more splits at once: the same sums in the same order as in a larger
+    batch, element by element."""
+    p = sis.Plan(n, 5.0, m_angle=2, parity=parity)
+    few, many = 5, 300
+    g = torch.Generator(device=DEV).manual_seed(splits)
+    h = torch.randn((many, p.n_dof), dtype=torch.float64, device=DEV, generator=g)
+    delta = torch.rand(many, dtype=torch.float64, device=DEV, generator=g) + 0.5
+    out = {}
+    for nc in (few, many):
+        p.set_contraction_config(nc, 128, 16, splits)
+        r = torch.full((nc, p.n_dof), np.nan, dtype=torch.float64, device=DEV)
+        am = torch.full((nc, 4), np.nan, dtype=torch.float64, device=DEV)
+        p.collide(h[:nc], delta[:nc], r, amom_out=am)
+        out[nc] = (r, am)
+    assert torch.equal(out[few][0], out[many][0][:few])
+    assert (out[few][1] - out[many][1][:few]).abs().max() <= 1e-12 * out[many][1].abs().max()
