@@ -1940,8 +1940,9 @@ __device__ __forceinline__ void sweep1d_block(const SweepArgs& a, int bx, int cs
   in.run(h1, h2, r_in, c_in, sh);
 }
 
-__global__ __launch_bounds__(kSweepNT) void sweep1d_kernel(SweepArgs a) {
-  sweep1d_block<kSweepNT, kSweepAhead>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+template <int NT>
+__global__ __launch_bounds__(NT) void sweep1d_kernel(SweepArgs a) {
+  sweep1d_block<NT, kSweepAhead>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Calls f(v1, v2, v3, h) for every unknown of row `row` (n3 values): in 16-byte pairs for
@@ -4274,8 +4275,17 @@ hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
 
 hipError_t launch_sweep1d(const SweepArgs& a, hipStream_t s) {
   const int half = a.n3 / 2;
-  dim3 grid((half + kSweepNT - 1) / kSweepNT, a.n_cases, a.nsp);
-  hipLaunchKernelGGL(sweep1d_kernel, grid, dim3(kSweepNT), 0, s, a);
+  // A wave a workgroup, but where there are more than two waves a SIMD: then bandwidth counts, and rows
+  // whose halves are not whole 128-byte lines leave lines shared by workgroups (of other XCDs) between
+  // every 64 velocities.  256 cases of 401 nodes, two species of 432 velocities: 453 -> 329 us with four
+  // waves, 404 with the form before this one; whole lines 2-10% slower with four, and halves that fill
+  // less than four fifths of them up to 47%.
+  const int waves = (half + kSweepNT - 1) / kSweepNT, fours = (half + 255) / 256;
+  const bool full = static_cast<int64_t>(waves) * a.n_cases * a.nsp >= 2 * 1024;
+  if (full && half % 16 != 0 && half * 5 >= fours * 256 * 4)
+    hipLaunchKernelGGL(sweep1d_kernel<256>, dim3(fours, a.n_cases, a.nsp), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(sweep1d_kernel<kSweepNT>, dim3(waves, a.n_cases, a.nsp), dim3(kSweepNT), 0, s, a);
   return hipGetLastError();
 }
 
