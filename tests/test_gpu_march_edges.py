@@ -1,4 +1,6 @@
-"""The planar sweep of many cases on rows whose halves are not whole cache lines, which takes four waves a workgroup.
+"""The serial marches at the edges they are built with: the planar sweep takes 24 nodes a chunk, the tube sweep 62
+columns a strip (th nodes in pairs of passes: 124), with loads 24 diagonals ahead; and the planar sweep of many cases
+on rows whose halves are not whole cache lines, which takes four waves a workgroup.
 
 Tolerances as in the other tests of the marches: stable recurrences of a few roundings a node, 1e-11."""
 import functools
@@ -11,9 +13,28 @@ torch = pytest.importorskip("torch")
 from oracle import transport as tr
 from oracle.velocity import VelocityGrid
 from paper_1612_04488_amd import inputs, sis
-from test_gpu_marches import DEV, TOL, dev, rel
+from test_gpu_marches import DEV, TOL, dev, rel, test_mixture_marches, test_planar_marches, test_tube_marches
 
 pytestmark = pytest.mark.gpu
+march_planar, march_mixture, march_tube = test_planar_marches, test_mixture_marches, test_tube_marches
+del test_planar_marches, test_mixture_marches, test_tube_marches
+
+
+@pytest.mark.parametrize("sections", [23, 24, 25, 47, 48, 49, 72])
+def test_planar_chunks(sections):
+    march_planar(sections)
+
+
+@pytest.mark.parametrize("sections", [23, 24, 25, 48, 49])
+def test_mixture_chunks(sections):
+    march_mixture(sections)
+
+
+@pytest.mark.parametrize("n_th,n_vr,n_vz,nodes", [(122, 2, 2, 9), (124, 2, 2, 9), (124, 2, 2, 25), (124, 2, 4, 70), (126, 2, 2, 24),
+                                                  (248, 2, 2, 7), (250, 2, 2, 7), (20, 2, 2, 23), (20, 2, 2, 24), (20, 2, 2, 25),
+                                                  (20, 2, 2, 26), (6, 2, 2, 48), (6, 2, 2, 49)])
+def test_tube_strips(n_th, n_vr, n_vz, nodes):
+    march_tube(n_th, n_vr, n_vz, nodes)
 
 
 @functools.lru_cache(maxsize=None)

@@ -1,6 +1,6 @@
-"""The serial marches (planar sweep, tube sweep, velocity equations) at the edges of their
-chunks and strips against the oracle: node counts around a chunk of the sweep (8) and of
-the velocity equation (256), th columns around a strip of the tube sweep (64).
+"""The serial marches (planar sweep, tube sweep, velocity equations) against the oracle: node
+counts around a group of the sweep (8 nodes) and a chunk of the velocity equation (256), and
+th columns of one strip of the tube sweep (62 a pass) and two.
 
 The recurrences are stable (positive upwind weights), so n steps of a few roundings each
 keep n * 1e-15 relative: 1e-11 covers the largest here (300 nodes + 66 columns) with the
