@@ -172,3 +172,16 @@ def test_wide_bf16_tile_on_a_small_grid():
     p.collide(h[at].contiguous(), delta[:len(at)], ref)
     assert torch.equal(rhs[at], ref)                    # the same products in the same order
     assert bool(torch.isfinite(rhs).all())
+
+
+@pytest.mark.parametrize("nc", [8191, 8192, 16_382, 16_383])
+def test_fixed_workspace_at_the_edges_of_its_passes(nc):
+    """8191 cells of 512 unknowns fit the fixed workspace (8 bytes of class rows and of sums an unknown): one pass, two
+    and three, of equal size or of whole tiles."""
+    p = sis.Plan(8, 5.0, m_angle=2)
+    h, delta = rnd(nc, nc, p.n_dof), rnd(nc + 1, nc).abs() + 0.5
+    rhs, ref = torch.full_like(h, np.nan), torch.full_like(h, np.nan)
+    p.set_contraction_config(nc, 128, 16, 1)
+    p.collide_noalloc(h, delta, rhs)
+    p.collide(h, delta, ref)
+    assert torch.equal(rhs, ref)
