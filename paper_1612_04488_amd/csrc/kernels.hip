@@ -4247,10 +4247,12 @@ hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
   const bool few = a.n_cells <= 256;
   // Few rows leave most compute units without one, and a row's orbits are then a chain of loads: 1024
   // threads a row (512 of the 161-register form; 104 rows of 13 824: 43 -> 33 us).  With more rows than
-  // units 256 stream as well.  Of two classes, whose orbits go in pairs, rows of 1728 orbits gain 4%
-  // (17 rows) and of 1000 lose 2 to 7%; of eight, 17 rows of 1728 gain 1% and of 1000 lose 2%; of four,
-  // rows of 512 to 4096 gain 1 to 8%.
-  const bool wide = few && a.sym.nvb > (logb == 1 ? 1536 : logb == 2 ? 512 : 1024);
+  // units 256 stream as well.  Four classes gain 1 to 11% at every length.  Two classes, by orbits or pairs
+  // of them a row: 864 pairs 0 to 4%, 1331 orbits 3 to 7%, 729 orbits 1% without the projection and -8% with
+  // it, 500 pairs -2 to -7%.  Eight, against the form with more splits in flight: 1331 orbits 1 to 2%,
+  // 1000 -2%.
+  const int items = a.sym.pairs ? a.sym.nvb / 2 : a.sym.nvb;
+  const bool wide = few && (logb == 1 ? items > (a.project ? 768 : 512) : logb == 2 || a.sym.nvb > 1024);
   // Short rows, few of them, have as many splits as it takes to fill the chip, and the rounds of loads
   // are what they wait for (17 rows of 1024, eight splits: 7.5 -> 6.1 us) -- where more at once are
   // fewer rounds: four splits of two classes are one round of four and would be four of one (0.7 us).
@@ -4259,7 +4261,8 @@ hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
 #define SIS_FINISH_(LOGB, A)                                                                             \
   if (wide) hipLaunchKernelGGL((finish_class_kernel<LOGB, A, LOGB == 2 ? 512 : 1024, false>), grid,      \
                                dim3(LOGB == 2 ? 512 : 1024), 0, s, a);                                   \
-  else if (deep) hipLaunchKernelGGL((finish_class_kernel<LOGB, A, 256, true>), grid, dim3(256), 0, s, a); \
+  else if (LOGB != 2 && deep)                                                                            \
+    hipLaunchKernelGGL((finish_class_kernel<LOGB, A, 256, LOGB != 2>), grid, dim3(256), 0, s, a);        \
   else hipLaunchKernelGGL((finish_class_kernel<LOGB, A, 256, false>), grid, dim3(256), 0, s, a)
 #define SIS_FINISH(LOGB) if (a.acc_f32) { SIS_FINISH_(LOGB, float); } else { SIS_FINISH_(LOGB, double); }
   switch (a.sym.logb) {

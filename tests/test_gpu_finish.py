@@ -58,12 +58,12 @@ def test_many_splits_of_few_rows(n, parity, splits):
     assert torch.equal(out[few][1], out[many][1][:few])
 
 
-@pytest.mark.parametrize("n,parity", [(20, 2), (24, 2), (20, 0), (22, 0), (18, 1)])
+@pytest.mark.parametrize("n,parity", [(20, 2), (18, 2), (24, 2), (20, 0), (22, 0), (10, 1), (18, 1)])
 @pytest.mark.parametrize("splits", [1, 2, 3, 4, 6, 8])
 def test_rows_and_splits_at_the_forms_limits(n, parity, splits):
-    """1000 and 1728 orbits of two classes, 1000 and 1331 of eight, 729 of four (256 threads below, more above), and
-    split counts of one round or less with more splits at once: the same sums in the same order as in a larger
-    batch, element by element."""
+    """500 pairs, 729 orbits and 864 pairs of two classes, 1000 and 1331 orbits of eight (256 threads below, 1024
+    above), 125 and 729 of four (512), and split counts of one round or less with more splits at once: the same
+    sums in the same order as in a larger batch, element by element."""
     p = sis.Plan(n, 5.0, m_angle=2, parity=parity)
     few, many = 5, 300
     g = torch.Generator(device=DEV).manual_seed(splits)
