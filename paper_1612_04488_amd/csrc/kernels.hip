@@ -2092,8 +2092,9 @@ __device__ __forceinline__ void diffusion1d_case(const DiffusionArgs& a, int cs)
       __syncthreads();
     }
   }
+  if (!a.state) return;   // (no flow rates: the sums are a third of a short march)
   block_sum<2>(flow, red);
-  if (threadIdx.x == 0 && a.state) {
+  if (threadIdx.x == 0) {
     const double M = 2.0 * flow[0], Q = 2.0 * flow[1];
     double* st = a.state + cs * 4;
     const double dM = fabs(M - st[0]) / fmax(fabs(M), 1e-300);
@@ -2233,8 +2234,9 @@ __device__ __forceinline__ void diffusion1d_mix_case(const DiffusionArgs& a, int
       __syncthreads();
     }
   }
+  if (!a.state) return;
   block_sum<4>(flow, red);
-  if (threadIdx.x == 0 && a.state) {
+  if (threadIdx.x == 0) {
     double* st = a.state + cs * 6;  // M_A, M_B, Q_A, Q_B, residual, iterations
     double res = 0.0;
     bool bad = false;
@@ -3891,9 +3893,10 @@ __global__ __launch_bounds__(kDiffChunk) void diffusion_tube_kernel(TubeDiffArgs
       flow[1] += a.tw[node] * qn;
     }
   }
+  if (!a.state) return;
   block_sum<2>(flow, red);
   const double M = flow[0], Q = flow[1];
-  if (threadIdx.x == 0 && a.state) {
+  if (threadIdx.x == 0) {
     double* st = a.state + cs * 4;
     const double dM = fabs(M - st[0]) / fmax(fabs(M), 1e-300);
     const double dQ = fabs(Q - st[1]) / fmax(fabs(Q), 1e-300);
