@@ -881,7 +881,6 @@ sis::TubeDiffArgs tube_diff_args(sis_plan* p, sis_geom* g, const double* mom, co
 sis::Diff2DArgs diff2d_args(sis_plan* p, sis_geom* g, const double* mom, const double* amom, double N) {
   sis::Diff2DArgs a{};
   a.n_cases = g->n_cases;
-  a.n_grid = g->t2.n_grid;
   a.n2 = g->d_n2;
   a.grid_off = g->d_goff;
   a.dflag = g->d_dflag;
@@ -1436,7 +1435,7 @@ sis_status create_geometry_2d(sis_plan* p, const sis_geometry_desc* d, hipStream
   G2_TRY(upload(&g->delta_cell, dcell, stream));
   G2_TRY(upload(&g->flow_cell, fcell, stream));
   G2_TRY(upload(&g->case_of_cell, t.cell_case, stream));
-  G2_TRY(dmalloc(&g->work, static_cast<size_t>(t.n_grid) * sis::kDiffWork * p->nsp));
+  if (p->nsp == 1) G2_TRY(dmalloc(&g->work, static_cast<size_t>(t.n_grid) * sis::kDiffWork));   // CG
   G2_TRY(upload(&g->have_x, std::vector<int32_t>(d->n_cases, 0), stream));
   G2_TRY(upload(&g->cg_iters, std::vector<int32_t>(d->n_cases, 0), stream));
   G2_TRY(hipStreamSynchronize(stream));

@@ -251,7 +251,8 @@ struct Sweep2DArgs {
   int max_n2;                // largest n2 over the cases
 };
 hipError_t launch_sweep2d(const Sweep2DArgs& a, hipStream_t s);
-// Kernel form launch_sweep2d takes: 1 sweep2d_rows_kernel (max_n2 <= 128 and h under 2 GiB),
+// Kernel form launch_sweep2d takes: 1 sweep2d_rows_kernel or, for few cases, sweep2d_lanes_kernel
+// (max_n2 <= 128 and h under 2 GiB),
 // else for anti-diagonals of up to max_diag cells 2 sweep2d_pipelined_kernel (max_diag <= 192)
 // or 3 sweep2d_kernel.
 int sweep2d_form(int max_diag, int max_n2, int64_t row_bytes_total);
@@ -262,7 +263,6 @@ hipError_t launch_moments2d(int n3, int nsp, const double* mass_ratio, int64_t n
 
 struct Diff2DArgs {
   int n_cases;
-  int64_t n_grid;            // grid cells of all cases (species workspace stride)
   const int32_t* n2;
   const int64_t* grid_off;
   const int8_t* dflag;
@@ -284,7 +284,7 @@ struct Diff2DArgs {
   int nsp;
   double chi[2], mass_ratio[2], Ns[2], cUs[2], cqs[2];
   double flow_factor;        // sqrt(m / m_A) (mixtures)
-  double* work;              // [species][grid][kDiffWork]
+  double* work;              // [grid][kDiffWork] (null for mixtures, which have no CG)
   int32_t* have_x;           // [n_cases]: warm start available
   double tol;
   int max_iter;
@@ -316,8 +316,8 @@ struct Diff2DArgs {
   double* yvec;              // [nsp * unknowns]
 };
 constexpr int kInverseGroup = 8;
-// workspace per (species, grid cell): Uh G1 G12 G2 A1 A2 | CG: x r p Ap | P_B13 P_B23
-constexpr int kDiffWork = 12;
+// CG workspace per grid cell: Uh G1 G12 G2 A1 A2 | x r p Ap
+constexpr int kDiffWork = 10;
 // CG kernel for cases without an inverse, then (if a.direct) right sides, y = A^-1 b, outputs
 hipError_t launch_diffusion2d(const Diff2DArgs& a, hipStream_t s);
 // Newton-Schulz helpers (plan time): per-block sum of squares of I - P into part[blocks];

@@ -3169,50 +3169,37 @@ __device__ inline void block_sum_big(double (&v)[K], double* sh /* >= 16*K */) {
   __syncthreads();
 }
 
-// Workspace of species s of case cs: per grid cell Uh G1 G12 G2 A1 A2 (x r p Ap for CG)
-// and, for mixtures, P_B13 P_B23 (species B's shear stresses, in every species' slots).
-__device__ inline double* d2_work(const Diff2DArgs& a, int cs, int s) {
-  return a.work + (static_cast<int64_t>(s) * a.n_grid + a.grid_off[cs]) * kDiffWork;
-}
+// Workspace of case cs for CG (one gas): per grid cell Uh G1 G12 G2 A1 A2, x r p Ap.
+__device__ inline double* d2_work(const Diff2DArgs& a, int cs) { return a.work + a.grid_off[cs] * kDiffWork; }
 
-__device__ void d2_fill_work(const Diff2DArgs& a, int cs, int s, double* W, int ng, bool warm) {
+__device__ void d2_fill_work(const Diff2DArgs& a, int cs, double* W, int ng, bool warm) {
   const int64_t g0 = a.grid_off[cs];
-  const double del = a.delta_case[cs];
-  const int nsp = a.nsp;
-  const double chi = a.chi[s], Nd = a.Ns[s] * del;
+  const double Nd = a.Ns[0] * a.delta_case[cs];
   for (int g = threadIdx.x; g < ng; g += blockDim.x) {
     const int cell = a.gcell[g0 + g];
     double* w = W + static_cast<int64_t>(g) * kDiffWork;
     if (cell >= 0) {
-      const int64_t row = static_cast<int64_t>(cell) * nsp + s;
-      const double* m = a.mom + row * 8;
-      w[0] = m[0] / chi; w[1] = m[2]; w[2] = m[3]; w[3] = m[4];
+      const double* m = a.mom + static_cast<int64_t>(cell) * 8;
+      w[0] = m[0] / a.chi[0]; w[1] = m[2]; w[2] = m[3]; w[3] = m[4];
       if (a.amom) {
-        const double* am = a.amom + row * 4;
+        const double* am = a.amom + static_cast<int64_t>(cell) * 4;
         w[4] = am[0] + Nd * am[1];
         w[5] = am[2] + Nd * am[3];
       } else {
         w[4] = 0.0; w[5] = 0.0;
       }
       if (!warm) w[6] = w[0];
-      if (nsp == 2) {
-        const double* mb = a.mom + (static_cast<int64_t>(cell) * 2 + 1) * 8;
-        w[10] = mb[5];
-        w[11] = mb[6];
-      } else {
-        w[10] = 0.0; w[11] = 0.0;
-      }
     } else {
       for (int k = 0; k < 6; ++k) w[k] = 0.0;
       w[6] = 0.0;
-      w[10] = 0.0; w[11] = 0.0;
     }
     w[7] = 0.0; w[8] = 0.0; w[9] = 0.0;
   }
 }
 
-// The fields of that workspace at grid cell g of a case (0 .. 5, 10, 11): as filled, or straight
-// from the moments (the inverse form needs them once, and its cells are then independent).
+// The fields 0 .. 5 of that workspace at grid cell g of a case: as filled, or straight from the
+// moments (the inverse form needs them once, and its cells are then independent; there 10 and 11 are the
+// shear stresses P_B13, P_B23 of a mixture's species B).
 struct D2Work {
   const double* W;
   __device__ double operator()(int g, int f) const { return W[static_cast<int64_t>(g) * kDiffWork + f]; }
@@ -3296,7 +3283,7 @@ __device__ void d2_outputs(const Diff2DArgs& a, int cs, int ng, const double* us
   const int nsp = a.nsp;
   double fr[4] = {0.0, 0.0, 0.0, 0.0};   // (M, Q) per species
   for (int s = 0; s < nsp; ++s) {
-    const double* W = d2_work(a, cs, s);
+    const double* W = INVERSE ? nullptr : d2_work(a, cs);
     const int64_t voff = nsp * a.uoff[cs] + static_cast<int64_t>(s) * a.n_unknown[cs];
     for (int g = threadIdx.x; g < ng; g += blockDim.x) {
       const int64_t G = g0 + g;
@@ -3359,9 +3346,9 @@ __global__ __launch_bounds__(kD2Threads) void diffusion2d_kernel(Diff2DArgs a) {
   const int ng = static_cast<int>(a.grid_off[cs + 1] - g0);
   const double del = a.delta_case[cs];
   const bool pois = a.flow_case[cs] == 1;
-  double* W = d2_work(a, cs, 0);
+  double* W = d2_work(a, cs);
   const bool warm = a.have_x && a.have_x[cs];
-  d2_fill_work(a, cs, 0, W, ng, warm);
+  d2_fill_work(a, cs, W, ng, warm);
   __syncthreads();
   int it = 0;
   if (a.sis) {
