@@ -180,7 +180,9 @@ typedef struct {
 
 /* Build the tables on the host (threads) and assemble the operator on the
  * current device with `stream`.  Synchronous.  Owns 8 to 12 n_dof^2 bytes of
- * device memory plus tables.                                                 */
+ * device memory plus tables: the matrix and, where the device has room for them, the
+ * blocks.  A plan without blocks applies the matrix (FP64 only: the low precisions
+ * are made from the blocks, SIS_E_OOM).                                     */
 sis_status sis_plan_create(const sis_velocity_desc* desc, hipStream_t stream, sis_plan_t* out);
 sis_status sis_plan_destroy(sis_plan_t plan);
 sis_status sis_plan_query(sis_plan_t plan, sis_plan_info* out);
@@ -304,8 +306,9 @@ sis_status sis_geometry_diffusion_info(sis_geom_t geom, int32_t* n_inverse, int3
  * (correction h_a += dU_a 2 (m_a/m_A) v3 f_a; the correction of both species
  * enters L+ of each), amom_out is [n_cells][2][4]; S_a = v3 f_a for
  * Poiseuille, 0 otherwise; project must be 0.
- * The class rows and split-K sums go to a workspace of the plan that grows on demand, which it
- * cannot while `stream` is capturing: a captured call takes what earlier calls have made room for
+ * The class rows and split-K sums go to a workspace of the plan that grows on demand; where the
+ * device has no room for it FP64 applies the whole matrix in place.  It cannot grow while `stream` is
+ * capturing: a captured call takes what earlier calls have made room for
  * (fewer splits, then the tile without class rows, then passes of at least 256 cells).  With less
  * than that FP64, and the bf16 forms fixed to the 32-row tile with one split, apply the whole
  * matrix in FP64, in place and at 2 to 8 times the operations; the others return

@@ -459,7 +459,7 @@ void set_gemm_operands(const sis_plan* p, int precision, int tile, const double*
 sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* h, Scratch* ws_acc, Scratch* ws_x,
                      hipStream_t s) {
   const auto key = std::make_pair(n_cells, precision);
-  if (p->gemm_choice.count(key)) return SIS_OK;
+  if (p->gemm_choice.count(key) || !p->opb) return SIS_OK;
   const int64_t M = pass_cells(p, n_cells, precision, 1);
   const int64_t row = p->row_len();
   sis::GemmArgs g{};
@@ -658,6 +658,25 @@ sis_status collide_pass(sis_plan* p, const CollideArgs& c, int64_t c0, int64_t n
   return SIS_OK;
 }
 
+// The step by the whole matrix in FP64, whose sums are written over the right side: no workspace.
+sis_status collide_whole(sis_plan* p, const CollideArgs& c, int64_t n_cells, hipStream_t s) {
+  sis::GemmArgs g{};
+  g.X = c.h;
+  g.op64 = p->op;
+  g.acc = c.rhs;
+  g.M = n_cells;
+  g.N = g.K = p->ndof;
+  g.splits = 1;
+  g.tile = n_cells >= 256 ? 0 : 1;
+  HIP_TRY(sis::launch_gemm(g, s));
+  sis::FinishArgs f = finish_args(p, n_cells, c.h, c.dU, c.delta, c.flow, c.project, c.rhs, c.lh, c.amom, c.cell_active,
+                                  0, nullptr, nullptr);
+  f.splits = 1;
+  f.acc = c.rhs;
+  HIP_TRY(sis::launch_finish(f, s));
+  return SIS_OK;
+}
+
 sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const double* dU,
                        const double* delta, const int32_t* flow, int project, double* rhs,
                        double* lh, double* amom, const int32_t* cell_active, hipStream_t s,
@@ -680,6 +699,7 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
   CollideArgs c{h,   dU,   delta, flow,        project,
                 rhs, lh,   amom,  cell_active, precision < 0 ? p->precision : precision,
                 anchor_mode, xref, accref, 0, 0};
+  if (!p->opb) return collide_whole(p, c, n_cells, s);   // (a plan without blocks is FP64)
   gemm_config(p, n_cells, c.precision, &c.tile, &c.splits);
   int64_t pass = pass_cells(p, n_cells, c.precision, c.splits);
   const size_t acc_bytes = static_cast<size_t>(c.splits) * pass * p->row_len() * sum_bytes(c.precision);
@@ -689,27 +709,18 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
   const bool capturing = cs != hipStreamCaptureStatusNone;
   const bool in_place = c.precision == SIS_PREC_FP64 || (own_rows(c.precision, c.tile) && c.splits == 1);
   if (!capturing) {
-    HIP_TRY(ws_acc->ensure(acc_bytes));
-    HIP_TRY(ws_x->ensure(x_bytes));
+    hipError_t e = ws_acc->ensure(acc_bytes);
+    if (e == hipSuccess) e = ws_x->ensure(x_bytes);
+    if (e == hipErrorOutOfMemory && c.precision == SIS_PREC_FP64 && !c.anchor_mode) {
+      (void)hipGetLastError();
+      return collide_whole(p, c, n_cells, s);
+    }
+    HIP_TRY(e);
   } else if (!fit_workspace(p, n_cells, ws_acc->bytes, ws_x->bytes, c, &pass)) {
     // no workspace yet and none can be made: the whole matrix in FP64, written over the right side in place
     if (c.anchor_mode || !in_place)
       return fail(SIS_E_UNSUPPORTED, "no workspace for this contraction while the stream is capturing: run it once before");
-    sis::GemmArgs g{};
-    g.X = h;
-    g.op64 = p->op;
-    g.acc = rhs;
-    g.M = n_cells;
-    g.N = g.K = p->ndof;
-    g.splits = 1;
-    g.tile = n_cells >= 256 ? 0 : 1;
-    HIP_TRY(sis::launch_gemm(g, s));
-    sis::FinishArgs f = finish_args(p, n_cells, h, dU, delta, flow, project, rhs, lh, amom, cell_active, 0, nullptr,
-                                    nullptr);
-    f.splits = 1;
-    f.acc = rhs;
-    HIP_TRY(sis::launch_finish(f, s));
-    return SIS_OK;
+    return collide_whole(p, c, n_cells, s);
   }
   if (capturing) ws_acc->captured = ws_x->captured = true;
   for (int64_t c0 = 0; c0 < n_cells; c0 += pass)
@@ -1484,13 +1495,20 @@ sis_status build_velocity_tables(sis_plan* p, hipStream_t stream) {
   return SIS_OK;
 }
 
-// The operator on the reflection classes of the stored rows (see sis::SymMap).
+// The operator on the reflection classes of the stored rows (see sis::SymMap).  Where the device has no room
+// for the blocks beside the matrix (polar grids of more than 150 000 velocities) there are none.
 sis_status build_class_operator(sis_plan* p, hipStream_t stream) {
   const int cart[3] = {p->n, p->d2, p->d3}, pol[3] = {p->n_vr, p->n_th, p->n_vz};
   const bool cart_m[3] = {true, p->parity < 2, p->parity < 1}, pol_m[3] = {false, true, false};
   if (!sis::make_sym_map(p->sym, p->nsp, p->polar ? pol : cart, p->polar ? pol_m : cart_m))
     return fail(SIS_E_UNSUPPORTED, "velocity grid too large for the contraction's index arithmetic");
-  HIP_TRY(dmalloc(&p->opb, static_cast<size_t>(p->nb()) * p->sym.kb * p->sym.ld));
+  const hipError_t e = dmalloc(&p->opb, static_cast<size_t>(p->nb()) * p->sym.kb * p->sym.ld);
+  if (e == hipErrorOutOfMemory) {   // the plan goes on with the whole matrix
+    p->opb = nullptr;
+    (void)hipGetLastError();
+    return SIS_OK;
+  }
+  HIP_TRY(e);
   HIP_TRY(sis::launch_class_operator(p->sym, p->op, p->opb, stream));
   return SIS_OK;
 }
@@ -2294,14 +2312,15 @@ sis_status create_polar_plan(const sis_velocity_desc* desc, hipStream_t stream, 
     return fail(SIS_E_INVALID, "polar grid: n_vr n_th n_vz must be even");
   }
   POL_TRY(sis::launch_gemm(g, stream));
-  if (sis_status st = build_class_operator(p, stream)) {
-    cleanup();
+  POL_TRY(hipStreamSynchronize(stream));
+  cleanup();   // before the blocks: up to 40 GB
+#undef POL_TRY
+  sis_status st = build_class_operator(p, stream);
+  if (st == SIS_OK && hipStreamSynchronize(stream) != hipSuccess) st = fail(SIS_E_DEVICE, "operator blocks");
+  if (st != SIS_OK) {
     delete p;
     return st;
   }
-  POL_TRY(hipStreamSynchronize(stream));
-  cleanup();
-#undef POL_TRY
   auto t2 = std::chrono::steady_clock::now();
   p->host_s = std::chrono::duration<double>(t1 - t0).count();
   p->dev_s = std::chrono::duration<double>(t2 - t1).count();
@@ -2807,6 +2826,8 @@ sis_status sis_plan_tables(sis_plan_t p, double* v1d, double* feq, double* nu, d
 sis_status sis_plan_set_precision(sis_plan_t p, int32_t precision, hipStream_t stream) {
   if (sis_status st = check_plan(p)) return st;
   const int64_t rows = static_cast<int64_t>(p->nb()) * p->sym.kb;
+  if (precision >= SIS_PREC_FP32 && precision <= SIS_PREC_BF16 && !p->opb)
+    return fail(SIS_E_OOM, "no device memory for the operator's blocks");
   if (precision == SIS_PREC_FP64) {
   } else if (precision == SIS_PREC_FP32) {
     if (!p->op32) {
@@ -3013,6 +3034,7 @@ sis_status sis_collide_noalloc(sis_plan_t p, int64_t n_cells, const double* h, c
   // the plan's configuration for this shape (tuned by earlier sis_collide calls, else the
   // default heuristic); no tuning here, since tuning allocates
   CollideArgs c{h, dU, delta, flow, project, rhs_out, lh_out, amom_out, nullptr, p->precision, 0, nullptr, nullptr, 0, 0};
+  if (!p->opb) return collide_whole(p, c, n_cells, stream);
   gemm_config(p, n_cells, c.precision, &c.tile, &c.splits);
   // FP32: 4 bytes per unknown; the bf16 forms: 4 bytes per padded unknown (pair layout)
   if (c.precision != SIS_PREC_FP64) {
@@ -3466,7 +3488,7 @@ sis_status sis_state_create(sis_plan_t p, sis_geom_t g, const sis_solve_opts* o,
     ST_TRY(dmalloc(&b->bar, 4));
     ST_TRY(b->ws_acc.ensure(static_cast<size_t>(sp) * nc * n3 * 8));
   }
-  if (!b->persistent) {
+  if (!b->persistent && p->opb) {
     // contraction configurations of this shape (FP64 and the plan precision)
     if (sis_status st = tune_gemm(p, nc, SIS_PREC_FP64, b->h, &b->ws_acc, &b->ws_x, stream)) { delete b; return st; }
     if (p->precision != SIS_PREC_FP64)

@@ -185,3 +185,62 @@ def test_fixed_workspace_at_the_edges_of_its_passes(nc):
     p.collide_noalloc(h, delta, rhs)
     p.collide(h, delta, ref)
     assert torch.equal(rhs, ref)
+
+
+def leave(free_bytes):
+    """Tensors that hold the device's memory but for free_bytes (the first leaves more than it is asked to, and
+    others may come from the caching allocator's own blocks)."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold = []
+    for _ in range(20):
+        spare = torch.cuda.mem_get_info()[0] - free_bytes
+        if spare < 2 ** 25:
+            break
+        hold.append(torch.empty(spare, dtype=torch.uint8, device=DEV))
+    return hold
+
+
+def test_short_memory():
+    """A plan of 16 384 velocities -- 2.15 GB of matrix, 1.07 of blocks -- with 2.45 GB free: the matrix alone serves
+    every FP64 call, as it did before there were blocks; the low precisions, made from the blocks, say so.  Then, with
+    what is left, a batch whose class rows and sums take 0.4 GB each: FP64 goes by the whole matrix in place."""
+    polar = dict(n_vr=16, vr_max=4.0, n_th=32, n_vz=32)
+    ref = sis.Plan(0, 4.0, n_pad=8, m_angle=2, polar=polar)
+    batch, cells = sis.Plan(8, 5.0, m_angle=2, parity=1), 200_000
+    batch.set_contraction_config(cells, 128, 16, 1)
+    hb, db = rnd(1, cells, batch.n_dof), torch.ones(cells, dtype=torch.float64, device=DEV)
+    rb, rb2 = torch.full_like(hb, np.nan), torch.full_like(hb, np.nan)
+    hold = leave(2_450_000_000)
+    try:
+        before = torch.cuda.mem_get_info()[0]
+        p = sis.Plan(0, 4.0, n_pad=8, m_angle=2, polar=polar)
+        left = torch.cuda.mem_get_info()[0]
+        assert before - left < 1.2 * 8 * 16_384 ** 2 and left < 700_000_000
+        batch.collide(hb, db, rb)
+        torch.cuda.synchronize()
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+    batch.collide(hb, db, rb2)
+    assert (rb - rb2).abs().max() <= 1e-12 * rb2.abs().max()
+    for nc in (5, 300):
+        h, delta, dU = rnd(nc, nc, p.n_dof), rnd(nc + 1, nc).abs() + 0.5, rnd(nc + 2, nc)
+        for call in ("collide", "collide_noalloc"):
+            out = []
+            for q in (ref, p):
+                rhs, am = torch.full_like(h, np.nan), torch.full((nc, 4), np.nan, dtype=torch.float64, device=DEV)
+                getattr(q, call)(h, delta, rhs, dU=dU, amom_out=am)
+                out.append((rhs, am))
+            assert all((a - b).abs().max() <= 1e-12 * a.abs().max() for a, b in zip(*out)), (nc, call)
+    res = []
+    for q in (ref, p):
+        s = sis.State(q, sis.Geometry(q, [np.linspace(0.1, 1.0, 9)], [1.0], [1], kind="tube"), eps=0.0)
+        s.step(6)
+        res.append(s.results())
+        s.close()
+    for k in ("U", "q"):
+        assert np.abs(res[0][k] - res[1][k]).max() <= 1e-11 * np.abs(res[0][k]).max(), k
+    with pytest.raises(sis.SisError) as e:
+        p.set_precision("fp32")
+    assert e.value.code == -4
