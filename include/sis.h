@@ -505,7 +505,7 @@ sis_status sis_solve(sis_plan_t plan, sis_geom_t geom, const sis_solve_opts* opt
  * per-case flow rates / convergence flags, plus the captured graph of one
  * iteration.  Created with h = 0.  Owns ~2 cells*n3*8 bytes (4 with anchors) and
  * the contraction's workspace (the class rows and split-K sums of a pass of cells:
- * at most 2 GiB and 4 GiB).
+ * at most 2 GiB and 4 GiB; where they find no room FP64 plans apply the whole matrix in place).
  * sis_state_step enqueues n_iters iterations on `stream` (asynchronous);
  * converged cases are frozen by the kernels themselves.
  * sis_state_poll synchronises `stream` and returns the number of cases still

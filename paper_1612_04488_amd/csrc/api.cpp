@@ -455,7 +455,7 @@ void set_gemm_operands(const sis_plan* p, int precision, int tile, const double*
 // class rows the launch that writes them (so that timing noise
 // does not flip between near-equal configurations).  Not
 // callable while `s` is capturing.  Candidates whose split-K partials would
-// exceed 4 GiB are skipped.
+// exceed 4 GiB are skipped, and in FP64 those that find no room.
 sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* h, Scratch* ws_acc, Scratch* ws_x,
                      hipStream_t s) {
   const auto key = std::make_pair(n_cells, precision);
@@ -464,17 +464,28 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
   const int64_t row = p->row_len();
   sis::GemmArgs g{};
   g.M = M;
-  int dt, ds;
-  choose_gemm(n_cells, p->sym.kb, p->nb(), &dt, &ds);
   std::vector<std::pair<float, std::pair<int, int>>> timed;
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
   hipError_t err = hipSuccess;
+  // FP64 can do without the workspace: what finds no room is not a candidate
+  bool no_room = false;
+  auto room = [&](hipError_t e) {
+    no_room = e == hipErrorOutOfMemory && precision == SIS_PREC_FP64;
+    if (!no_room) return e;
+    (void)hipGetLastError();
+    return hipSuccess;
+  };
   // the class rows, per launch (two timed launches)
   float rows_ms = 0.f;
   if (!own_rows(precision, 0)) {
-    err = ws_x->ensure(class_row_bytes(p, precision) * M);
+    err = room(ws_x->ensure(class_row_bytes(p, precision) * M));
+    if (no_room) {
+      (void)hipEventDestroy(e0);
+      (void)hipEventDestroy(e1);
+      return SIS_OK;
+    }
     for (int r = 0; r < 3 && err == hipSuccess; ++r) {
       if (r == 1) err = hipEventRecord(e0, s);
       if (err == hipSuccess) err = sis::launch_class_rows(p->sym, precision, h, nullptr, nullptr, M, ws_x->p, s);
@@ -499,7 +510,8 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
       if (sp > 1 && sis::gemm_k_per_split(K, sp) < 64) continue;
       const double bytes = static_cast<double>(sp) * M * row * sum_bytes(precision);
       if (bytes > 4.0 * (1 << 30)) continue;
-      err = ws_acc->ensure(static_cast<size_t>(bytes));
+      err = room(ws_acc->ensure(static_cast<size_t>(bytes)));
+      if (no_room) continue;
       if (err != hipSuccess) break;
       set_gemm_operands(p, precision, tiles[ti], h, nullptr, ws_x->p, g);
       g.acc = ws_acc->p;
@@ -519,27 +531,26 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (err != hipSuccess) return fail(SIS_E_DEVICE, "contraction tuning: %s", hipGetErrorString(err));
-  std::pair<int, int> best(dt, ds);
-  if (!timed.empty()) {
-    // each split-K partial beyond the first costs the finish step one more row read per
-    // cell (M x row sums at the ~4 TB/s that the finish step streams): add it to the timing
-    for (auto& c : timed)
-      c.first += static_cast<float>((c.second.second - 1) * static_cast<double>(M) * row * sum_bytes(precision) / 4.0e12 * 1e3);
-    float fastest = timed[0].first;
-    for (const auto& c : timed) fastest = std::min(fastest, c.first);
-    // within 1% of the fastest: fewest split-K partials, then the larger tile, then the faster
-    int best_rows = -1, best_splits = 1 << 30;
-    float best_ms = 0.f;
-    for (const auto& c : timed) {
-      if (c.first > 1.01f * fastest) continue;
-      const int rows = sis::gemm_tile_rows(c.second.first), sp = c.second.second;
-      if (sp < best_splits || (sp == best_splits && rows > best_rows) ||
-          (sp == best_splits && rows == best_rows && c.first < best_ms)) {
-        best_splits = sp;
-        best_rows = rows;
-        best_ms = c.first;
-        best = c.second;
-      }
+  if (timed.empty()) return SIS_OK;   // (no room for any)
+  std::pair<int, int> best;
+  // each split-K partial beyond the first costs the finish step one more row read per
+  // cell (M x row sums at the ~4 TB/s that the finish step streams): add it to the timing
+  for (auto& c : timed)
+    c.first += static_cast<float>((c.second.second - 1) * static_cast<double>(M) * row * sum_bytes(precision) / 4.0e12 * 1e3);
+  float fastest = timed[0].first;
+  for (const auto& c : timed) fastest = std::min(fastest, c.first);
+  // within 1% of the fastest: fewest split-K partials, then the larger tile, then the faster
+  int best_rows = -1, best_splits = 1 << 30;
+  float best_ms = 0.f;
+  for (const auto& c : timed) {
+    if (c.first > 1.01f * fastest) continue;
+    const int rows = sis::gemm_tile_rows(c.second.first), sp = c.second.second;
+    if (sp < best_splits || (sp == best_splits && rows > best_rows) ||
+        (sp == best_splits && rows == best_rows && c.first < best_ms)) {
+      best_splits = sp;
+      best_rows = rows;
+      best_ms = c.first;
+      best = c.second;
     }
   }
   p->gemm_choice[key] = best;
@@ -713,6 +724,8 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
     if (e == hipSuccess) e = ws_x->ensure(x_bytes);
     if (e == hipErrorOutOfMemory && c.precision == SIS_PREC_FP64 && !c.anchor_mode) {
       (void)hipGetLastError();
+      ws_acc->drop();   // (half a workspace is of no use)
+      ws_x->drop();
       return collide_whole(p, c, n_cells, s);
     }
     HIP_TRY(e);
@@ -3495,10 +3508,18 @@ sis_status sis_state_create(sis_plan_t p, sis_geom_t g, const sis_solve_opts* o,
       if (sis_status st = tune_gemm(p, nc, p->precision, b->h, &b->ws_acc, &b->ws_x, stream)) { delete b; return st; }
     // the workspace of both, fixed here: the captured graphs refer to it
     for (const int prec : {static_cast<int>(SIS_PREC_FP64), p->precision}) {
-      const auto [tile, splits] = p->gemm_choice[std::make_pair(nc, prec)];
+      int tile, splits;
+      gemm_config(p, nc, prec, &tile, &splits);
       const int64_t pass = pass_cells(p, nc, prec, splits);
-      ST_TRY(b->ws_acc.ensure(static_cast<size_t>(splits) * pass * p->row_len() * sum_bytes(prec)));
-      if (!own_rows(prec, tile)) ST_TRY(b->ws_x.ensure(class_row_bytes(p, prec) * pass));
+      hipError_t e = b->ws_acc.ensure(static_cast<size_t>(splits) * pass * p->row_len() * sum_bytes(prec));
+      if (e == hipSuccess && !own_rows(prec, tile)) e = b->ws_x.ensure(class_row_bytes(p, prec) * pass);
+      if (e == hipErrorOutOfMemory && p->precision == SIS_PREC_FP64) {   // the whole matrix in place
+        (void)hipGetLastError();
+        b->ws_acc.drop();
+        b->ws_x.drop();
+        break;
+      }
+      ST_TRY(e);
     }
   }
   hipStream_t s = stream;

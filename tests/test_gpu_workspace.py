@@ -244,3 +244,46 @@ def test_short_memory():
     with pytest.raises(sis.SisError) as e:
         p.set_precision("fp32")
     assert e.value.code == -4
+
+
+def test_untuned_batch_that_fills_the_memory():
+    """Batches of more than 4 GiB of sums had neither tuning nor a workspace of their own in FP64.  A pass of their class
+    rows and sums takes 2 GiB each: where that is not free the step, and a state, go by the whole matrix in place."""
+    p = sis.Plan(8, 5.0, m_angle=2)
+    nodes, cases = 200, 5300
+    nc = nodes * cases                                  # 4.34 GB a distribution
+    x = np.linspace(-0.5, 0.0, nodes)
+    geom = sis.Geometry(p, [x] * cases, [1.0] * cases, [1] * cases)
+    h, delta = rnd(1, nc, p.n_dof), torch.ones(nc, dtype=torch.float64, device=DEV)
+    rhs = torch.full_like(h, np.nan)
+    hold = leave(1_000_000_000)
+    try:
+        p.collide(h, delta, rhs)
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] > 900_000_000       # nothing is kept of what did not suffice
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+    at = torch.tensor([0, 1, 127, 128, nc // 2, nc - 1], device=DEV)
+    ref = torch.empty((len(at), p.n_dof), dtype=torch.float64, device=DEV)
+    p.collide(h[at].contiguous(), delta[:len(at)], ref)
+    assert (rhs[at] - ref).abs().max() <= 1e-12 * ref.abs().max() and bool(torch.isfinite(rhs).all())
+    del h, rhs
+    for graph in (True, False):
+        torch.cuda.empty_cache()
+        hold = leave(2 * nc * p.n_dof * 8 + 1_000_000_000)
+        try:
+            s = sis.State(p, geom, eps=0.0, use_graph=graph)
+            s.step(3)
+            res = s.results()
+            s.close()
+        finally:
+            del hold
+            torch.cuda.empty_cache()
+        one = sis.State(p, sis.Geometry(p, [x], [1.0], [1]), eps=0.0)
+        one.step(3)
+        few = one.results()
+        one.close()
+        for k in ("U", "q"):
+            u = np.asarray(res[k]).reshape(cases, nodes)
+            assert np.abs(u - np.asarray(few[k]).reshape(1, nodes)).max() <= 1e-12 * np.abs(few[k]).max(), k
