@@ -44,11 +44,22 @@ PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16x3": 2500.0, "bf16": 2500.0}
 # stands, keyed by (workload, parity, precision, tile rows, split-K, k-stage), with the
 # profile summary that holds the pass; a launch configuration without a recorded pass
 # reports null.
-TRAFFIC_KIB = {}
+COUNTERS = "profiles/cases_class-blocks.md"
+TRAFFIC_KIB = {("duct-ipl081-24v-64x64-6cases", 1, "fp64", 128, 1, 16): (4193604.6 * 2.0, 1327104.0, COUNTERS),
+               ("duct-ipl081-24v-64x64-6cases", 1, "bf16x3", 256, 1, 32): (1115304.7 * 2.0, 663618.6, COUNTERS),
+               ("planar-hs-32v-100cells-8cases", 2, "fp64", 128, 4, 16): (557365.6 * 2.0, 206848.0, COUNTERS),
+               ("planar-hs-32v-100cells-8cases", 2, "bf16x3", 256, 2, 32): (171723.8 * 2.0, 51758.6, COUNTERS),
+               ("mixture-near-hs-24v-101to201nodes-16cases", 2, "fp64", 128, 3, 16): (1668390.4 * 2.0, 391392.0, COUNTERS),
+               ("mixture-near-hs-24v-101to201nodes-16cases", 2, "bf16x3", 256, 2, 32): (357081.7 * 2.0, 130508.0, COUNTERS)}
 # MFMA pipe utilisation of the same configuration from its counter pass:
 # SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE per XCD x 1024 SIMDs), and the shader clock
 # the kernel ran at (GRBM_GUI_ACTIVE per XCD / kernel duration).
-MFMA_BUSY = {}
+MFMA_BUSY = {("duct-ipl081-24v-64x64-6cases", 1, "fp64", 128, 1, 16): (0.929, 2.26),
+             ("duct-ipl081-24v-64x64-6cases", 1, "bf16x3", 256, 1, 32): (0.676, 1.99),
+             ("planar-hs-32v-100cells-8cases", 2, "fp64", 128, 4, 16): (0.898, 2.27),
+             ("planar-hs-32v-100cells-8cases", 2, "bf16x3", 256, 2, 32): (0.652, 2.14),
+             ("mixture-near-hs-24v-101to201nodes-16cases", 2, "fp64", 128, 3, 16): (0.833, 2.11),
+             ("mixture-near-hs-24v-101to201nodes-16cases", 2, "bf16x3", 256, 2, 32): (0.525, 2.10)}
 HBM_GBS = 8000.0
 # worker processes of the CPU baseline: the host's cores, at most the 16 that a
 # one-GPU share of the box holds
