@@ -560,7 +560,7 @@ sis_status tune_gemm(sis_plan* p, int64_t n_cells, int precision, const double* 
   return SIS_OK;
 }
 
-// Arguments of finish_kernel for a contraction of n_cells cells (partial sums set by the caller).
+// Arguments of the finish step for a contraction of n_cells cells (partial sums set by the caller).
 sis::FinishArgs finish_args(const sis_plan* p, int64_t n_cells, const double* h, const double* dU,
                             const double* delta, const int32_t* flow, int project, double* rhs, double* lh,
                             double* amom, const int32_t* cell_active, int anchor_mode, double* xref,
@@ -695,7 +695,7 @@ sis_status run_collide(sis_plan* p, int64_t n_cells, const double* h, const doub
                        double* accref = nullptr, Scratch* ws_acc = nullptr, Scratch* ws_x = nullptr,
                        bool h_is_zero = false) {
   if (h_is_zero) {
-    // L+ h = 0 for h = 0: no contraction; finish_kernel sums no partials (the anchor, if one
+    // L+ h = 0 for h = 0: no contraction; the finish step sums no partials (the anchor, if one
     // is being taken, becomes (0, 0))
     sis::FinishArgs f = finish_args(p, n_cells, h, dU, delta, flow, project, rhs, lh, amom, cell_active,
                                     anchor_mode, xref, accref);

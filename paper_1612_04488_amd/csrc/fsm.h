@@ -81,7 +81,7 @@ hipError_t launch_fsm_class(const FsmClassDims& d, int slab_l1, int64_t n_cells,
 // spectrum X (layout of S, one cell) or X = 1 when X is null:
 //   out[slot[t]][a1][a2][a3] = scale[t] Re sum_l E1(a1, l1) E2(a2, l2) E3(a3, l3) m_t(l) X(l)
 // for the terms t in [t0, t0 + nt), on output nodes given by the factor matrices
-// E1 [m1][L], E2 [m2][L], E3 [m3][Q] (E3 doubled for l3 > 0 as in FsmFactors).
+// E1 [m1][L], E2 [m2][L], E3 [m3][Q] (E3 doubled for l3 > 0: the conjugate half).
 // Terms with slot[t] < 0 are skipped.
 struct FsmTableArgs {
   FsmDims d;

@@ -1999,7 +1999,7 @@ __global__ __launch_bounds__(256) void moments_kernel(int n3, int nsp, double ms
 // One workgroup per case.  The march from the wall is a serial recurrence, so one lane
 // carries it, and nothing but it: the whole workgroup stages the nodes' equations into LDS
 // with the inverses of their diagonals, and takes the outputs and the flow-rate integrals
-// from the lane's values afterwards.  101 nodes: 9 us, and 26 with all of it on the lane.
+// from the lane's values afterwards.  101 nodes: 8 us (7 without flow rates), and 26 with all of it on the lane.
 constexpr int kDiffChunk = 256;
 
 __device__ __forceinline__ void diffusion1d_case(const DiffusionArgs& a, int cs) {
