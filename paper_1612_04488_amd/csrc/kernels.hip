@@ -46,10 +46,12 @@ __device__ __forceinline__ double div_known(double num, double den, double inv) 
 }
 
 // Block-wide sum of K values per thread, fixed order.  Result in out[] for all threads.
-template <int K>
+// NT: the workgroup's threads where they are known (0: not): the reads of the waves' sums are then in flight
+// together (a finish step of 17 rows of 512 with the projection: 15.8 -> 14.4 us with its contraction).
+template <int K, int NT = 0>
 __device__ inline void block_sum(double (&v)[K], double* sh /* >= 4*K */) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nw = (blockDim.x + 63) >> 6;
+  const int nw = NT ? NT / 64 : (blockDim.x + 63) >> 6;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const double s = wave_sum(v[k]);
@@ -59,6 +61,7 @@ __device__ inline void block_sum(double (&v)[K], double* sh /* >= 4*K */) {
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     double s = 0.0;
+#pragma unroll
     for (int w = 0; w < nw; ++w) s += sh[w * K + k];
     v[k] = s;
   }
@@ -1393,10 +1396,10 @@ __device__ __forceinline__ void finish_tail(const FinishArgs& a, int64_t c, doub
   __shared__ double sh[NT / 64 * 9];
   __shared__ double coef[5];
   if (a.project) {
-    block_sum<9>(m, sh);
+    block_sum<9, NT>(m, sh);
   } else {   // the last four only: the sums across lanes are a tenth of a short row's time
     double am[4] = {m[5], m[6], m[7], m[8]};
-    block_sum<4>(am, sh);
+    block_sum<4, NT>(am, sh);
     for (int k = 0; k < 4; ++k) m[5 + k] = am[k];
   }
   if (a.project) {
